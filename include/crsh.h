@@ -482,8 +482,9 @@ typedef struct crsh_frame_meta {
  * the plain calls.  top_item_capacity bounds the (top node, mesh) items of
  * one top-level pass: the sum over the frames that share a top level of
  * top nodes x meshes.  bundle / merge / levels shape every frame's
- * hierarchy; hit_block (64, 128 or 256) is the workgroup size of the final
- * tests.  ws: crsh_batch_ws_size() bytes. */
+ * hierarchy; hit_block (64, 128 or 256) sets how many level-1 pairs a
+ * workgroup of the final tests takes at a time (16 x hit_block at most); it
+ * never changes a result.  ws: crsh_batch_ws_size() bytes. */
 typedef struct crsh_batch {
     uint32_t n_frames;                  /* 1 .. CRSH_MAX_FRAMES */
     const crsh_frame *frames;

@@ -31,7 +31,8 @@ def top_nodes_bound(max_rays, B, F, levels):
 class DeviceBatch:
     """The frames (workloads) of one batch, uploaded once, with every device
     array the batched pipeline writes.  All frames use the hierarchy shape
-    (B, F, levels); hit_block is the workgroup size of the final tests."""
+    (B, F, levels); hit_block sets the pairs a workgroup of the final tests
+    takes at a time."""
 
     def __init__(self, wls, B, F, levels, hit_block=256, pair_capacity=1 << 22, keep_levels=False,
                  leaf_hit=False, ray_capacity=None, device="cuda"):
@@ -115,8 +116,8 @@ class DeviceBatch:
         self.reshape(self.B, self.F, self.levels, self.hit_block, pair_capacity)
 
     def reshape(self, B, F, levels, hit_block=None, pair_capacity=None):
-        """Change the hierarchy shape (and workgroup size of the final tests)
-        keeping the uploaded frames; node and pair storage are resized."""
+        """Change the hierarchy shape (and hit_block) keeping the uploaded frames;
+        node and pair storage are resized."""
         self.B, self.F, self.levels = int(B), int(F), int(levels)
         if hit_block is not None:
             self.hit_block = int(hit_block)

@@ -107,6 +107,41 @@ __device__ __forceinline__ T wave_sum(T v)
     return v;
 }
 
+// One step of a lane-shift sequence: the value CTRL moves to this lane, or
+// `none` where it moves none (ROWS: the rows of 16 lanes that take one).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_from(uint32_t none, uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, CTRL, ROWS, 0xF, false);
+}
+
+// inclusive prefix sum over the wave in six lane-shift additions (row_shr
+// 1, 2, 4, 8, then row 0 to 1 and 2 to 3, then rows 0-1 to 2-3)
+__device__ __forceinline__ uint32_t wave_scan_dpp(uint32_t v)
+{
+    v += dpp_from<0x111, 0xF>(0u, v);
+    v += dpp_from<0x112, 0xF>(0u, v);
+    v += dpp_from<0x114, 0xF>(0u, v);
+    v += dpp_from<0x118, 0xF>(0u, v);
+    v += dpp_from<0x142, 0xA>(0u, v);
+    v += dpp_from<0x143, 0xC>(0u, v);
+    return v;
+}
+
+// the wave's values combined by the associative, commutative `op` (none: its
+// identity), by the same shifts; the result is wave-uniform
+template <typename Op>
+__device__ __forceinline__ uint32_t wave_reduce(uint32_t v, uint32_t none, Op op)
+{
+    v = op(v, dpp_from<0x111, 0xF>(none, v));
+    v = op(v, dpp_from<0x112, 0xF>(none, v));
+    v = op(v, dpp_from<0x114, 0xF>(none, v));
+    v = op(v, dpp_from<0x118, 0xF>(none, v));
+    v = op(v, dpp_from<0x142, 0xA>(none, v));
+    v = op(v, dpp_from<0x143, 0xC>(none, v));
+    return __builtin_amdgcn_readlane(v, WAVE - 1);
+}
+
 // Exclusive block scan of one value per thread; returns the exclusive prefix
 // and the block total.  scratch: NWAVES entries of LDS.
 template <typename T, int NWAVES>
@@ -237,36 +272,54 @@ __host__ __device__ constexpr size_t align256(size_t x) { return (x + 255) & ~(s
 size_t sort_ws_bytes(uint32_t cap);
 size_t hash_ws_bytes(uint64_t pixels);
 size_t trav_ws_bytes(uint32_t m, uint32_t node_cap, uint64_t top_items, uint64_t max_pairs);
-// Final-test workspace: packed triangles (48 B each), then per ray slot the
-// packed ray (32 B: origin and direction in two arrays of 16 B per slot) and
-// a closest-hit key (8 B).  Slots: one per sorted ray in
-// the plain form; in the batched form B per level-1 node, at most the rays
-// plus B - 1 per frame.
+// Final-test workspace: packed triangles (48 B each) and their filter entries
+// (48 B each, one more for padding), then per ray slot the packed ray (48 B:
+// three arrays of 16 B per slot) and a closest-hit key (8 B).  Slots: one per
+// sorted ray in the plain form; in the batched form B per level-1 node, at
+// most the rays plus B - 1 per frame.
 size_t hit_ws_bytes(uint32_t m, uint32_t slots);
 // bounds of the final tests' 32-bit byte offsets (16 B per ray slot in each
-// of two arrays, 48 B per triangle)
+// of its arrays, 48 B per triangle)
 #define CRSH_HIT_MAX_SLOTS (1u << 27)
 #define CRSH_HIT_MAX_TRIS (1u << 26)
 constexpr uint32_t hit_slots(uint32_t rays, bool batch)
 {
     return batch ? rays + CRSH_MAX_FRAMES * (CRSH_MAX_BUNDLE - 1) : rays;
 }
+struct hit_tris_ws {
+    float4 *tri;                 // v0, e1, e2
+    float4 *ftri;                // the filter's vectors and error bound
+};
+inline size_t hit_tris_bytes(uint32_t m) { return align256((size_t)m * 48) + align256(((size_t)m + 1) * 48); }
+inline hit_tris_ws carve_hit_tris(void *at, uint32_t m)
+{
+    return hit_tris_ws{(float4 *)at, (float4 *)((char *)at + align256((size_t)m * 48))};
+}
 struct hit_slots_ws {
     float4 *org;                 // per slot: origin, tmax
-    float *dir;                  // per slot: direction (12 bytes)
+    float4 *dir;                 // per slot: direction, its length
+    float4 *mom;                 // per slot: origin x direction, |origin| |direction|
     unsigned long long *keys;    // per slot (batched form)
+    uint64_t *part;              // per workgroup of k_hit: its three counts
     uint32_t slots;
 };
+constexpr uint32_t HIT_MAX_GRID = 4096;    // most workgroups of k_hit
 inline hit_slots_ws carve_hit_slots(void *at, uint32_t slots)
 {
+    const size_t a = align256((size_t)slots * 16);
     hit_slots_ws h;
     h.org = (float4 *)at;
-    h.dir = (float *)((char *)at + align256((size_t)slots * 16));
-    h.keys = (unsigned long long *)((char *)h.dir + align256((size_t)slots * 16));
+    h.dir = (float4 *)((char *)at + a);
+    h.mom = (float4 *)((char *)at + 2 * a);
+    h.keys = (unsigned long long *)((char *)at + 3 * a);
+    h.part = (uint64_t *)((char *)at + 3 * a + align256((size_t)slots * 8));
     h.slots = slots;
     return h;
 }
-inline size_t hit_slots_bytes(uint32_t slots) { return 2 * align256((size_t)slots * 16) + align256((size_t)slots * 8); }
+inline size_t hit_slots_bytes(uint32_t slots)
+{
+    return 3 * align256((size_t)slots * 16) + align256((size_t)slots * 8) + (size_t)HIT_MAX_GRID * 3 * 8;
+}
 
 // Stage launchers shared by the plain entry points (bd == nullptr) and the
 // batched form (bd: the batch's device view, frame-aware kernels).
@@ -297,19 +350,23 @@ crsh_status leaf_hit_launch(const crsh_rays *sorted, const uint32_t *sorted_ids,
 crsh_status hit_check(const crsh_rays *sorted, const uint32_t *sorted_ids, int32_t bundle, const crsh_pairs *level1,
                       const crsh_scene *scene, crsh_hits *hits, crsh_meta *meta, void *ws, int32_t hit_block,
                       const char *who);
-void hit_prep_launch(const crsh_scene *scene, float4 *tri, hipStream_t stream);
-void hit_pairs_launch(const crsh_rays *sorted, const float4 *tri, const hit_slots_ws &hs, const crsh_pairs *level1,
+void hit_pack_launch(const crsh_scene *scene, const hit_tris_ws &tri, const crsh_rays *sorted,
+                     const hit_slots_ws &hs, int32_t bundle, const crsh_meta *meta, const batch_dev *bd,
+                     hipStream_t stream);
+uint32_t hit_pairs_launch(const hit_tris_ws &tri, const hit_slots_ws &hs, const crsh_pairs *level1,
                       int32_t bundle, const crsh_scene *scene, float t_min, crsh_hits *hits, crsh_meta *meta,
                       const batch_dev *bd, int32_t hit_block, hipStream_t stream, bool packed = false,
                       uint32_t tri_base = 0);
 // final tests of the level-1 pairs given as level-2 pairs and level-1 pass
-// masks (the fused last level); rays packed by hit_pairs_launch first
+// masks (the fused last level); rays packed by hit_pack_launch first
 void hit_masked_launch(const crsh_rays *sorted, const float4 *tri, const hit_slots_ws &hs, const crsh_pairs *level2,
                        const uint32_t *mask, int32_t merge, int32_t bundle, const crsh_scene *scene, float t_min,
                        crsh_hits *hits, crsh_meta *meta, const batch_dev *bd, int32_t hit_block, hipStream_t stream);
+// parts: workgroups of the k_hit launch before (hit_pairs_launch's result)
 void hit_final_launch(const crsh_rays *sorted, const uint32_t *sorted_ids, const float4 *tri,
                       const hit_slots_ws &hs, int32_t bundle, const crsh_scene *scene, float t_min,
-                      crsh_hits *hits, crsh_meta *meta, const batch_dev *bd, hipStream_t stream);
+                      crsh_hits *hits, crsh_meta *meta, const batch_dev *bd, uint32_t parts,
+                      hipStream_t stream);
 void tri_spheres_launch(const crsh_scene *scene, uint32_t b, uint32_t e, float4 *out, hipStream_t stream);
 size_t leaf_hit_ws_bytes(uint32_t m, uint32_t node_cap, uint64_t level2_cap, uint32_t rays);
 size_t sort_chunked_ws_bytes(uint32_t cap);

@@ -1,45 +1,83 @@
 // Stage 5: final intersection tests and closest hit (Sec. 3.3.8).
 //
-// k_hit_prep   triangles repacked as 3 x float4 (v0, e1 = v1 - v0,
-//              e2 = v2 - v0): one 48-byte fetch per test instead of nine
-//              scattered loads; e1, e2 are the same single roundings the
-//              test would make.
-// k_hit        persistent waves over the level-1 pairs; a group of G lanes
-//              (G = bundle rounded up to a power of two) takes one pair, one
-//              lane per ray of its leaf, so a leaf's rays are read
-//              contiguously from the sorted ray arrays.  A hit lowers the
-//              ray's 64-bit (order-mapped t, triangle) key with an atomic
+// k_hit_pack   ray slots (below), and triangles repacked twice: 3 x float4
+//              (v0, e1 = v1 - v0, e2 = v2 - v0; e1, e2 are the same single
+//              roundings the test would make) for the test itself, and
+//              3 x float4 of the filter (below) with its error bound.
+// k_hit        persistent workgroups over the level-1 pairs: a chunk of pairs
+//              is binned by leaf in LDS, each leaf's rays are tested against
+//              its triangles with matrix instructions, and what that filter
+//              cannot reject goes through the test as written.  A hit lowers
+//              the ray's 64-bit (order-mapped t, triangle) key with an atomic
 //              minimum: the closest hit, ties to the lower triangle id.
 // k_hit_final  one thread per sorted ray: decode the key, recompute u, v with
 //              the same test, write the result at the ray id.
-// Ray slots: k_hit reads the rays of leaf l at slots l * B + j, j < B, of two
-// packed arrays: (origin, tmax), 16 bytes a slot, and the direction, 12
-// bytes a slot; the interval start t_min is the frame's.  In the plain form
-// slot s is sorted ray s.  In the batched form a frame's rays are bundled B
-// at a time from its own first ray, so only a frame's last leaf can hold
-// fewer than B rays; its slots are padded (zeros, a marker in place of tmax)
-// and the closest-hit keys are kept by slot, so the pair loop finds a ray
-// with no per-leaf lookup.  k_hit_final maps each sorted ray back to its
-// slot through its frame's first leaf and first ray.
+// Ray slots: k_hit reads the rays of leaf l at slots l * B + j, j < B, of
+// three packed arrays of 16 bytes a slot: (origin, tmax), (direction, its
+// length) and (origin x direction, |origin| |direction|); the interval start
+// t_min is the frame's.  In the plain form slot s is sorted ray s.  In the
+// batched form a frame's rays are bundled B at a time from its own first ray,
+// so only a frame's last leaf can hold fewer than B rays; its slots are padded
+// (zeros, a length of -1) and the closest-hit keys are kept by slot, so the
+// pair loop finds a ray with no per-leaf lookup.  k_hit_final maps each
+// sorted ray back to its slot through its frame's first leaf and first ray.
 #include "batch.hpp"
 #include "intersect.hpp"
 
 namespace crsh {
 
-__global__ void k_hit_prep(const float *__restrict__ v0x, const float *__restrict__ v0y,
-                           const float *__restrict__ v0z, const float *__restrict__ v1x,
-                           const float *__restrict__ v1y, const float *__restrict__ v1z,
-                           const float *__restrict__ v2x, const float *__restrict__ v2y,
-                           const float *__restrict__ v2z, uint32_t m, float4 *tri)
+// The filter.  The test accepts u = a / det in [0, 1] with
+// a = (O - v0) . (D x e2) and det = e1 . (D x e2), i.e. |2 a - det| <= |det|.
+// With the ray's moment M = O x D both are sums of products of one ray vector
+// and one triangle vector,
+//     2 a - det = M . (2 e2) - D . (2 e2 x v0 + e2 x e1),   det = D . (e2 x e1),
+// so a leaf's rays against its triangles are a small matrix product.  A pair
+// is rejected when |2 a - det| - |det| > T with
+//     T = 2^-17 |e2| |D| (|O| + |v0| + |e1|).
+// Error bound (u = 2^-24, first order): the two forms above come out within
+// u |e2||D| (19 |O| + 21 |v0| + 10.5 |e1|) and 6.5 u |e1||e2||D|, the test's
+// own a and det within 7.5 u |e2||D| (|O| + |v0|) and 6.5 u |e1||e2||D|, and
+// 16 u |e1||e2||D| more keeps a / det 2^-21 away from 0 and 1, so that the
+// rounded quotient falls on the same side: together at most
+// u |e2||D| (34 |O| + 36 |v0| + 46 |e1|), against T's 128 u.  Where a length
+// lies outside [2^-10, 2^20] (direction), above 2^20 (edges) or above 2^40
+// (origin, v0), or is a NaN, a product could overflow or underflow: such a
+// triangle has zero vectors and a large T, such a ray a mark, and neither is
+// ever rejected.  All filter arithmetic is therefore on finite values.
+constexpr float FLT_REL = 0x1p-17f;
+constexpr float FLT_TINY = 0x1p-40f;       // added to lengths: their squares may underflow
+constexpr float FLT_KEEP = -2.0f;          // |O||D| of a ray that the filter may not reject
+
+// Per triangle: (2 e2, E0), (-(2 e2 x v0 + e2 x e1), E1), (e2 x e1, 0) with
+// T = E0 |O||D| + E1 |D|.  Entry m pads a leaf's last triangles: its T is
+// negative for every ray (rejected).
+struct tri_verts {
+    const float *v[9];
+};
+__device__ __forceinline__ void put_tri(const tri_verts &V, uint32_t t, uint32_t m, const hit_tris_ws &out)
 {
-    for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < m; t += gridDim.x * blockDim.x) {
-        float ax = v0x[t], ay = v0y[t], az = v0z[t];
-        float e1x = v1x[t] - ax, e1y = v1y[t] - ay, e1z = v1z[t] - az;
-        float e2x = v2x[t] - ax, e2y = v2y[t] - ay, e2z = v2z[t] - az;
-        tri[3 * t + 0] = make_float4(ax, ay, az, e1x);
-        tri[3 * t + 1] = make_float4(e1y, e1z, e2x, e2y);
-        tri[3 * t + 2] = make_float4(e2z, 0.0f, 0.0f, 0.0f);
+    float4 *const tri = out.tri + 3 * (size_t)t, *const ftri = out.ftri + 3 * (size_t)t;
+    if (t == m) {
+        ftri[0] = make_float4(0.0f, 0.0f, 0.0f, -1.0f);
+        ftri[1] = make_float4(0.0f, 0.0f, 0.0f, 0x1p-60f);
+        ftri[2] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        return;
     }
+    const f3 a = mk(V.v[0][t], V.v[1][t], V.v[2][t]);
+    const f3 e1 = mk(V.v[3][t], V.v[4][t], V.v[5][t]) - a;
+    const f3 e2 = mk(V.v[6][t], V.v[7][t], V.v[8][t]) - a;
+    tri[0] = make_float4(a.x, a.y, a.z, e1.x);
+    tri[1] = make_float4(e1.y, e1.z, e2.x, e2.y);
+    tri[2] = make_float4(e2.z, 0.0f, 0.0f, 0.0f);
+    const float la = len(a) + FLT_TINY, l1 = len(e1) + FLT_TINY, l2 = len(e2) + FLT_TINY;
+    const bool ok = la <= 0x1p40f && l1 <= 0x1p20f && l2 <= 0x1p20f;
+    const f3 z = mk(0.0f, 0.0f, 0.0f);
+    const f3 n = ok ? cross(e2, e1) : z;
+    const f3 w = ok ? cross(e2, a) * 2.0f + n : z;
+    const f3 e = ok ? e2 * 2.0f : z;
+    ftri[0] = make_float4(e.x, e.y, e.z, ok ? FLT_REL * l2 : 0.0f);
+    ftri[1] = make_float4(-w.x, -w.y, -w.z, ok ? FLT_REL * l2 * (la + l1) : 0x1p60f);
+    ftri[2] = make_float4(n.x, n.y, n.z, 0.0f);
 }
 
 struct sorted_rays {
@@ -58,58 +96,50 @@ __device__ __forceinline__ uint32_t batch_slots(const crsh_meta *meta, uint32_t 
     return (uint32_t)(ns < slot_cap ? ns : slot_cap);
 }
 
-// Plain form: sorted rays repacked as (origin, tmax), 16 bytes a slot, and
-// the direction, 12 bytes a slot (the interval start is the frame's, a
-// kernel argument): a 16-byte and a 12-byte load per test instead of seven
-// scattered ones, and the 16 rays of a leaf are 256 and 192 contiguous
-// bytes.
-__global__ void k_hit_rays(sorted_rays R, const crsh_meta *meta, uint32_t cap, float4 *org, float *dir3)
+// A ray's slot: origin and tmax; direction and the |D| of the filter's T;
+// O x D and the |O||D| of T, or FLT_KEEP in its place.
+__device__ __forceinline__ void put_slot(const hit_slots_ws &hs, uint32_t p, f3 O, f3 D, float tmax)
 {
-    const uint32_t n = min(meta->n_rays, cap);
-    for (uint32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < n; s += gridDim.x * blockDim.x) {
-        org[s] = make_float4(R.ox[s], R.oy[s], R.oz[s], R.tmax[s]);
-        dir3[3 * (size_t)s + 0] = R.dx[s];
-        dir3[3 * (size_t)s + 1] = R.dy[s];
-        dir3[3 * (size_t)s + 2] = R.dz[s];
-    }
+    const float lo = len(O) + FLT_TINY, ld = len(D);
+    const bool ok = lo <= 0x1p40f && ld <= 0x1p20f && ld >= 0x1p-10f;
+    const f3 M = cross(O, D);
+    hs.org[p] = make_float4(O.x, O.y, O.z, tmax);
+    hs.dir[p] = make_float4(D.x, D.y, D.z, ok ? ld : 1.0f);
+    hs.mom[p] = make_float4(M.x, M.y, M.z, ok ? lo * ld : FLT_KEEP);
 }
 
-__device__ __forceinline__ f3 buf_load3(__amdgpu_buffer_rsrc_t r, uint32_t off)
+// Triangles and ray slots packed, in one launch.  Plain form: slot s is sorted
+// ray s.  Batched form: slot p = leaf * B + j holds ray j of level-1 node
+// `leaf` (first ray and count as the build recorded them), or padding; every
+// slot's closest-hit key starts at all ones.
+template <bool BATCH>
+__global__ void k_hit_pack(tri_verts V, uint32_t m, hit_tris_ws tri, sorted_rays R, const crsh_meta *meta,
+                           uint32_t ray_cap, uint32_t B, batch_dev bd, hit_slots_ws hs)
 {
-    typedef float v3f __attribute__((ext_vector_type(3)));
-    const v3f v = __builtin_amdgcn_raw_buffer_load_b96(r, off, 0, 0);
-    return mk(v.x, v.y, v.z);
-}
-
-// Batched form: slot p = leaf * B + j holds ray j of level-1 node `leaf`
-// (first ray and count as the build recorded them), or zeros and the padding
-// marker; every slot's closest-hit key starts at all ones.
-__global__ void k_hit_rays_batch(sorted_rays R, const crsh_meta *meta, uint32_t ray_cap, uint32_t B,
-                                 uint32_t slot_cap, batch_dev bd, float4 *org, float *dir3,
-                                 unsigned long long *keys)
-{
+    const uint32_t stride = gridDim.x * blockDim.x, gid = blockIdx.x * blockDim.x + threadIdx.x;
     const uint32_t n = min(meta->n_rays, ray_cap);
-    const uint32_t ns = batch_slots(meta, B, slot_cap);
-    for (uint32_t p = blockIdx.x * blockDim.x + threadIdx.x; p < ns; p += gridDim.x * blockDim.x) {
-        const uint32_t leaf = p / B;
-        const uint32_t j = p - leaf * B;
-        const uint32_t info = bd.node_info[leaf];
-        const uint32_t f = info >> INFO_FRAME_SHIFT;
-        const uint32_t s = bd.node_first[leaf] + j;
-        float dx = 0.0f, dy = 0.0f, dz = 0.0f;
-        if (j < (info & INFO_COUNT_MASK) && s < n && f < bd.n_frames) {
-            org[p] = make_float4(R.ox[s], R.oy[s], R.oz[s], slot_tmax(R.tmax[s]));
-            dx = R.dx[s];
-            dy = R.dy[s];
-            dz = R.dz[s];
-        } else {
-            org[p] = make_float4(0.0f, 0.0f, 0.0f, __uint_as_float(PAD_SLOT));
+    const uint32_t ns = BATCH ? batch_slots(meta, B, hs.slots) : n;
+    for (uint32_t p = gid; p < ns; p += stride) {
+        uint32_t s = p;
+        bool ok = true;
+        if constexpr (BATCH) {
+            const uint32_t leaf = p / B;
+            const uint32_t j = p - leaf * B;
+            const uint32_t info = bd.node_info[leaf];
+            s = bd.node_first[leaf] + j;
+            ok = j < (info & INFO_COUNT_MASK) && s < n && info >> INFO_FRAME_SHIFT < bd.n_frames;
+            hs.keys[p] = ~0ull;
         }
-        dir3[3 * (size_t)p + 0] = dx;
-        dir3[3 * (size_t)p + 1] = dy;
-        dir3[3 * (size_t)p + 2] = dz;
-        keys[p] = ~0ull;
+        if (ok) {
+            put_slot(hs, p, mk(R.ox[s], R.oy[s], R.oz[s]), mk(R.dx[s], R.dy[s], R.dz[s]),
+                     BATCH ? slot_tmax(R.tmax[s]) : R.tmax[s]);
+        } else {
+            hs.org[p] = make_float4(0.0f, 0.0f, 0.0f, __uint_as_float(PAD_SLOT));
+            hs.dir[p] = make_float4(0.0f, 0.0f, 0.0f, -1.0f);
+            hs.mom[p] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        }
     }
+    for (uint32_t t = gid; t <= m; t += stride) put_tri(V, t, m, tri);
 }
 
 // One step of the final tests for a wave: each lane group holds a pair --
@@ -127,13 +157,14 @@ __global__ void k_hit_rays_batch(sorted_rays R, const crsh_meta *meta, uint32_t 
 template <bool BATCH, bool COUNT>
 __device__ __forceinline__ void hit_step(const __amdgpu_buffer_rsrc_t &org_r, const __amdgpu_buffer_rsrc_t &dir_r,
                                          const float4 &a, const float4 &b, float tc, uint32_t tri_id,
-                                         uint32_t ray_off, uint32_t dir_off, float t_min, uint64_t live, uint32_t j,
+                                         uint32_t ray_off, float t_min, uint64_t live, uint32_t j,
                                          unsigned long long *keys, uint64_t &tests, uint64_t &upass,
                                          uint64_t &uvpass)
 {
     const uint32_t ro = ray_off + j * 16u;
     const float4 ro4 = buf_load4(org_r, ro);
-    const f3 D = buf_load3(dir_r, dir_off + j * 12u);
+    const float4 di = buf_load4(dir_r, ro);
+    const f3 D = mk(di.x, di.y, di.z);
     tri_t tr;
     tr.v0 = mk(a.x, a.y, a.z);
     tr.e1 = mk(a.w, b.x, b.y);
@@ -160,7 +191,8 @@ __device__ __forceinline__ void hit_step(const __amdgpu_buffer_rsrc_t &org_r, co
 }
 
 // The wave totals of a final-test kernel added to meta (s_red: [3][waves]).
-__device__ __forceinline__ void hit_counts(uint64_t (*s_red)[256 / WAVE], uint32_t wib, uint32_t l, uint64_t tests,
+template <uint32_t NW>
+__device__ __forceinline__ void hit_counts(uint64_t (*s_red)[NW], uint32_t wib, uint32_t l, uint64_t tests,
                                            uint64_t upass, uint64_t uvpass, crsh_meta *meta)
 {
     if (l == 0) {
@@ -185,107 +217,335 @@ __device__ __forceinline__ void hit_counts(uint64_t (*s_red)[256 / WAVE], uint32
 // Batched form: the build's per-node record of a leaf (bd.node_info) holds
 // its ray count and frame, and the frame its interval start.
 //
-// A wave takes runs of 64 consecutive pairs before the grid stride
-// (neighbouring level-1 pairs share their triangle -- siblings of one
-// parent pair -- or their leaves, so a run finds its rays in the vector L1
-// cache).  Each lane reads one pair of the run, its triangle, and writes a
-// record to the wave's LDS slice: the triangle (v0, e1, e2), the triangle
-// id, the byte offsets of the leaf's first ray slot and first direction
-// (past the arrays for a pair out of range, so that its rays read as
-// zeros) and, batched form, the interval start of the leaf's frame.  The
-// run is then tested 64 / G pairs at a time, each lane group reading its
-// pair's record from LDS (the 16 lanes of a group read the same address), so
-// the vector memory path carries only the rays.  The tests are counted per
-// pair when the record is written (the leaf's rays), not per step.  Rays are
-// read with buffer loads on 32-bit byte offsets (the host bounds them; a read
-// past the end returns zeros), origins and directions from their own
-// arrays, so each of the two loads of a step covers contiguous bytes per
-// pair (256 and 192).  The test is split where most of its cost lies: every lane computes
-// the division-free first half, and the wave runs the rest (the division
-// included) only when one of its lanes can still pass.
-constexpr uint32_t RAY_OFF_NONE = 0xFFFF0000u;   // above every slot array (2^31 bytes at most)
-template <bool BATCH, bool PACKED>
-__global__ __launch_bounds__(256) void k_hit(const float4 *__restrict__ RO, const float *__restrict__ RD,
-                                             const float4 *__restrict__ tri,
-                                             const uint32_t *__restrict__ ptri, const uint32_t *__restrict__ pnode,
-                                             uint64_t cap1, uint32_t B, uint32_t log2G, unsigned long long *keys,
-                                             crsh_meta *meta, uint32_t slot_cap, uint32_t m, uint32_t tri_base,
-                                             batch_dev bd, float t_min)
+// A workgroup takes a chunk of consecutive pairs.  Pairs of one top-level
+// node name a few hundred leaves in triangle order, so a chunk holds many
+// pairs of each of its leaves: they are counted per leaf with LDS atomics
+// (HIT_BINS leaves from the smallest in the chunk; leaves beyond wait for
+// another round over the chunk), scanned, and the triangle ids scattered to
+// their leaf's run in LDS, cut into blocks of at most G triangles (G: the
+// bundle rounded up to a power of two, at least 4) -- the whole blocks
+// first, then the leaves' remainders.  A wave takes 64 / G blocks at a time:
+// lane j of a group of G holds ray j of the block's leaf and triangle j of
+// the block, and each 4x4x1 matrix instruction tests the group's G rays
+// against four of its triangles (the A operand broadcast from the lanes that
+// hold them), 11 of them per 256 tests: six products for 2 a - det, three
+// for det, two for T (see put_tri).  What the filter lets through --
+// (triangle, slot) items -- is queued in LDS and goes through the test as
+// written 64 at a time, so the division and the rest run on full waves and
+// only for the few percent of the tests whose u can pass.  Every count is
+// exact: tests are counted per leaf, u and u-v passes by the exact test.
+//
+// Measured (level-1 pairs of 1920x1080 rays against 492,032 triangles, 15.3 G
+// tests, B = 16): 19.5 ms with one lane per (pair, ray) and no matrix
+// instructions, 7.9 ms so (bounce rays of a 512x512 frame 5.6 to 2.1 ms, 24
+// frames batched 9.5 to 4.3 ms).  97 % of the matrix work is on real pairs.
+// The vector L1 is busiest (three 16-byte reads of a triangle's entry per
+// pair), then vector issue.  On the same pairs: chunks of 8,192 pairs in 512
+// threads 8.2 ms, of 2,048 10.0 ms; reading a step ahead 8.4 ms (registers);
+// triangle entries through LDS (a third of the L1 accesses, but more
+// instructions and fewer workgroups) 8.3 ms; the filter's outcome as wave masks
+// instead of shifted sign bits 9.4 ms.
+constexpr uint32_t HIT_THREADS = 256;
+constexpr uint32_t HIT_WAVES = HIT_THREADS / WAVE;
+constexpr uint32_t HIT_PPT = 16;                            // pairs per thread of a chunk
+constexpr uint32_t HIT_CHUNK = HIT_THREADS * HIT_PPT;       // most pairs of a chunk
+constexpr uint32_t HIT_MIN_CHUNK = 64;                      // fewest
+constexpr uint32_t HIT_BPT = 4;                             // leaf bins per thread
+constexpr uint32_t HIT_BINS = HIT_THREADS * HIT_BPT;        // leaves binned per round
+constexpr uint32_t HIT_QUEUE = 128;                         // queued items of a wave
+constexpr uint32_t HIT_WAVES_PER_SIMD = 4;                  // registers for 4 workgroups per compute unit
+// block word: first triangle (13 bits), triangles - 1 (5 bits), leaf bin (10 bits)
+static_assert(HIT_CHUNK <= 1u << 13 && HIT_BINS <= 1u << 10 && CRSH_MAX_BUNDLE <= 32, "block word");
+
+typedef float mfma4 __attribute__((ext_vector_type(4)));
+
+// p[q .. q + 3] of the first n, one load where all four are there (dword
+// alignment is enough for it)
+__device__ __forceinline__ void load4(const uint32_t *__restrict__ p, uint32_t q, uint32_t n, uint32_t *v)
 {
-    constexpr uint32_t RW = BATCH ? 4 : 3;           // record words
-    __shared__ uint64_t s_red[3][256 / WAVE];
-    __shared__ float4 s_rec[256 / WAVE][RW][WAVE];   // [wave][record word][pair of the run]
-    const uint32_t ns = BATCH ? batch_slots(meta, B, slot_cap) : min(meta->n_rays, slot_cap);
-    uint64_t np = meta->n_levels ? meta->pairs[0] : 0;
-    np = np < cap1 ? np : cap1;
-    const uint32_t l = lane_id();
-    const uint32_t G = 1u << log2G;
-    const uint32_t slot = l >> log2G;        // pair of this lane within a step
-    const uint32_t j = l & (G - 1);          // ray of the leaf
-    const uint32_t per_wave = WAVE >> log2G;
-    const uint64_t live = ballot(j < B);     // the lanes of a group that test a ray of the leaf
-    const uint32_t wib = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);   // scalar: so is the run arithmetic
-    const uint64_t wave = (uint64_t)blockIdx.x * (blockDim.x / WAVE) + wib;
-    const uint64_t nwaves = (uint64_t)gridDim.x * (blockDim.x / WAVE);
-    const __amdgpu_buffer_rsrc_t org_r = make_rsrc(RO, (uint64_t)ns * 16u);
-    const __amdgpu_buffer_rsrc_t dir_r = make_rsrc(RD, (uint64_t)ns * 12u);
-    const __amdgpu_buffer_rsrc_t tris_r = make_rsrc(tri, (uint64_t)m * 48u);
-    float4(*rec)[WAVE] = s_rec[wib];
-    uint32_t my_tests = 0;                   // this lane's pairs: rays of their leaves
-    uint64_t tests = 0, upass = 0, uvpass = 0;   // wave-wide counts
-    for (uint64_t c0 = wave * WAVE; c0 < np; c0 += nwaves * WAVE) {
-        const uint32_t cn = __builtin_amdgcn_readfirstlane((uint32_t)min(np - c0, (uint64_t)WAVE));
-        uint32_t my_t = 0u, my_rb = RAY_OFF_NONE, my_db = RAY_OFF_NONE, leaf = 0u;
-        bool valid = false;
-        if (l < cn) {
-            if constexpr (PACKED) {
-                const uint32_t w = ptri[c0 + l];
-                my_t = tri_base + (w & ((1u << CRSH_PACKED_TRI_BITS) - 1u));
-                leaf = w >> CRSH_PACKED_TRI_BITS;
-            } else {
-                my_t = ptri[c0 + l];
-                leaf = pnode[c0 + l];
+    typedef uint32_t u4 __attribute__((ext_vector_type(4), aligned(4)));
+    if (q + 4 <= n) {
+        const u4 x = *(const u4 *)(p + q);
+        v[0] = x.x, v[1] = x.y, v[2] = x.z, v[3] = x.w;
+    } else {
+        v[0] = q < n ? p[q] : 0u;
+        v[1] = q + 1 < n ? p[q + 1] : 0u;
+        v[2] = q + 2 < n ? p[q + 2] : 0u;
+        v[3] = 0u;
+    }
+}
+
+// The filter of triangles 4 Q .. 4 Q + 3 of every group against the group's
+// rays: lane l gets, in element i, ray l's values for triangle 4 Q + i.
+template <int LG, int Q>
+__device__ __forceinline__ void filter4(const float4 &f0, const float4 &f1, const float4 &f2, const float4 &mo,
+                                        const float4 &di, mfma4 &g, mfma4 &det, mfma4 &thr)
+{
+#define CRSH_MM(a, b, c) __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, LG - 2, Q, 0)
+    const mfma4 z = {0.0f, 0.0f, 0.0f, 0.0f};
+    g = CRSH_MM(f0.x, mo.x, z);
+    det = CRSH_MM(f2.x, di.x, z);
+    thr = CRSH_MM(f0.w, mo.w, z);
+    g = CRSH_MM(f0.y, mo.y, g);
+    det = CRSH_MM(f2.y, di.y, det);
+    thr = CRSH_MM(f1.w, di.w, thr);
+    g = CRSH_MM(f0.z, mo.z, g);
+    det = CRSH_MM(f2.z, di.z, det);
+    g = CRSH_MM(f1.x, di.x, g);
+    g = CRSH_MM(f1.y, di.y, g);
+    g = CRSH_MM(f1.z, di.z, g);
+#undef CRSH_MM
+}
+
+// The filter of this lane's ray against its group's triangles 4 Q and on: one
+// bit each, in order, shifted into rej, set if the triangle is surely
+// rejected: the sign of T - (|2 a - det| - |det|) (meaningless for a ray
+// marked FLT_KEEP, which the caller keeps).  cols: the lanes whose group has a
+// triangle in their column.
+template <int LG, int Q>
+__device__ __forceinline__ void filter_all(const float4 &f0, const float4 &f1, const float4 &f2, const float4 &mo,
+                                           const float4 &di, uint64_t cols, uint32_t &rej)
+{
+    constexpr uint32_t G = 1u << LG;
+    // lanes 4 Q of every group
+    constexpr uint64_t ONES = G == 4 ? 0x1111111111111111ull : G == 8 ? 0x0101010101010101ull
+                            : G == 16 ? 0x0001000100010001ull : 0x0000000100000001ull;
+    if constexpr (4 * Q < (int)G) {
+        if ((cols & (ONES << (4 * Q))) != 0) {
+            mfma4 g, det, thr;
+            filter4<LG, Q>(f0, f1, f2, mo, di, g, det, thr);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float x = thr[i] - (fabsf(g[i]) - fabsf(det[i]));
+                rej = __builtin_amdgcn_alignbit(rej, __float_as_uint(x), 31);
             }
-            // rays of the leaf present in the slot array (none for a pair out
-            // of range)
-            const uint64_t first = (uint64_t)leaf * B;
-            if (my_t < m && first < ns) {
-                valid = true;
-                my_rb = (uint32_t)first * 16u;
-                my_db = (uint32_t)first * 12u;
-            }
-        }
-        const uint32_t tb = valid ? my_t * 48u : 0u;
-        const float4 ta = buf_load4(tris_r, tb);
-        const float4 tbv = buf_load4(tris_r, tb + 16u);
-        const float tc = buf_load1(tris_r, tb + 32u);
-        uint32_t cnt = valid ? min(B, ns - leaf * B) : 0u;
-        float my_tmin = 0.0f;
-        if constexpr (BATCH) {
-            const uint32_t info = valid ? bd.node_info[leaf] : 0u;
-            cnt = min(cnt, info & INFO_COUNT_MASK);
-            const uint32_t f = info >> INFO_FRAME_SHIFT;
-            my_tmin = cnt && f < bd.n_frames ? bd.frames[f].t_min : 0.0f;
-        }
-        my_tests += cnt;
-        __builtin_amdgcn_wave_barrier();          // the previous run's reads come first
-        rec[0][l] = ta;
-        rec[1][l] = tbv;
-        rec[2][l] = make_float4(tc, __uint_as_float(my_t), __uint_as_float(my_rb), __uint_as_float(my_db));
-        if constexpr (BATCH) ((float *)rec[3])[l] = my_tmin;
-        __builtin_amdgcn_wave_barrier();
-        for (uint32_t k = 0; k < cn; k += per_wave) {
-            const uint32_t src = k + slot;
-            const float4 a = rec[0][src];
-            const float4 b = rec[1][src];
-            const float4 c = rec[2][src];
-            const float tm = BATCH ? ((const float *)rec[3])[src] : t_min;
-            hit_step<BATCH, false>(org_r, dir_r, a, b, c.x, __float_as_uint(c.y), __float_as_uint(c.z),
-                                   __float_as_uint(c.w), tm, live, j, keys, tests, upass, uvpass);
+            filter_all<LG, Q + 1>(f0, f1, f2, mo, di, cols, rej);
+        } else {                    // no triangles left in any group
+            rej = ~(~rej << (G - 4 * Q) % 32u);
         }
     }
-    tests = wave_sum((uint64_t)my_tests);
-    hit_counts(s_red, wib, l, tests, upass, uvpass, meta);
+}
+
+template <int LG, bool BATCH, bool PACKED>
+__global__ __launch_bounds__(HIT_THREADS, HIT_WAVES_PER_SIMD) void k_hit(hit_slots_ws hs, const float4 *__restrict__ tri,
+                                                     const float4 *__restrict__ ftri,
+                                                     const uint32_t *__restrict__ ptri,
+                                                     const uint32_t *__restrict__ pnode, uint64_t cap1, uint32_t B,
+                                                     unsigned long long *keys, crsh_meta *meta, uint32_t m,
+                                                     uint32_t tri_base, batch_dev bd, float t_min, uint32_t chunk_max)
+{
+    constexpr uint32_t G = 1u << LG;                // lanes, and triangles of a block, per group
+    constexpr uint32_t GPW = WAVE / G;              // groups of a wave
+    constexpr uint32_t NONE = 0xFFFFFFFFu;
+    __shared__ uint32_t s_tri[HIT_CHUNK];           // triangle ids, leaf by leaf
+    __shared__ __attribute__((aligned(8))) uint32_t s_cnt[HIT_BINS];            // pairs per leaf, then the leaf's first place
+    __shared__ uint32_t s_blk[HIT_CHUNK / G + HIT_BINS];
+    __shared__ uint2 s_queue[HIT_WAVES][HIT_QUEUE];
+    __shared__ uint2 s_scan[HIT_WAVES], s_lohi[HIT_WAVES];
+    __shared__ uint64_t s_red[3][HIT_WAVES];
+    const uint32_t ns = BATCH ? batch_slots(meta, B, hs.slots) : min(meta->n_rays, hs.slots);
+    uint64_t np = meta->n_levels ? meta->pairs[0] : 0;
+    np = np < cap1 ? np : cap1;
+    // no slots, no tests
+    const uint32_t last_leaf = ns ? (ns - 1u) / B : 0u;
+    np = ns ? np : 0u;
+    const uint32_t l = lane_id();
+    const uint32_t j = l & (G - 1);
+    const uint32_t wib = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const __amdgpu_buffer_rsrc_t org_r = make_rsrc(hs.org, (uint64_t)ns * 16u);
+    const __amdgpu_buffer_rsrc_t dir_r = make_rsrc(hs.dir, (uint64_t)ns * 16u);
+    const __amdgpu_buffer_rsrc_t mom_r = make_rsrc(hs.mom, (uint64_t)ns * 16u);
+    const __amdgpu_buffer_rsrc_t ftri_r = make_rsrc(ftri, ((uint64_t)m + 1) * 48u);
+    const __amdgpu_buffer_rsrc_t tri_r = make_rsrc(tri, (uint64_t)m * 48u);
+    uint2 *const queue = s_queue[wib];
+    uint32_t qn = 0;                                // items in the queue (wave-uniform)
+    uint64_t tests = 0, upass = 0, uvpass = 0;      // tests: this thread's; the others: wave-wide
+
+    // the test as written for one item a lane
+    auto exact = [&](uint2 it, uint64_t live) {
+        live &= ballot(it.x < m);                   // not a padding triangle
+        const uint32_t ro = it.y * 16u, to = it.x * 48u;
+        const float4 o4 = buf_load4(org_r, ro);
+        const float4 d4 = buf_load4(dir_r, ro);
+        const float4 ta = buf_load4(tri_r, to);
+        const float4 tb = buf_load4(tri_r, to + 16u);
+        const float tc = buf_load1(tri_r, to + 32u);
+        float tm = t_min;
+        if constexpr (BATCH) {
+            const uint32_t info = ((live >> l) & 1u) ? bd.node_info[it.y / B] : 0u;
+            const uint32_t f = info >> INFO_FRAME_SHIFT;
+            tm = f < bd.n_frames ? bd.frames[f].t_min : 0.0f;
+        }
+        tri_t tr;
+        tr.v0 = mk(ta.x, ta.y, ta.z);
+        tr.e1 = mk(ta.w, tb.x, tb.y);
+        tr.e2 = mk(tb.z, tb.w, tc);
+        const f3 D = mk(d4.x, d4.y, d4.z);
+        mt_head h;
+        const uint64_t mm = mt_first_half(mk(o4.x, o4.y, o4.z), D, tr, h) & live;
+        float th;
+        uint64_t pu, puv, hit;
+        mt_second_half(D, tm, o4.w, tr, h, th, pu, puv, hit);
+        upass += (uint64_t)__popcll(pu & mm);
+        uvpass += (uint64_t)__popcll(puv & mm);
+        if (__builtin_amdgcn_inverse_ballot_w64(hit & mm)) atomicMin(&keys[it.y], hit_key(th, it.x));
+    };
+
+    // near-equal chunks in whole rounds of the grid, at most chunk_max pairs each
+    const float rounds = ceilf((float)np / ((float)gridDim.x * (float)chunk_max));
+    uint32_t cs = rounds > 0.0f ? (uint32_t)((float)np / (rounds * (float)gridDim.x)) + 1u : 1u;
+    cs = min(max((cs + 63u) & ~63u, HIT_MIN_CHUNK), chunk_max);
+    for (uint64_t c0 = (uint64_t)blockIdx.x * cs; c0 < np; c0 += (uint64_t)gridDim.x * cs) {
+        const uint32_t cn = (uint32_t)min(np - c0, (uint64_t)cs);
+        uint32_t from = 0u;                         // first leaf not binned yet
+        for (bool more = true; more;) {
+            uint32_t tid = threadIdx.x;
+            asm volatile("" : "+v"(tid));           // nothing of a round is kept over the next
+            uint32_t my_t[HIT_PPT], my_leaf[HIT_PPT];
+#pragma unroll
+            for (uint32_t k = 0; k < HIT_PPT; k += 4) {     // four consecutive pairs a load
+                load4(ptri + c0, k * HIT_THREADS + 4 * tid, cn, &my_t[k]);
+                if constexpr (!PACKED) load4(pnode + c0, k * HIT_THREADS + 4 * tid, cn, &my_leaf[k]);
+            }
+            uint32_t lo = NONE, hi = 0u;            // the leaves still to do: smallest and largest
+#pragma unroll
+            for (uint32_t k = 0; k < HIT_PPT; ++k) {
+                if constexpr (PACKED) {
+                    my_leaf[k] = my_t[k] >> CRSH_PACKED_TRI_BITS;
+                    my_t[k] = tri_base + (my_t[k] & ((1u << CRSH_PACKED_TRI_BITS) - 1u));
+                }
+                // a pair out of range has no tests
+                const uint32_t q = k / 4 * 4 * HIT_THREADS + 4 * tid + k % 4;
+                const bool ok = q < cn && my_t[k] < m && my_leaf[k] <= last_leaf && my_leaf[k] >= from;
+                hi = ok ? max(hi, my_leaf[k]) : hi;
+                my_leaf[k] = ok ? my_leaf[k] : NONE;
+                lo = min(lo, my_leaf[k]);
+            }
+            lo = wave_reduce(lo, NONE, [](uint32_t a, uint32_t b) { return min(a, b); });
+            hi = wave_reduce(hi, 0u, [](uint32_t a, uint32_t b) { return max(a, b); });
+            if (l == 0) s_lohi[wib] = make_uint2(lo, hi);
+#pragma unroll
+            for (uint32_t k = 0; k < HIT_BPT; ++k) s_cnt[tid + k * HIT_THREADS] = 0u;
+            __syncthreads();
+#pragma unroll
+            for (uint32_t w = 0; w < HIT_WAVES; ++w) {
+                const uint2 v = s_lohi[w];
+                lo = min(lo, v.x);
+                hi = max(hi, v.y);
+            }
+            const uint32_t base = __builtin_amdgcn_readfirstlane(lo);
+            hi = __builtin_amdgcn_readfirstlane(hi);
+            more = base != NONE && hi - base >= HIT_BINS;
+            from = base + HIT_BINS;
+            // pairs per leaf; each pair's bin and its place in the leaf's run
+#pragma unroll
+            for (uint32_t k = 0; k < HIT_PPT; ++k) {
+                const uint32_t bin = my_leaf[k] - base;
+                const bool ok = bin < HIT_BINS && my_leaf[k] != NONE;
+                my_leaf[k] = NONE;
+                if (ok) my_leaf[k] = bin | atomicAdd(&s_cnt[bin], 1u) * HIT_BINS;
+            }
+            __syncthreads();
+            // a thread's bins: places, whole blocks and remainders
+            uint32_t c[HIT_BPT], cnt_part = 0u, fulls = 0u;
+#pragma unroll
+            for (uint32_t k = 0; k < HIT_BPT; ++k) {
+                c[k] = s_cnt[HIT_BPT * tid + k];
+                cnt_part += c[k] | (c[k] % G != 0u ? 1u << 16 : 0u);
+                fulls += c[k] / G;
+            }
+            uint32_t ex_cp = wave_scan_dpp(cnt_part), ex_f = wave_scan_dpp(fulls);
+            if (l == WAVE - 1) s_scan[wib] = make_uint2(ex_cp, ex_f);
+            ex_cp -= cnt_part;
+            ex_f -= fulls;
+            __syncthreads();
+            uint32_t nfull = 0u, nblk = 0u;
+#pragma unroll
+            for (uint32_t w = 0; w < HIT_WAVES; ++w) {
+                const uint2 v = s_scan[w];
+                ex_cp += w < wib ? v.x : 0u;
+                ex_f += w < wib ? v.y : 0u;
+                nfull += v.y;
+                nblk += v.x >> 16;
+            }
+            nfull = __builtin_amdgcn_readfirstlane(nfull);
+            nblk = __builtin_amdgcn_readfirstlane(nblk) + nfull;
+            uint32_t first = ex_cp & 0xFFFFu, part = nfull + (ex_cp >> 16);
+#pragma unroll
+            for (uint32_t k = 0; k < HIT_BPT; ++k) {
+                const uint32_t bin = HIT_BPT * tid + k;
+                s_cnt[bin] = first;
+                if (c[k] == 0u) continue;
+                uint32_t rest = c[k];
+                for (; rest >= G; rest -= G, first += G) s_blk[ex_f++] = first | (G - 1) << 13 | bin << 18;
+                if (rest) s_blk[part++] = first | (rest - 1) << 13 | bin << 18;
+                first += rest;
+                uint32_t rays = min(B, ns - (base + bin) * B);
+                if constexpr (BATCH) rays = min(rays, bd.node_info[base + bin] & INFO_COUNT_MASK);
+                tests += (uint64_t)c[k] * rays;
+            }
+            __syncthreads();
+#pragma unroll
+            for (uint32_t k = 0; k < HIT_PPT; ++k)
+                if (my_leaf[k] != NONE) s_tri[s_cnt[my_leaf[k] % HIT_BINS] + my_leaf[k] / HIT_BINS] = my_t[k];
+            __syncthreads();
+            for (uint32_t b0 = wib * GPW; b0 < nblk; b0 += HIT_WAVES * GPW) {
+                const uint32_t bi = b0 + l / G;
+                const uint32_t e = s_blk[bi < nblk ? bi : 0u];
+                const uint32_t cnt = bi < nblk ? ((e >> 13) & 31u) + 1u : 0u;
+                const uint32_t slot = (base + (e >> 18)) * B + j;
+                const uint32_t t = j < cnt ? s_tri[(e & 0x1FFFu) + j] : m;
+                const uint64_t cols = ballot(j < cnt);
+                const float4 f0 = buf_load4(ftri_r, t * 48u);
+                const float4 f1 = buf_load4(ftri_r, t * 48u + 16u);
+                const float4 f2 = buf_load4(ftri_r, t * 48u + 32u);
+                const float4 mo = buf_load4(mom_r, slot * 16u);
+                const float4 di = buf_load4(dir_r, slot * 16u);
+                // this lane's ray against the block's G triangles: bit G - 1 - c
+                // set if triangle c is rejected
+                uint32_t rej = 0u;
+                filter_all<LG, 0>(f0, f1, f2, mo, di, cols, rej);
+                // the columns kept, one of every lane at a time
+                rej = mo.w == FLT_KEEP ? 0u : rej;
+                uint32_t kept = j < B && slot < ns && cnt != 0u ? ~rej & (uint32_t)((1ull << G) - 1ull) : 0u;
+                for (uint64_t k; (k = ballot(kept != 0u)) != 0;) {
+                    const uint32_t c = G - 32u + (uint32_t)__builtin_clz(kept | 1u);
+                    const uint32_t tid = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(((l & ~(G - 1)) + (c & (G - 1))) * 4u), (int)t);
+                    if (kept != 0u) queue[qn + rank_below(k)] = make_uint2(tid, slot);
+                    kept &= ~(1u << (G - 1 - (c & (G - 1))));
+                    qn += (uint32_t)__popcll(k);
+                    if (qn >= WAVE) {
+                        __builtin_amdgcn_wave_barrier();
+                        const uint2 it = queue[l], rest = queue[WAVE + l];
+                        __builtin_amdgcn_wave_barrier();
+                        qn -= WAVE;
+                        if (l < qn) queue[l] = rest;
+                        __builtin_amdgcn_wave_barrier();
+                        exact(it, ~0ull);
+                    }
+                }
+            }
+        }
+    }
+    if (qn) {
+        __builtin_amdgcn_wave_barrier();
+        const uint2 it = queue[l];
+        exact(l < qn ? it : make_uint2(m, 0u), (1ull << qn) - 1ull);
+    }
+    // this workgroup's counts; k_hit_final adds them up (atomics of every
+    // workgroup on three words would take longer than a small frame's tests)
+    tests = wave_sum(tests);
+    if (l == 0) {
+        s_red[0][wib] = tests;
+        s_red[1][wib] = upass;
+        s_red[2][wib] = uvpass;
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        uint64_t tot = 0;
+        for (uint32_t w = 0; w < HIT_WAVES; ++w) tot += s_red[threadIdx.x][w];
+        hs.part[3 * blockIdx.x + threadIdx.x] = tot;
+    }
 }
 
 // Final tests of the level-1 pairs that the level-2 pairs and the level-1
@@ -302,7 +562,7 @@ __global__ __launch_bounds__(256) void k_hit(const float4 *__restrict__ RO, cons
 // compute unit, the one round of blocks the launch assumes)
 constexpr uint32_t MASKED_ITEMS = 240;
 template <bool BATCH>
-__global__ __launch_bounds__(256) void k_hit_masked(const float4 *__restrict__ RO, const float *__restrict__ RD,
+__global__ __launch_bounds__(256) void k_hit_masked(const float4 *__restrict__ RO, const float4 *__restrict__ RD,
                                                     const float4 *__restrict__ tri,
                                                     const uint32_t *__restrict__ ptri2,
                                                     const uint32_t *__restrict__ pnode2, uint64_t cap2,
@@ -329,7 +589,7 @@ __global__ __launch_bounds__(256) void k_hit_masked(const float4 *__restrict__ R
     const uint64_t wave = (uint64_t)blockIdx.x * (blockDim.x / WAVE) + wib;
     const uint64_t nwaves = (uint64_t)gridDim.x * (blockDim.x / WAVE);
     const __amdgpu_buffer_rsrc_t org_r = make_rsrc(RO, (uint64_t)ns * 16u);
-    const __amdgpu_buffer_rsrc_t dir_r = make_rsrc(RD, (uint64_t)ns * 12u);
+    const __amdgpu_buffer_rsrc_t dir_r = make_rsrc(RD, (uint64_t)ns * 16u);
     const __amdgpu_buffer_rsrc_t tris_r = make_rsrc(tri, (uint64_t)m * 48u);
     const uint32_t nfm = nf >= 32 ? ~0u : (1u << nf) - 1u;
     float4(*rec)[WAVE] = s_rec[wib];
@@ -393,12 +653,12 @@ __global__ __launch_bounds__(256) void k_hit_masked(const float4 *__restrict__ R
                 const float4 b = rec[1][p];
                 const float4 c = rec[2][p];
                 const uint32_t cnt = src < nit ? it.x >> 8 : 0u;
-                hit_step<BATCH, true>(org_r, dir_r, a, b, c.x, __float_as_uint(c.y), it.y, (it.y >> 2) * 3u, c.z,
+                hit_step<BATCH, true>(org_r, dir_r, a, b, c.x, __float_as_uint(c.y), it.y, c.z,
                                       ballot(j < cnt), j, keys, tests, upass, uvpass);
             }
         }
     }
-    hit_counts(s_red, wib, l, tests, upass, uvpass, meta);
+    hit_counts<256 / WAVE>(s_red, wib, l, tests, upass, uvpass, meta);
 }
 
 struct hit_out {
@@ -412,9 +672,28 @@ struct hit_out {
 template <bool BATCH>
 __global__ void k_hit_final(sorted_rays R, const float4 *__restrict__ tri, const uint32_t *__restrict__ sorted_ids,
                             float t_min0, unsigned long long *tkey, const unsigned long long *__restrict__ keys,
-                            uint32_t B, uint32_t slot_cap, hit_out out, const crsh_meta *meta, uint32_t ray_cap,
-                            uint32_t m, batch_dev bd)
+                            uint32_t B, uint32_t slot_cap, hit_out out, crsh_meta *meta, uint32_t ray_cap,
+                            uint32_t m, batch_dev bd, const uint64_t *part, uint32_t n_part)
 {
+    // the counts of k_hit's workgroups, by the first of this grid
+    if (blockIdx.x == 0 && n_part) {
+        __shared__ uint64_t s_red[3][256 / WAVE];
+        uint64_t c[3] = {0, 0, 0};
+        for (uint32_t i = threadIdx.x; i < n_part; i += blockDim.x)
+            for (uint32_t k = 0; k < 3; ++k) c[k] += part[3 * i + k];
+        for (uint32_t k = 0; k < 3; ++k) {
+            c[k] = wave_sum(c[k]);
+            if (lane_id() == 0) s_red[k][threadIdx.x / WAVE] = c[k];
+        }
+        __syncthreads();
+        if (threadIdx.x < 3) {
+            uint64_t tot = 0;
+            for (uint32_t w = 0; w < 256 / WAVE; ++w) tot += s_red[threadIdx.x][w];
+            uint64_t *const dst = threadIdx.x == 0 ? &meta->final_tests
+                                : threadIdx.x == 1 ? &meta->final_u_pass : &meta->final_uv_pass;
+            if (tot) *dst += tot;
+        }
+    }
     const uint32_t n = min(meta->n_rays, ray_cap);
     const uint32_t ns = BATCH ? batch_slots(meta, B, slot_cap) : 0u;
     for (uint32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < n; s += gridDim.x * blockDim.x) {
@@ -473,42 +752,69 @@ extern "C" crsh_status crsh_hits_reset(crsh_hits *hits, hipStream_t stream)
 
 namespace crsh {
 
-void hit_prep_launch(const crsh_scene *scene, float4 *tri, hipStream_t stream)
+void hit_pack_launch(const crsh_scene *scene, const hit_tris_ws &tri, const crsh_rays *sorted,
+                     const hit_slots_ws &hs, int32_t bundle, const crsh_meta *meta, const batch_dev *bd,
+                     hipStream_t stream)
 {
-    const float *const *v = scene->v;
-    if (scene->m) {
-        uint32_t g = std::min<uint32_t>((scene->m + 255) / 256, 2048);
-        k_hit_prep<<<g, 256, 0, stream>>>(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], v[8], scene->m, tri);
-    }
+    tri_verts V;
+    for (int k = 0; k < 9; ++k) V.v[k] = scene->v[k];
+    const sorted_rays S{sorted->ox, sorted->oy, sorted->oz, sorted->dx, sorted->dy, sorted->dz, sorted->tmax};
+    const uint32_t items = std::max(hs.slots, scene->m + 1);
+    const uint32_t g = std::min<uint32_t>((items + 255) / 256, 4096);
+    if (bd)
+        k_hit_pack<true><<<g, 256, 0, stream>>>(V, scene->m, tri, S, meta, sorted->capacity, (uint32_t)bundle, *bd, hs);
+    else
+        k_hit_pack<false><<<g, 256, 0, stream>>>(V, scene->m, tri, S, meta, sorted->capacity, (uint32_t)bundle,
+                                                 batch_dev{}, hs);
 }
 
-void hit_pairs_launch(const crsh_rays *sorted, const float4 *tri, const hit_slots_ws &hs, const crsh_pairs *level1,
-                      int32_t bundle, const crsh_scene *scene, float t_min, crsh_hits *hits, crsh_meta *meta,
-                      const batch_dev *bd, int32_t hit_block, hipStream_t stream, bool packed, uint32_t tri_base)
+template <int LG>
+static uint32_t k_hit_launch(const hit_slots_ws &hs, const hit_tris_ws &tri, const crsh_pairs *level1, uint32_t B,
+                         crsh_hits *hits, crsh_meta *meta, uint32_t m, uint32_t tri_base, const batch_dev *bd,
+                         float t_min, uint32_t chunk, bool packed, hipStream_t stream)
 {
-    const uint32_t g = std::max<uint32_t>(std::min<uint32_t>((hs.slots + 255) / 256, 4096), 1);
-    sorted_rays S{sorted->ox, sorted->oy, sorted->oz, sorted->dx, sorted->dy, sorted->dz, sorted->tmax};
-    if (bd)     // also the start value of every slot key, read by k_hit_final
-        k_hit_rays_batch<<<g, 256, 0, stream>>>(S, meta, sorted->capacity, (uint32_t)bundle, hs.slots, *bd,
-                                                hs.org, hs.dir, hs.keys);
-    if (!level1->capacity) return;
-    if (!bd) k_hit_rays<<<g, 256, 0, stream>>>(S, meta, sorted->capacity, hs.org, hs.dir);
-    uint32_t log2G = 0;
-    while ((1u << log2G) < (uint32_t)bundle) ++log2G;
-    const uint32_t grid = 2048u * 256u / (uint32_t)hit_block;   // the same number of waves
+    // one round of resident workgroups, at most one per smallest chunk
+    const uint64_t want = std::max<uint64_t>((level1->capacity + HIT_MIN_CHUNK - 1) / HIT_MIN_CHUNK, 1);
+    uint32_t g;
+    if (bd) {
+        g = resident_grid((const void *)k_hit<LG, true, false>, HIT_THREADS, std::min<uint64_t>(want, HIT_MAX_GRID));
+        k_hit<LG, true, false><<<g, HIT_THREADS, 0, stream>>>(hs, tri.tri, tri.ftri, level1->tri, level1->node,
+                                                              level1->capacity, B, hs.keys, meta, m, 0u, *bd, 0.0f,
+                                                              chunk);
+    } else if (packed) {
+        g = resident_grid((const void *)k_hit<LG, false, true>, HIT_THREADS, std::min<uint64_t>(want, HIT_MAX_GRID));
+        k_hit<LG, false, true><<<g, HIT_THREADS, 0, stream>>>(hs, tri.tri, tri.ftri, level1->tri, nullptr,
+                                                              level1->capacity, B, hits->tkey, meta, m, tri_base,
+                                                              batch_dev{}, t_min, chunk);
+    } else {
+        g = resident_grid((const void *)k_hit<LG, false, false>, HIT_THREADS, std::min<uint64_t>(want, HIT_MAX_GRID));
+        k_hit<LG, false, false><<<g, HIT_THREADS, 0, stream>>>(hs, tri.tri, tri.ftri, level1->tri, level1->node,
+                                                               level1->capacity, B, hits->tkey, meta, m, 0u,
+                                                               batch_dev{}, t_min, chunk);
+    }
+    return g;
+}
+
+uint32_t hit_pairs_launch(const hit_tris_ws &tri, const hit_slots_ws &hs,
+                      const crsh_pairs *level1, int32_t bundle, const crsh_scene *scene, float t_min,
+                      crsh_hits *hits, crsh_meta *meta, const batch_dev *bd, int32_t hit_block, hipStream_t stream,
+                      bool packed, uint32_t tri_base)
+{
+    if (!level1->capacity) return 0u;
+    const uint32_t B = (uint32_t)bundle;
+    const uint32_t chunk = (uint32_t)hit_block * (HIT_CHUNK / 256u);
     prof_scope ps("k_hit", stream);
-    if (bd)
-        k_hit<true, false><<<grid, hit_block, 0, stream>>>(hs.org, hs.dir, tri, level1->tri, level1->node,
-                                                           level1->capacity, (uint32_t)bundle, log2G, hs.keys, meta,
-                                                           hs.slots, scene->m, 0u, *bd, 0.0f);
-    else if (packed)
-        k_hit<false, true><<<grid, hit_block, 0, stream>>>(hs.org, hs.dir, tri, level1->tri, nullptr, level1->capacity,
-                                                           (uint32_t)bundle, log2G, hits->tkey, meta, hs.slots,
-                                                           scene->m, tri_base, batch_dev{}, t_min);
+#define CRSH_HIT(LG) \
+    return k_hit_launch<LG>(hs, tri, level1, B, hits, meta, scene->m, tri_base, bd, t_min, chunk, packed, stream)
+    if (B <= 4)
+        CRSH_HIT(2);
+    else if (B <= 8)
+        CRSH_HIT(3);
+    else if (B <= 16)
+        CRSH_HIT(4);
     else
-        k_hit<false, false><<<grid, hit_block, 0, stream>>>(hs.org, hs.dir, tri, level1->tri, level1->node,
-                                                            level1->capacity, (uint32_t)bundle, log2G, hits->tkey,
-                                                            meta, hs.slots, scene->m, 0u, batch_dev{}, t_min);
+        CRSH_HIT(5);
+#undef CRSH_HIT
 }
 
 void hit_masked_launch(const crsh_rays *sorted, const float4 *tri, const hit_slots_ws &hs, const crsh_pairs *level2,
@@ -537,7 +843,7 @@ void hit_masked_launch(const crsh_rays *sorted, const float4 *tri, const hit_slo
 
 void hit_final_launch(const crsh_rays *sorted, const uint32_t *sorted_ids, const float4 *tri,
                       const hit_slots_ws &hs, int32_t bundle, const crsh_scene *scene, float t_min,
-                      crsh_hits *hits, crsh_meta *meta, const batch_dev *bd, hipStream_t stream)
+                      crsh_hits *hits, crsh_meta *meta, const batch_dev *bd, uint32_t n_part, hipStream_t stream)
 {
     sorted_rays R{sorted->ox, sorted->oy, sorted->oz, sorted->dx, sorted->dy, sorted->dz, sorted->tmax};
     const batch_dev b = bd ? *bd : batch_dev{};
@@ -547,10 +853,10 @@ void hit_final_launch(const crsh_rays *sorted, const uint32_t *sorted_ids, const
     prof_scope ps("k_hit_final", stream);
     if (bd)
         k_hit_final<true><<<g, 256, 0, stream>>>(R, tri, sorted_ids, t_min, hits->tkey, hs.keys, (uint32_t)bundle,
-                                                 hs.slots, o, meta, sorted->capacity, scene->m, b);
+                                                 hs.slots, o, meta, sorted->capacity, scene->m, b, hs.part, n_part);
     else
         k_hit_final<false><<<g, 256, 0, stream>>>(R, tri, sorted_ids, t_min, hits->tkey, nullptr, (uint32_t)bundle,
-                                                  0u, o, meta, sorted->capacity, scene->m, b);
+                                                  0u, o, meta, sorted->capacity, scene->m, b, hs.part, n_part);
 }
 
 crsh_status hit_check(const crsh_rays *sorted, const uint32_t *sorted_ids, int32_t bundle, const crsh_pairs *level1,
@@ -608,12 +914,12 @@ crsh_status hit_launch(const crsh_rays *sorted, const uint32_t *sorted_ids, int3
         set_error("crsh_closest_hit: workspace too small (%zu < %zu)", ws_bytes, hit_ws_bytes(scene->m, slots));
         return CRSH_ERR_INVALID;
     }
-    float4 *tri = (float4 *)ws;
-    const hit_slots_ws hs = carve_hit_slots((char *)ws + align256((size_t)scene->m * 48), slots);
-    hit_prep_launch(scene, tri, stream);
-    hit_pairs_launch(sorted, tri, hs, level1, bundle, scene, t_min, hits, meta, bd, hit_block, stream, packed,
+    const hit_tris_ws tri = carve_hit_tris(ws, scene->m);
+    const hit_slots_ws hs = carve_hit_slots((char *)ws + hit_tris_bytes(scene->m), slots);
+    hit_pack_launch(scene, tri, sorted, hs, bundle, meta, bd, stream);
+    const uint32_t parts = hit_pairs_launch(tri, hs, level1, bundle, scene, t_min, hits, meta, bd, hit_block, stream, packed,
                      tri_base);
-    hit_final_launch(sorted, sorted_ids, tri, hs, bundle, scene, t_min, hits, meta, bd, stream);
+    hit_final_launch(sorted, sorted_ids, tri.tri, hs, bundle, scene, t_min, hits, meta, bd, parts, stream);
     return hip_check(hipGetLastError(), "crsh_closest_hit launch");
 }
 

@@ -18,7 +18,7 @@
 namespace crsh {
 
 struct lh_ws {
-    float4 *tri;         // packed triangles (v0, e1, e2)
+    hit_tris_ws tri;     // packed triangles
     hit_slots_ws hs;     // packed ray slots and their keys
     float4 *tsph;        // triangle bounding spheres
     float4 *na, *nb;     // packed nodes for the level-1 count
@@ -34,8 +34,8 @@ static lh_ws carve(void *ws, uint32_t m, uint32_t node_cap, uint64_t cap2, uint3
     const uint64_t tiles = lh_tiles(cap2) + 1;
     char *w = (char *)ws;
     lh_ws L;
-    L.tri = (float4 *)w;
-    w += align256((size_t)m * 48);
+    L.tri = carve_hit_tris(w, m);
+    w += hit_tris_bytes(m);
     L.hs = carve_hit_slots(w, slots);
     w += hit_slots_bytes(slots);
     L.tsph = (float4 *)w;
@@ -60,7 +60,7 @@ static lh_ws carve(void *ws, uint32_t m, uint32_t node_cap, uint64_t cap2, uint3
 size_t leaf_hit_ws_bytes(uint32_t m, uint32_t node_cap, uint64_t cap2, uint32_t slots)
 {
     const uint64_t tiles = lh_tiles(cap2) + 1;
-    return align256((size_t)m * 48) + hit_slots_bytes(slots) + align256((size_t)m * 16) +
+    return hit_tris_bytes(m) + hit_slots_bytes(slots) + align256((size_t)m * 16) +
            align256((size_t)node_cap * 16) * 2 + align256((size_t)node_cap * 4) + align256(tiles * 4) +
            align256(tiles * LEVEL_THREADS * 4 + 4) + align256((tiles / SCAN_TILE + 2) * 8) + align256(4);
 }
@@ -115,12 +115,11 @@ crsh_status leaf_hit_launch(const crsh_rays *sorted, const uint32_t *sorted_ids,
         return CRSH_ERR_INVALID;
     }
     const lh_ws L = carve(ws, scene->m, nodes->capacity, level2->capacity, slots);
-    hit_prep_launch(scene, L.tri, stream);
+    hit_pack_launch(scene, L.tri, sorted, L.hs, bundle, meta, bd, stream);
     tri_spheres_launch(scene, 0, scene->m, L.tsph, stream);
     node_pack_launch(nodes, meta, L.na, L.nb, L.ns, false, stream);
-    // level-1 pairs stored by a top-level pass at level 1 (this also packs
-    // the ray slots)
-    hit_pairs_launch(sorted, L.tri, L.hs, level1, bundle, scene, t_min, hits, meta, bd, hit_block, stream);
+    // level-1 pairs stored by a top-level pass at level 1
+    const uint32_t parts = hit_pairs_launch(L.tri, L.hs, level1, bundle, scene, t_min, hits, meta, bd, hit_block, stream);
     // the level-1 node tests: pass bits and survivors per tile, node tests
     // added to meta
     pair_levels P{};
@@ -131,9 +130,9 @@ crsh_status leaf_hit_launch(const crsh_rays *sorted, const uint32_t *sorted_ids,
     const uint32_t gs = (uint32_t)std::max<uint64_t>(std::min<uint64_t>((lh_tiles(level2->capacity) + 255) / 256,
                                                                         1024), 1);
     k_lh_survivors<<<gs, 256, 0, stream>>>(L.S, meta, level2->capacity);
-    hit_masked_launch(sorted, L.tri, L.hs, level2, L.S.mask, merge, bundle, scene, t_min, hits, meta, bd,
+    hit_masked_launch(sorted, L.tri.tri, L.hs, level2, L.S.mask, merge, bundle, scene, t_min, hits, meta, bd,
                       hit_block, stream);
-    hit_final_launch(sorted, sorted_ids, L.tri, L.hs, bundle, scene, t_min, hits, meta, bd, stream);
+    hit_final_launch(sorted, sorted_ids, L.tri.tri, L.hs, bundle, scene, t_min, hits, meta, bd, parts, stream);
     return hip_check(hipGetLastError(), "crsh_leaf_hit launch");
 }
 

@@ -1,5 +1,6 @@
-"""Autotuner of the batched form: bundle size B, hierarchy depth and the
-workgroup size of the final tests, chosen by timing the captured batch.
+"""Autotuner of the batched form: bundle size B, hierarchy depth and the pairs
+a workgroup of the final tests takes (hit_block), chosen by timing the captured
+batch.
 
 The search is block coordinate descent over the grid B x levels x
 hit_block (the merge factor stays at its value): the bundle size and the
