@@ -79,15 +79,17 @@ size_t hash_ws_bytes(uint64_t pixels)
 
 size_t trav_ws_bytes(uint32_t m, uint32_t node_cap, uint64_t top_items, uint64_t max_pairs)
 {
-    uint64_t level_tiles = (max_pairs + LEVEL_TILE - 1) / LEVEL_TILE;
-    uint64_t items = std::max<uint64_t>(top_items, level_tiles) + 1;
+    const uint64_t tiles = max_pairs / STEP_THREADS + 2;
+    const uint64_t items = std::max<uint64_t>(top_items, tiles) + 1;
     return align256((size_t)m * 16)                            // triangle spheres
            + align256((size_t)node_cap * 16) * 2               // packed nodes
            + align256((size_t)node_cap * 4)
-           + align256(items * 4) + align256(items * 8)         // counts, offsets
-           + align256(level_tiles * LEVEL_THREADS * 4 + 4)     // pass masks
+           + align256(top_items * 4 + 4) + align256(tiles * 4) // counts of top-level items and tiles
+           + align256(items * 8)                               // offsets
+           + align256(max_pairs * 2 + 2) * 2                   // pass bits of two levels
            + align256((items / SCAN_TILE_ITEMS + 2) * 8)       // scan look-back words
-           + align256(4);                                      // scan tile counter
+           + align256(4)                                       // scan tile counter
+           + TRAV_PARTS * 8 * 4;                               // sums per workgroup
 }
 
 size_t hit_ws_bytes(uint32_t m, uint32_t slots) { return hit_tris_bytes(m) + hit_slots_bytes(slots); }

@@ -250,21 +250,17 @@ constexpr uint32_t SORT_PASSES = 4;       // 8-bit digits of a 32-bit key
 constexpr uint32_t HASH_BLOCK = 256;      // pixels per hash block
 constexpr uint64_t HASH_STATIC_MAX_PIXELS = CRSH_HASH_STATIC_MAX_PIXELS;  // crsh_hash_static
 constexpr uint32_t LEVEL_THREADS = 256;   // threads of a traversal tile
-#ifndef CRSH_EMIT_PPT
-#define CRSH_EMIT_PPT 2
-#endif
-constexpr uint32_t LEVEL_PPT = 1;   // parent pairs per thread of the count pass
+constexpr uint32_t LEVEL_PPT = 1;   // parent pairs per thread of the fused last level's count pass
 constexpr uint32_t LEVEL_TILE = LEVEL_THREADS * LEVEL_PPT;   // parent pairs per count tile
 constexpr uint32_t COUNT_THREADS = 512;    // threads of a count block: COUNT_TPS tiles per step
 constexpr uint32_t COUNT_TPS = COUNT_THREADS / LEVEL_THREADS;
-constexpr uint32_t COUNT_WINDOW = 1024;    // child nodes a count block keeps in LDS (36 B each)
-#define COUNT_WAVES_PER_SIMD 6             // 3 count blocks per compute unit (LDS: 48 KiB each)
-constexpr uint32_t EMIT_PPT = CRSH_EMIT_PPT;     // parent pairs per thread of the emit pass
-constexpr uint32_t EMIT_TILE = LEVEL_THREADS * EMIT_PPT;     // parent pairs per emit tile
-static_assert(EMIT_PPT % LEVEL_PPT == 0, "an emit tile covers whole count tiles");
-// parent pairs per emit thread for NF children per parent: the thread's pass
-// bits (NF per pair) must fit one 32-bit mask word
-constexpr int emit_ppt(int nf) { return (int)EMIT_PPT * nf <= 32 ? (int)EMIT_PPT : 32 / nf; }
+constexpr uint32_t COUNT_WINDOW = 1024;    // child nodes a block keeps in LDS (36 B each)
+constexpr uint32_t STEP_THREADS = 512;     // threads of a level step
+// parent pairs per thread and per tile of a level step, for NF children per
+// parent: the tile's list of surviving children (2 B each) stays within 16 KiB
+constexpr uint32_t step_ppt(int nf) { return nf <= 4 ? 2u : 1u; }
+constexpr uint32_t step_tile(int nf) { return STEP_THREADS * step_ppt(nf); }
+constexpr uint32_t TRAV_PARTS = 2048;      // most workgroups of a pass that counts node tests
 constexpr uint32_t SCAN_TILE_ITEMS = 4096;                 // counts per scan tile
 
 __host__ __device__ constexpr size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -321,6 +317,11 @@ inline size_t hit_slots_bytes(uint32_t slots)
     return 3 * align256((size_t)slots * 16) + align256((size_t)slots * 8) + (size_t)HIT_MAX_GRID * 3 * 8;
 }
 
+// the vertex arrays of crsh_scene
+struct tri_verts {
+    const float *v[9];
+};
+
 // Stage launchers shared by the plain entry points (bd == nullptr) and the
 // batched form (bd: the batch's device view, frame-aware kernels).
 struct batch_dev;
@@ -367,7 +368,6 @@ void hit_final_launch(const crsh_rays *sorted, const uint32_t *sorted_ids, const
                       const hit_slots_ws &hs, int32_t bundle, const crsh_scene *scene, float t_min,
                       crsh_hits *hits, crsh_meta *meta, const batch_dev *bd, uint32_t parts,
                       hipStream_t stream);
-void tri_spheres_launch(const crsh_scene *scene, uint32_t b, uint32_t e, float4 *out, hipStream_t stream);
 size_t leaf_hit_ws_bytes(uint32_t m, uint32_t node_cap, uint64_t level2_cap, uint32_t rays);
 size_t sort_chunked_ws_bytes(uint32_t cap);
 

@@ -51,9 +51,6 @@ constexpr float FLT_KEEP = -2.0f;          // |O||D| of a ray that the filter ma
 // Per triangle: (2 e2, E0), (-(2 e2 x v0 + e2 x e1), E1), (e2 x e1, 0) with
 // T = E0 |O||D| + E1 |D|.  Entry m pads a leaf's last triangles: its T is
 // negative for every ray (rejected).
-struct tri_verts {
-    const float *v[9];
-};
 __device__ __forceinline__ void put_tri(const tri_verts &V, uint32_t t, uint32_t m, const hit_tris_ws &out)
 {
     float4 *const tri = out.tri + 3 * (size_t)t, *const ftri = out.ftri + 3 * (size_t)t;

@@ -46,14 +46,10 @@ static lh_ws carve(void *ws, uint32_t m, uint32_t node_cap, uint64_t cap2, uint3
     w += align256((size_t)node_cap * 16);
     L.ns = (float *)w;
     w += align256((size_t)node_cap * 4);
+    L.S = trav_scratch{};
     L.S.cnt = (uint32_t *)w;
     w += align256(tiles * 4);
-    L.S.off = nullptr;
-    L.S.mask = (uint32_t *)w;
-    w += align256(tiles * LEVEL_THREADS * 4 + 4);
-    L.S.scan_flags = (uint64_t *)w;
-    w += align256((tiles / SCAN_TILE + 2) * 8);
-    L.S.scan_ctr = (uint32_t *)w;
+    L.S.bits = (uint32_t *)w;
     return L;
 }
 
@@ -62,7 +58,7 @@ size_t leaf_hit_ws_bytes(uint32_t m, uint32_t node_cap, uint64_t cap2, uint32_t 
     const uint64_t tiles = lh_tiles(cap2) + 1;
     return hit_tris_bytes(m) + hit_slots_bytes(slots) + align256((size_t)m * 16) +
            align256((size_t)node_cap * 16) * 2 + align256((size_t)node_cap * 4) + align256(tiles * 4) +
-           align256(tiles * LEVEL_THREADS * 4 + 4) + align256((tiles / SCAN_TILE + 2) * 8) + align256(4);
+           align256(tiles * LEVEL_THREADS * 4 + 4);
 }
 
 // level-1 pairs formed: the survivors of every tile of the level-1 count
@@ -116,8 +112,7 @@ crsh_status leaf_hit_launch(const crsh_rays *sorted, const uint32_t *sorted_ids,
     }
     const lh_ws L = carve(ws, scene->m, nodes->capacity, level2->capacity, slots);
     hit_pack_launch(scene, L.tri, sorted, L.hs, bundle, meta, bd, stream);
-    tri_spheres_launch(scene, 0, scene->m, L.tsph, stream);
-    node_pack_launch(nodes, meta, L.na, L.nb, L.ns, false, stream);
+    trav_prep_launch(scene, 0, scene->m, L.tsph, nodes, meta, L.na, L.nb, L.ns, L.S, 0, 0, stream);
     // level-1 pairs stored by a top-level pass at level 1
     const uint32_t parts = hit_pairs_launch(L.tri, L.hs, level1, bundle, scene, t_min, hits, meta, bd, hit_block, stream);
     // the level-1 node tests: pass bits and survivors per tile, node tests
@@ -126,11 +121,11 @@ crsh_status leaf_hit_launch(const crsh_rays *sorted, const uint32_t *sorted_ids,
     P.p[0] = pairs_dev{level1->tri, level1->node, level1->capacity, 0u, 0u};
     P.p[1] = pairs_dev{level2->tri, level2->node, level2->capacity, 0u, 0u};
     level_count_launch(2, merge, L.na, L.nb, L.ns, L.tsph, scene->m, P, L.S, meta, bd, lh_tiles(level2->capacity),
-                       top_levels, stream, false);
+                       top_levels, stream);
     const uint32_t gs = (uint32_t)std::max<uint64_t>(std::min<uint64_t>((lh_tiles(level2->capacity) + 255) / 256,
                                                                         1024), 1);
     k_lh_survivors<<<gs, 256, 0, stream>>>(L.S, meta, level2->capacity);
-    hit_masked_launch(sorted, L.tri.tri, L.hs, level2, L.S.mask, merge, bundle, scene, t_min, hits, meta, bd,
+    hit_masked_launch(sorted, L.tri.tri, L.hs, level2, L.S.bits, merge, bundle, scene, t_min, hits, meta, bd,
                       hit_block, stream);
     hit_final_launch(sorted, sorted_ids, L.tri.tri, L.hs, bundle, scene, t_min, hits, meta, bd, parts, stream);
     return hip_check(hipGetLastError(), "crsh_leaf_hit launch");

@@ -1,21 +1,22 @@
 // Stage 4: hierarchy traversal (Sec. 3.3.7, Eq. 9).
 //
-// Every level is produced in three launches with no wait between blocks:
-//   count  each work item (top level: one (top node, mesh) pair per wave;
-//          lower levels: a tile of 256 parent pairs, one (parent, child)
-//          test per lane, child nodes read from a run of them copied to
-//          LDS) runs its Eq. 9 tests and records how many pass
-//          (lower levels also keep the pass bits, one per child slot,
-//          packed in 32-bit words);
-//   scan   exclusive scan of the counts -> output offset of every item;
-//   emit   each item writes its survivors at its offset, in (parent pair,
-//          child) order -- at the top level (node, mesh, triangle) order;
-//          lower levels in tiles of two count tiles, staged through LDS.
-// The pair arrays therefore come out trimmed (Fig. 4) and in the order of a
-// sequential traversal, so they are deterministic.  Work is spread with
-// grid-stride loops; nothing depends on which blocks are resident.  Pairs are
-// two arrays (triangle, node) or, for crsh_traverse_packed, one 32-bit word
-// each (Sec. 3.3.7's encoding), a compile-time choice of every kernel.
+// A level's pairs are written together with what the next level needs of
+// them: the Eq. 9 tests of every pair's children run where the pair is
+// emitted, while its triangle and node are in registers.  Per level:
+//   scan   exclusive scan of the survivors of every tile of pairs -> where a
+//          tile's children go on the next level;
+//   step   the pairs of a tile that have surviving children write them at that
+//          place, in (parent pair, child) order, staged through LDS; every
+//          pair written is tested against the children of its node at once
+//          (child nodes read from a run of them copied to LDS) and leaves a
+//          pass bit per child and the survivors of its tile for the next scan.
+// The top level comes before, from its own count (one (top node, mesh) pair
+// per wave), scan and emit; its emit tests the children in the same way.  No
+// launch waits between blocks but the scan's look-back.
+// The pair arrays come out trimmed (Fig. 4) and in the order of a sequential
+// traversal, so they are deterministic.  Pairs are two arrays (triangle, node)
+// or, for crsh_traverse_packed, one 32-bit word each (Sec. 3.3.7's encoding),
+// a compile-time choice of every kernel.
 //
 // Batched form: frames have their own top levels, so levels are produced from
 // the highest down; on each level the pairs that descend from the level above
@@ -23,52 +24,56 @@
 // of the frames whose top is this level.  A top-level item is (frame, top
 // node, mesh of the frame); a parent's children are the range recorded with
 // it by the build (first child, count), so below the top a frame is looked
-// up only when a count block copies a new run of child nodes to LDS.
+// up only when a block copies a new run of child nodes to LDS.
+//
+// crsh_leaf_hit forms the level-1 pass bits from the stored level-2 pairs with
+// a count pass of its own (k_level_count_lanes).
 #include "bounds.hpp"
 #include "traverse.hpp"
 
 
 namespace crsh {
 
-__global__ void k_tri_sph(const float *__restrict__ v0x, const float *__restrict__ v0y,
-                          const float *__restrict__ v0z, const float *__restrict__ v1x,
-                          const float *__restrict__ v1y, const float *__restrict__ v1z,
-                          const float *__restrict__ v2x, const float *__restrict__ v2y,
-                          const float *__restrict__ v2z, uint32_t b, uint32_t e, float4 *out)
+// One launch before the traversal:
+// - bounding spheres of the triangles [b, e);
+// - traversal copy of the nodes: (cx, cy, cz, r), (ax, ay, az, tan) and sec,
+//   with sec = -1 marking a cone of 90 degrees or more (c <= 0 gives no
+//   positive sec, c > 0 always does), so one test reads 36 bytes in 3 loads;
+// - n_cnt tile counts and the workgroup sums of S cleared (n_cnt != 0), the
+//   per-call pair counts cleared and a hierarchy of more levels than there is
+//   pair storage for flagged (levels != 0).
+__global__ void k_trav_prep(tri_verts V, uint32_t b, uint32_t e, float4 *tsph, node_arrays nd, crsh_meta *meta,
+                            float4 *na, float4 *nb, float *ns, trav_scratch S, uint64_t n_cnt, uint32_t levels)
 {
-    const float third = 1.0f / 3.0f;
-    for (uint32_t t = b + blockIdx.x * blockDim.x + threadIdx.x; t < e; t += gridDim.x * blockDim.x) {
-        f3 a = mk(v0x[t], v0y[t], v0z[t]);
-        f3 bb = mk(v1x[t], v1y[t], v1z[t]);
-        f3 c = mk(v2x[t], v2y[t], v2z[t]);
-        f3 ctr = ((a + bb) + c) * third;
-        float r = fmax2(fmax2(len(a - ctr), len(bb - ctr)), len(c - ctr));
-        float m = fmax2(fmax2(fabsf(ctr.x), fabsf(ctr.y)), fabsf(ctr.z));
-        r = r + SPHERE_PAD * (r + m);
-        out[t] = make_float4(ctr.x, ctr.y, ctr.z, r);
-    }
-}
-
-// Traversal copy of the nodes: (cx, cy, cz, r), (ax, ay, az, tan) and sec,
-// with sec = -1 marking a cone of 90 degrees or more (c <= 0 gives no
-// positive sec, c > 0 always does), so one test reads 36 bytes in 3 loads.
-// Also clears the per-call pair counts.
-__global__ void k_node_pack(node_arrays nd, crsh_meta *meta, float4 *na, float4 *nb, float *ns, bool clear_pairs)
-{
+    const uint32_t gid = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
     const uint32_t nl = meta->n_levels;
+    if (levels && gid < CRSH_MAX_LEVELS) meta->pairs[gid] = 0;
+    if (levels && gid == 0 && nl > levels) atomicOr(&meta->status, CRSH_OVERFLOW_PAIRS);
+    for (uint64_t i = gid; i < n_cnt; i += stride) S.cnt[i] = 0u;
+    if (n_cnt && gid < TRAV_PARTS) S.part[gid] = 0u;
     const uint32_t total = nl ? meta->level_off[nl - 1] + meta->level_cnt[nl - 1] : 0;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
+    for (uint32_t i = gid; i < total; i += stride) {
         na[i] = make_float4(nd.cx[i], nd.cy[i], nd.cz[i], nd.r[i]);
         nb[i] = make_float4(nd.ax[i], nd.ay[i], nd.az[i], nd.tan[i]);
         ns[i] = nd.c[i] > 0.0f ? nd.sec[i] : -1.0f;
     }
-    if (clear_pairs && blockIdx.x == 0 && threadIdx.x < CRSH_MAX_LEVELS) meta->pairs[threadIdx.x] = 0;
+    const float third = 1.0f / 3.0f;
+    for (uint64_t t = (uint64_t)b + gid; t < e; t += stride) {
+        const f3 p = mk(V.v[0][t], V.v[1][t], V.v[2][t]);
+        const f3 q = mk(V.v[3][t], V.v[4][t], V.v[5][t]);
+        const f3 u = mk(V.v[6][t], V.v[7][t], V.v[8][t]);
+        const f3 c = ((p + q) + u) * third;
+        float r = fmax2(fmax2(len(p - c), len(q - c)), len(u - c));
+        const float m = fmax2(fmax2(fabsf(c.x), fabsf(c.y)), fabsf(c.z));
+        r = r + SPHERE_PAD * (r + m);
+        tsph[t] = make_float4(c.x, c.y, c.z, r);
+    }
 }
 
 // number of work items of a level: top level (parent_level 0) = top nodes x
-// meshes, lower levels = tiles of LEVEL_TILE parent pairs
+// meshes, lower levels = tiles of `tile` parent pairs
 __device__ __forceinline__ uint64_t level_items(const crsh_meta *meta, int32_t parent_level, uint32_t n_mesh,
-                                                const pair_levels &P)
+                                                const pair_levels &P, uint32_t tile)
 {
     const uint32_t nl = meta->n_levels;
     if (parent_level == 0) return nl ? (uint64_t)meta->level_cnt[nl - 1] * n_mesh : 0;
@@ -76,20 +81,24 @@ __device__ __forceinline__ uint64_t level_items(const crsh_meta *meta, int32_t p
     uint64_t nin = meta->pairs[parent_level - 1];
     const uint64_t cap = P.p[parent_level - 1].cap;
     nin = nin < cap ? nin : cap;
-    return (nin + LEVEL_TILE - 1) / LEVEL_TILE;
+    return (nin + tile - 1) / tile;
 }
 
-__device__ __forceinline__ void clear_scan(const trav_scratch &S, uint64_t items)
+// the look-back words and the ticket of the scan that follows this launch
+__device__ __forceinline__ void clear_scan(const trav_scratch &S)
 {
-    const uint64_t nt = (items + SCAN_TILE - 1) / SCAN_TILE;
-    const uint64_t gid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (uint64_t i = gid; i < nt; i += (uint64_t)gridDim.x * blockDim.x) S.scan_flags[i] = 0;
+    const uint32_t gid = blockIdx.x * blockDim.x + threadIdx.x;
+    for (uint32_t i = gid; i < S.n_flags; i += gridDim.x * blockDim.x) S.scan_flags[i] = 0;
     if (gid == 0) *S.scan_ctr = 0;
 }
 
 // ------------------------------------------------------------- top level
 // Item -> (node i within the level, mesh m).  Plain: item = i * n_mesh + m.
-// Batch: the item's frame, then (top node, mesh) within the frame.
+// Batch: the item's frame, then (top node, mesh) within the frame.  A wave's
+// items -- wave, wave + nwaves, wave + 2 nwaves, ... -- are looked up one per
+// lane, 64 at a time, and those with triangles to test worked on one after
+// the other by the whole wave, their values taken from the lane that has
+// them.
 template <bool BATCH>
 __device__ __forceinline__ void top_item(uint64_t item, uint32_t n_mesh, uint32_t top, uint32_t off,
                                          const batch_dev &bd, const float4 *na, const float4 *nb, const float *ns,
@@ -123,6 +132,20 @@ __device__ __forceinline__ void top_item(uint64_t item, uint32_t n_mesh, uint32_
     }
 }
 
+__device__ __forceinline__ uint32_t from_lane(uint32_t v, uint32_t src) { return __builtin_amdgcn_readlane(v, src); }
+__device__ __forceinline__ float from_lane(float v, uint32_t src)
+{
+    return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), src));
+}
+__device__ __forceinline__ float4 from_lane(float4 v, uint32_t src)
+{
+    return make_float4(from_lane(v.x, src), from_lane(v.y, src), from_lane(v.z, src), from_lane(v.w, src));
+}
+__device__ __forceinline__ uint64_t from_lane(uint64_t v, uint32_t src)
+{
+    return (uint64_t)from_lane((uint32_t)(v >> 32), src) << 32 | from_lane((uint32_t)v, src);
+}
+
 // top level of this pass (0-based) and its number of items
 template <bool BATCH>
 __device__ __forceinline__ bool top_pass(const crsh_meta *meta, const batch_dev &bd, uint32_t L, uint32_t n_mesh,
@@ -136,7 +159,7 @@ __device__ __forceinline__ bool top_pass(const crsh_meta *meta, const batch_dev 
         n_items = bd.top[0];
     } else {
         top = nl - 1;
-        n_items = level_items(meta, 0, n_mesh, P);
+        n_items = level_items(meta, 0, n_mesh, P, 1u);
     }
     return true;
 }
@@ -153,96 +176,188 @@ __global__ __launch_bounds__(256) void k_top_count(const float4 *__restrict__ na
     __shared__ uint64_t s_red[3][256 / WAVE];
     uint32_t top;
     uint64_t n_items;
+    clear_scan(S);
     if (!top_pass<BATCH>(meta, bd, L, n_mesh, P, top, n_items)) return;
-    clear_scan(S, n_items);
     const uint32_t off = meta->level_off[top];
     const uint32_t l = lane_id();
     const uint64_t wave = (uint64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
     const uint64_t nwaves = (uint64_t)gridDim.x * (blockDim.x / WAVE);
-    uint64_t tests = 0, mhits = 0, items = 0;
-    for (uint64_t it = wave; it < n_items; it += nwaves) {
-        float4 A, Bv;
-        float Sg;
-        uint32_t i, b, e;
+    uint64_t tests = 0, mhits = 0, items = 0;       // tests: this lane's
+    for (uint64_t it0 = wave; it0 < n_items; it0 += nwaves * WAVE) {
+        const uint64_t it = it0 + l * nwaves;
+        const bool real = it < n_items;
+        float4 lA, lB;
+        float lS;
+        uint32_t i, lb, le;
         bool pass;
-        top_item<BATCH>(it, n_mesh, top, off, bd, na, nb, ns, msph, mesh_first, mesh_count, tri_begin, tri_end,
-                        A, Bv, Sg, i, b, e, pass);
-        ++items;
-        mhits += pass ? 1 : 0;
-        tests += e - b;
-        uint32_t cnt = 0;
-        for (uint32_t t0 = b; t0 < e; t0 += WAVE) {
-            const uint32_t t = t0 + l;
-            bool ok = false;
-            if (t < e) {
-                const float4 s = tsph[t];
-                ok = packed_meets(A, Bv, Sg, mk(s.x, s.y, s.z), s.w);
+        top_item<BATCH>(real ? it : it0, n_mesh, top, off, bd, na, nb, ns, msph, mesh_first, mesh_count, tri_begin,
+                        tri_end, lA, lB, lS, i, lb, le, pass);
+        items += (uint64_t)__popcll(ballot(real));
+        mhits += (uint64_t)__popcll(ballot(real && pass));
+        if (real) tests += le - lb;
+        if (real && le == lb) S.cnt_top[it] = 0u;
+        for (uint64_t todo = ballot(real && le > lb); todo; todo &= todo - 1u) {
+            const uint32_t src = (uint32_t)__builtin_ctzll(todo);
+            const float4 A = from_lane(lA, src), Bv = from_lane(lB, src);
+            const float Sg = from_lane(lS, src);
+            const uint32_t b = from_lane(lb, src), e = from_lane(le, src);
+            uint32_t cnt = 0;
+            for (uint32_t t0 = b; t0 < e; t0 += WAVE) {
+                const uint32_t t = t0 + l;
+                bool ok = false;
+                if (t < e) {
+                    const float4 s = tsph[t];
+                    ok = packed_meets(A, Bv, Sg, mk(s.x, s.y, s.z), s.w);
+                }
+                cnt += (uint32_t)__popcll(ballot(ok));
             }
-            cnt += (uint32_t)__popcll(ballot(ok));
+            if (l == src) S.cnt_top[it] = cnt;
         }
-        if (l == 0) S.cnt[it] = cnt;
     }
+    tests = wave_sum(tests);
     if (l == 0) {
         s_red[0][threadIdx.x / WAVE] = tests;
         s_red[1][threadIdx.x / WAVE] = mhits;
         s_red[2][threadIdx.x / WAVE] = items;
     }
+    // the scan that follows adds the blocks' sums to meta (atomics of every
+    // block on three words would outlast a small frame's pass)
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint64_t a = 0, bq = 0, c = 0;
-        for (int w = 0; w < 256 / WAVE; ++w) {
-            a += s_red[0][w];
-            bq += s_red[1][w];
-            c += s_red[2][w];
-        }
-        if (a) atomicAdd((unsigned long long *)&meta->tests[top], (unsigned long long)a);
-        if (bq) atomicAdd((unsigned long long *)&meta->mesh_hits, (unsigned long long)bq);
-        if (c) atomicAdd((unsigned long long *)&meta->mesh_tests, (unsigned long long)c);
+    if (threadIdx.x < 3) {
+        uint64_t t = 0;
+        for (int w = 0; w < 256 / WAVE; ++w) t += s_red[threadIdx.x][w];
+        S.top_part[3 * blockIdx.x + threadIdx.x] = t;
     }
 }
 
-template <bool BATCH, bool PACKED = false>
+// Pass bits of a pair's children: one byte per pair for merge factors up to
+// 8, else two.
+template <int NF>
+struct mask_type {
+    typedef uint8_t t;
+};
+template <>
+struct mask_type<16> {
+    typedef uint16_t t;
+};
+
+// NF: the merge factor rounded up to a power of two.  Top-level pairs written
+// at or above level `lowest` + 1 are tested against their node's children.
+template <int NF, bool BATCH, bool PACKED>
 __global__ __launch_bounds__(256) void k_top_emit(const float4 *__restrict__ na, const float4 *__restrict__ nb,
                                                   const float *__restrict__ ns, const float4 *__restrict__ tsph,
                                                   const uint32_t *__restrict__ mesh_first,
                                                   const uint32_t *__restrict__ mesh_count,
                                                   const float *__restrict__ msph, uint32_t n_mesh,
-                                                  uint32_t tri_begin, uint32_t tri_end, pair_levels P,
-                                                  trav_scratch S, const crsh_meta *meta, batch_dev bd, uint32_t L)
+                                                  uint32_t tri_begin, uint32_t tri_end, uint32_t F, uint32_t lowest,
+                                                  pair_levels P, trav_scratch S, const crsh_meta *meta, batch_dev bd,
+                                                  uint32_t L)
 {
+    typedef typename mask_type<NF>::t mask_t;
+    constexpr uint32_t TILE = step_tile(NF);
+    __shared__ uint64_t s_red[256 / WAVE];
+    __shared__ float4 s_ca[256 / WAVE][NF], s_cb[256 / WAVE][NF];   // a wave's item: children of its node
+    __shared__ float s_cs[256 / WAVE][NF];
+    const uint32_t wib = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     uint32_t top;
     uint64_t n_items;
+    clear_scan(S);
     if (!top_pass<BATCH>(meta, bd, L, n_mesh, P, top, n_items)) return;
     const pairs_dev out = P.p[top];
     if (out.tri == nullptr) return;
+    const bool test = top >= lowest;         // level top + 1 (1-based) >= lowest + 1
+    mask_t *const mask = (mask_t *)S.mask[(top + 1) & 1];
     const uint32_t off = meta->level_off[top];
+    const uint32_t offk = test ? meta->level_off[top - 1] : 0u, nk = test ? meta->level_cnt[top - 1] : 0u;
     const uint32_t l = lane_id();
     const uint64_t wave = (uint64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
     const uint64_t nwaves = (uint64_t)gridDim.x * (blockDim.x / WAVE);
-    for (uint64_t it = wave; it < n_items; it += nwaves) {
-        if (S.cnt[it] == 0) continue;
-        float4 A, Bv;
-        float Sg;
-        uint32_t i, b, e;
+    uint64_t tests = 0;
+    for (uint64_t it0 = wave; it0 < n_items; it0 += nwaves * WAVE) {
+        const uint64_t it = it0 + l * nwaves;
+        const bool some = it < n_items && S.cnt_top[it] != 0;
+        uint64_t todo = ballot(some);
+        if (todo == 0) continue;
+        float4 lA, lB;
+        float lS;
+        uint32_t li, lb, le;
         bool pass;
-        top_item<BATCH>(it, n_mesh, top, off, bd, na, nb, ns, msph, mesh_first, mesh_count, tri_begin, tri_end,
-                        A, Bv, Sg, i, b, e, pass);
-        uint64_t pos = S.off[it];
-        for (uint32_t t0 = b; t0 < e; t0 += WAVE) {
-            const uint32_t t = t0 + l;
-            bool ok = false;
-            if (t < e) {
-                const float4 s = tsph[t];
-                ok = packed_meets(A, Bv, Sg, mk(s.x, s.y, s.z), s.w);
+        const uint64_t use = some ? it : it0 + (uint64_t)__builtin_ctzll(todo) * nwaves;
+        top_item<BATCH>(use, n_mesh, top, off, bd, na, nb, ns, msph, mesh_first, mesh_count, tri_begin, tri_end,
+                        lA, lB, lS, li, lb, le, pass);
+        const uint64_t lpos = S.off[use];
+        // the node's children
+        uint32_t lfirst = li * F, lnch = 0u;
+        if (test) {
+            lnch = lfirst < nk ? min(F, nk - lfirst) : 0u;
+            if constexpr (BATCH) {
+                lfirst = bd.node_first[off + li];
+                lnch = lfirst < nk ? min(bd.node_info[off + li] & INFO_COUNT_MASK, nk - lfirst) : 0u;
             }
-            const uint64_t mask = ballot(ok);
-            const uint64_t at = pos + rank_below(mask);
-            if (ok && at < out.cap) {
-                pair_put<PACKED>(out, at, t, i);
+        }
+        for (; todo; todo &= todo - 1u) {
+            const uint32_t src = (uint32_t)__builtin_ctzll(todo);
+            const float4 A = from_lane(lA, src), Bv = from_lane(lB, src);
+            const float Sg = from_lane(lS, src);
+            const uint32_t i = from_lane(li, src), b = from_lane(lb, src), e = from_lane(le, src);
+            const uint32_t first = from_lane(lfirst, src), nch = from_lane(lnch, src);
+            __builtin_amdgcn_wave_barrier();     // the previous item's reads come first
+            if (l < nch) {
+                s_ca[wib][l] = na[offk + first + l];
+                s_cb[wib][l] = nb[offk + first + l];
+                s_cs[wib][l] = ns[offk + first + l];
             }
-            pos += (uint32_t)__popcll(mask);
+            __builtin_amdgcn_wave_barrier();
+            uint64_t pos = from_lane(lpos, src);
+            uint64_t tile = pos / TILE;          // survivors of the tile being written
+            uint32_t in_tile = 0u;
+            float4 s_n = b < e ? tsph[min(b + l, e - 1)] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            for (uint32_t t0 = b; t0 < e; t0 += WAVE) {
+                const uint32_t t = t0 + l;
+                const float4 s = s_n;                // the next 64 are requested before these are tested
+                s_n = tsph[min(min(t0 + WAVE, e - 1) + l, e - 1)];
+                const uint64_t in_mesh = e - t0 >= WAVE ? ~0ull : (1ull << (e - t0)) - 1ull;
+                const uint64_t mk64 = packed_meets_mask(A, Bv, Sg, mk(s.x, s.y, s.z), s.w) & in_mesh;
+                if (mk64 == 0) continue;
+                const uint32_t rank = rank_below(mk64);
+                const uint64_t at = pos + rank;
+                const bool put = ((mk64 >> l) & 1u) && at < out.cap;
+                if (put) pair_put<PACKED>(out, at, t, i);
+                if (test) {
+                    const uint64_t pm = ballot(put);
+                    // the lanes whose pair lies in the current tile; the others in the next
+                    const uint64_t in = ballot(at / TILE == tile);
+                    uint32_t bits = 0u, ca = 0u, cb = 0u;
+                    auto child = [&](uint32_t r) {
+                        const uint64_t m = packed_meets_mask(s_ca[wib][r], s_cb[wib][r], s_cs[wib][r],
+                                                             mk(s.x, s.y, s.z), s.w) & pm;
+                        bits = bits + bits + (__builtin_amdgcn_inverse_ballot_w64(m) ? 1u : 0u);
+                        ca += (uint32_t)__popcll(m & in);
+                        cb += (uint32_t)__popcll(m & ~in);
+                    };
+                    if (nch == NF) {
+#pragma unroll
+                        for (uint32_t r = NF; r-- > 0;) child(r);
+                    } else {
+                        for (uint32_t r = nch; r-- > 0;) child(r);
+                    }
+                    if (put) mask[at] = (mask_t)bits;
+                    tests += (uint64_t)__popcll(pm) * nch;
+                    in_tile += ca;
+                    if ((pos + (uint32_t)__popcll(mk64)) / TILE != tile) {
+                        if (l == 0 && in_tile) atomicAdd(&S.cnt[tile], in_tile);
+                        ++tile;
+                        in_tile = cb;
+                    }
+                }
+                pos += (uint32_t)__popcll(mk64);
+            }
+            if (l == 0 && in_tile) atomicAdd(&S.cnt[tile], in_tile);
         }
     }
+    if (l == 0) s_red[threadIdx.x / WAVE] = tests;
+    __syncthreads();
+    if (threadIdx.x == 0) S.part[blockIdx.x] += s_red[0] + s_red[1] + s_red[2] + s_red[3];
 }
 
 // ----------------------------------------------------------- lower levels
@@ -317,7 +432,7 @@ __device__ __forceinline__ float quad_pick_again(float v, uint32_t r)
 // parent's children are the range the build recorded with it (first,
 // count); the lane that reads a parent's pair reads that record too, in the
 // same stage as the sphere, and puts it in the parent's LDS record.
-template <int NF, bool BATCH, bool PACKED, bool STAGED>
+template <int NF, bool BATCH, bool STAGED>
 __global__ __launch_bounds__(COUNT_THREADS) void k_level_count_lanes(int32_t parent_level, uint32_t F,
                                                                      const float4 *__restrict__ na,
                                                                      const float4 *__restrict__ nb,
@@ -345,8 +460,7 @@ __global__ __launch_bounds__(COUNT_THREADS) void k_level_count_lanes(int32_t par
     __shared__ float s_ws[WN];
     const uint32_t nl = meta->n_levels;
     if ((uint32_t)parent_level > nl || parent_level < 2) return;
-    const uint64_t ntiles = level_items(meta, parent_level, 0, P);
-    clear_scan(S, ntiles);                  // the scan that follows reads these
+    const uint64_t ntiles = level_items(meta, parent_level, 0, P, LEVEL_TILE);
     const pairs_dev in = P.p[parent_level - 1];
     if (in.tri == nullptr || P.p[parent_level - 2].tri == nullptr) return;
     uint64_t nin = meta->pairs[parent_level - 1];
@@ -401,14 +515,9 @@ __global__ __launch_bounds__(COUNT_THREADS) void k_level_count_lanes(int32_t par
         const uint32_t nq = lhi == 0u ? min(llo, (uint32_t)LEVEL_TILE) : (lhi >> 31 ? 0u : (uint32_t)LEVEL_TILE);
         const __amdgpu_buffer_rsrc_t rt = make_rsrc(in.tri + q0, (uint64_t)nq * 4u);
         const uint32_t w = __builtin_amdgcn_raw_buffer_load_b32(rt, own * 4u, 0, 0);
-        if constexpr (PACKED) {
-            tri = in.tri_base + (w & ((1u << CRSH_PACKED_TRI_BITS) - 1u));
-            par = own < nq ? w >> CRSH_PACKED_TRI_BITS : NONE;
-        } else {
-            const __amdgpu_buffer_rsrc_t rn = make_rsrc(in.node + q0, (uint64_t)nq * 4u);
-            tri = w;
-            par = own < nq ? __builtin_amdgcn_raw_buffer_load_b32(rn, own * 4u, 0, 0) : NONE;
-        }
+        const __amdgpu_buffer_rsrc_t rn = make_rsrc(in.node + q0, (uint64_t)nq * 4u);
+        tri = w;
+        par = own < nq ? __builtin_amdgcn_raw_buffer_load_b32(rn, own * 4u, 0, 0) : NONE;
     };
     uint64_t tests = 0;                     // wave-wide
     uint32_t parity = 0;
@@ -452,7 +561,7 @@ __global__ __launch_bounds__(COUNT_THREADS) void k_level_count_lanes(int32_t par
     for (uint32_t step = blockIdx.x; step < nsteps32; step += gridDim.x, parity ^= 1u) {
         const uint64_t tile = step * COUNT_TPS + half;
         // this wave's slice-0 word of the tile's pass masks (scalar)
-        uint2 *const mrow = (uint2 *)S.mask + (tile * LEVEL_TILE + tw * PW) * NF / 64;
+        uint2 *const mrow = (uint2 *)S.bits + (tile * LEVEL_TILE + tw * PW) * NF / 64;
         const __amdgpu_buffer_rsrc_t mrs = make_rsrc(mrow, tile < ntiles ? (NF - 1) * (PR * NF / 64) * 8u + 8u : 0u);
         // this step's parent values: kept in registers (quad broadcast) or
         // put in the wave's records (the wave's previous reads of them are
@@ -645,110 +754,304 @@ __global__ __launch_bounds__(COUNT_THREADS) void k_level_count_lanes(int32_t par
     }
 }
 
-// Survivors of a tile are first placed in LDS at their tile-local offsets
-// and then copied out with consecutive lanes writing consecutive pairs, so
-// the stores are coalesced whatever the pass masks.
-// Emit pass: PPT parent pairs per thread, EMIT_TILE per block iteration,
-// covering EMIT_PPT / LEVEL_PPT count tiles (their masks, survivor counts and
-// the first one's output offset).
-template <int NF, int PPT, bool BATCH, bool PACKED = false>
-__global__ __launch_bounds__(LEVEL_THREADS) void k_level_emit(int32_t parent_level, uint32_t F, pair_levels P,
-                                                              trav_scratch S, const crsh_meta *meta, batch_dev bd)
+// One level step: tiles of step_tile(NF) parent pairs of level parent_level,
+// their surviving children written on the level below and, TEST, tested
+// against their own children (level parent_level - 2) for the next step.
+//
+// A thread holds step_ppt(NF) consecutive parents' pass bits; a block scan
+// places their survivors, which are listed in LDS (2 bytes: parent of the
+// tile, child), so the writing lanes are full and store consecutive pairs
+// whatever the bits.  A lane then owns one written pair: its triangle sphere
+// is read once for all its children, its pass bits go out as one byte (two
+// for merge factors above 8) and the survivors of every 64 consecutive pairs
+// are added up as wave masks, then per tile of the next level in LDS.
+//
+// Child nodes (36 bytes a test) come from LDS where they can (STAGED): the
+// descendants of one top-level node on a level are a contiguous run, aligned
+// from the frame's first node, and pairs are ordered by top-level node first,
+// so consecutive tiles keep testing children of the same nodes.  A block
+// copies the children of the run of nodes that its first written pair names,
+// and of as many whole runs after it as fit, child r of every node in an
+// array of its own (lanes with neighbouring nodes then read neighbouring
+// 16 bytes); pairs outside the copy read the node arrays.  Blocks take
+// several consecutive tiles at a time where there are enough, so that a copy
+// lasts.
+//
+// What bounds it: the tests' arithmetic (1080p frame of 201,632 triangles, the
+// step that tests level 1: vector ALUs 75 % busy, 175 lane instructions per
+// written pair, about 30 a test); the last step (no test) writes and reads
+// pairs at 4.6 TB/s, near the 5.3 TB/s a large copy reaches.  Measured on that
+// frame: steps 1.33 + 2.45 + 5.13 + 8.40 + 4.29 ms and the top emit 0.61, where
+// a count pass and an emit pass per level, each reading the pair list, took
+// 29.1 ms; 1024x1024 reflections 2.07 ms (2.7), 24 frames of a batch 5.3 (7.4).
+// Requesting a tile's inputs a tile ahead is what pays for the fusion (24 to 28
+// ms without), and 6 waves per SIMD: the compiler's own choice is 4, where only
+// merge factors above 8 stay (their lists need the LDS of 4).
+template <int NF, bool BATCH, bool PACKED, bool TEST, bool STAGED>
+__global__ __launch_bounds__(STEP_THREADS, NF == 16 ? 4 : 6) void k_level_step(int32_t parent_level, uint32_t F,
+                                                             const float4 *__restrict__ na,
+                                                             const float4 *__restrict__ nb,
+                                                             const float *__restrict__ ns,
+                                                             const float4 *__restrict__ tsph, uint32_t m,
+                                                             pair_levels P, trav_scratch S, const crsh_meta *meta,
+                                                             batch_dev bd)
 {
-    static_assert(PPT * NF <= 32, "one bit per child");
-    constexpr uint32_t TILE = LEVEL_THREADS * PPT;
-    constexpr uint32_t TILE_OUT = TILE * NF;
-    constexpr uint32_t R = PPT / LEVEL_PPT;    // count tiles per emit tile
-    static_assert(PPT % LEVEL_PPT == 0, "whole count tiles");
-    __shared__ uint32_t s_scan[LEVEL_THREADS / WAVE];
-    __shared__ uint32_t s_tri[TILE_OUT];
-    __shared__ uint32_t s_node[TILE_OUT];
+    typedef typename mask_type<NF>::t mask_t;
+    constexpr uint32_t PPT = step_ppt(NF), TILE = step_tile(NF);
+    constexpr uint32_t NW = STEP_THREADS / WAVE;
+    constexpr uint32_t WP = COUNT_WINDOW / NF;           // nodes whose children the copy holds
+    constexpr uint32_t WN = TEST && STAGED ? COUNT_WINDOW : 1u;
+    __shared__ uint16_t s_item[TILE * NF];               // 16 x parent of the tile + child
+    __shared__ uint2 s_par[TILE];                        // triangle, first child
+    __shared__ uint32_t s_wave[2][NW];
+    __shared__ uint32_t s_next[NF + 2];                  // survivors per tile of the next level
+    __shared__ float4 s_wa[WN], s_wb[WN];
+    __shared__ float s_ws[WN];
     const uint32_t nl = meta->n_levels;
+    if (TEST) clear_scan(S);
     if ((uint32_t)parent_level > nl) return;
     const pairs_dev in = P.p[parent_level - 1];
     const pairs_dev out = P.p[parent_level - 2];
     if (in.tri == nullptr || out.tri == nullptr) return;
     uint64_t nin = meta->pairs[parent_level - 1];
     nin = nin < in.cap ? nin : in.cap;
-    const uint64_t ctiles = (nin + LEVEL_TILE - 1) / LEVEL_TILE;
-    const uint64_t ntiles = (nin + TILE - 1) / TILE;
-    const uint32_t offp = meta->level_off[parent_level - 1];
-    const uint32_t np = meta->level_cnt[parent_level - 1];
-    // pass mask (NF bits per parent pair, PPT pairs: bits of one packed
-    // word), survivor count and output offset of emit tile T
-    auto tile_head = [&](uint64_t T, uint32_t &mask, uint32_t &cnt, uint64_t &off) {
-        constexpr uint32_t BITS = PPT * NF;
-        const uint64_t p0 = T * TILE + (uint64_t)threadIdx.x * PPT;
-        mask = 0;
-        if (p0 < nin) {
-            const uint64_t bit = p0 * NF;
-            const uint32_t w = S.mask[bit / 32];
-            mask = BITS == 32 ? w : (w >> (uint32_t)(bit % 32)) & ((1u << (BITS % 32)) - 1u);
-        }
-        cnt = 0;
-#pragma unroll
-        for (uint32_t r = 0; r < R; ++r)
-            if (T * R + r < ctiles) cnt += S.cnt[T * R + r];
-        off = S.off[T * R];
+    const uint32_t ntiles = (uint32_t)min((nin + TILE - 1) / TILE, (uint64_t)0x7FFFFFFFu);
+    const mask_t *const mask = (const mask_t *)S.mask[parent_level & 1];
+    mask_t *const mask_out = (mask_t *)S.mask[(parent_level - 1) & 1];
+    const uint32_t offp = meta->level_off[parent_level - 1], np = meta->level_cnt[parent_level - 1];
+    // the level written and the level below it
+    const uint32_t off1 = meta->level_off[parent_level - 2], n1 = meta->level_cnt[parent_level - 2];
+    const uint32_t off2 = TEST ? meta->level_off[parent_level - 3] : 0u;
+    const uint32_t n2 = TEST ? meta->level_cnt[parent_level - 3] : 0u;
+    const uint32_t l = lane_id();
+    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    // consecutive tiles of a block: up to 8 where every block gets 8 such shares
+    const uint32_t ch = min(max(ntiles / (gridDim.x * 8u), 1u), 8u);
+    auto next_of = [&](uint32_t t) { return (t + 1) % ch ? t + 1 : t + 1 + (gridDim.x - 1) * ch; };
+    // a tile's inputs: pass bits and pairs of this thread's parents, and the
+    // place of the tile's children; nothing looks at them until they are used
+    // (`zero` keeps the last a per-lane value: read as a scalar it would be
+    // waited for at once), so they arrive while the tile before is worked on.
+    // Reads past the level's pairs return zeros (or, one pair past an odd
+    // end, bits that are cut off at use).
+    uint32_t zero = 0u;
+    asm volatile("" : "+v"(zero));
+    struct tile_in {
+        uint32_t bits, tri[PPT], par[PPT];
+        uint64_t off;
     };
-    // Software pipeline over the block's tiles: the pass mask, survivor
-    // count and output offset of the next tile are loaded while the current
-    // tile is compacted, and a tile's parent pairs are requested before its
-    // scan, so no tile waits for two dependent round trips to memory.
-    uint32_t mask_n = 0, cnt_n = 0;
-    uint64_t off_n = 0;
-    if (blockIdx.x < ntiles) tile_head(blockIdx.x, mask_n, cnt_n, off_n);
-    for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const uint32_t mask = mask_n, cnt = cnt_n;
-        const uint64_t base = off_n;
-        const uint64_t q0 = tile * TILE + (uint64_t)threadIdx.x * PPT;
-        uint32_t tri[PPT], par[PPT];
+    auto load_tile = [&](uint32_t t, tile_in &v) {
+        const uint64_t q = (uint64_t)t * TILE;
+        const uint32_t n = t < ntiles ? (uint32_t)min(nin - q, (uint64_t)TILE) : 0u;
+        const __amdgpu_buffer_rsrc_t rm = make_rsrc(mask + q, ((n + PPT - 1) / PPT) * PPT * (uint32_t)sizeof(mask_t));
+        if constexpr (PPT * sizeof(mask_t) == 2)
+            v.bits = __builtin_amdgcn_raw_buffer_load_b16(rm, threadIdx.x * 2u, 0, 0);
+        else
+            v.bits = __builtin_amdgcn_raw_buffer_load_b8(rm, threadIdx.x, 0, 0);
+        const __amdgpu_buffer_rsrc_t rt = make_rsrc(in.tri + q, n * 4u);
+        const __amdgpu_buffer_rsrc_t rn = make_rsrc(PACKED ? in.tri : in.node + q, n * 4u);
 #pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            const bool live = ((mask >> (k * NF)) & ((1u << NF) - 1u)) != 0u && q0 + k < nin;
-            tri[k] = 0u;
-            par[k] = 0u;
-            if (live) pair_get<PACKED>(in, q0 + k, tri[k], par[k]);
+        for (uint32_t k = 0; k < PPT; ++k) {
+            const uint32_t o = (threadIdx.x * PPT + k) * 4u;
+            v.tri[k] = __builtin_amdgcn_raw_buffer_load_b32(rt, o, 0, 0);
+            if constexpr (!PACKED) v.par[k] = __builtin_amdgcn_raw_buffer_load_b32(rn, o, 0, 0);
         }
-        // first child of each parent: p * F, or (batched form) the build's
-        // record, requested here so that its latency overlaps the scan
-        uint32_t first[PPT];
+        v.off = S.off[(t < ntiles ? t : 0u) + zero];
+    };
+    uint32_t wlo = 0u, wlen = 0u;           // nodes whose children are in LDS (block-uniform)
+    uint32_t wend = 0u;                     // children of the copy's frame from the copy's first child on
+    uint32_t wfull = 0u;                    // nodes of the copy with NF children each
+    uint64_t tests64 = 0;                   // this wave's
+    uint32_t parity = 0u;
+    uint64_t prev_tile = 0;                 // first next-level tile of s_next
+    if (TEST && threadIdx.x < NF + 2) s_next[threadIdx.x] = 0u;
+    uint32_t tile = blockIdx.x * ch;
+    tile_in next;
+    if (tile < ntiles) load_tile(tile, next);
+    for (; tile < ntiles; tile = next_of(tile), parity ^= 1u) {
+        const tile_in cur = next;
+        load_tile(next_of(tile), next);
+        const uint32_t q0 = threadIdx.x * PPT;
+        const uint32_t nq = (uint32_t)min(nin - (uint64_t)tile * TILE, (uint64_t)TILE);
+        const uint32_t bits_in = PPT == 2 && q0 + 1 >= nq ? (q0 < nq ? cur.bits & 0xFFu : 0u) : cur.bits;
+        uint32_t mk_[PPT], tri[PPT], first[PPT];
 #pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            first[k] = par[k] * F;
-            if constexpr (BATCH) {
-                const bool live = ((mask >> (k * NF)) & ((1u << NF) - 1u)) != 0u && par[k] < np;
-                first[k] = live ? bd.node_first[offp + par[k]] : 0u;
+        for (uint32_t k = 0; k < PPT; ++k) {
+            mk_[k] = PPT == 2 ? (bits_in >> (8 * k)) & 0xFFu : bits_in;
+            uint32_t par;
+            if constexpr (PACKED) {
+                tri[k] = in.tri_base + (cur.tri[k] & ((1u << CRSH_PACKED_TRI_BITS) - 1u));
+                par = cur.tri[k] >> CRSH_PACKED_TRI_BITS;
+            } else {
+                tri[k] = cur.tri[k];
+                par = cur.par[k];
             }
+            first[k] = par * F;
+            if constexpr (BATCH) first[k] = mk_[k] && par < np ? bd.node_first[offp + par] : 0u;
         }
-        const uint64_t nt = tile + gridDim.x;
-        if (nt < ntiles) tile_head(nt, mask_n, cnt_n, off_n);
-        if (cnt == 0) continue;                  // uniform over the block
-        uint32_t total;
-        const uint32_t ex = block_excl_scan<uint32_t, LEVEL_THREADS / WAVE>((uint32_t)__popc(mask), s_scan, total);
-        if (mask) {
-            uint32_t at = ex;
+        const uint32_t mine = (uint32_t)__popc(bits_in);
+        const uint32_t incl = wave_scan_dpp(mine);
+        if (l == WAVE - 1) s_wave[parity][w] = incl;
+        __syncthreads();
+        // every wave is past the previous tile: its next-level sums go out
+        if (TEST && threadIdx.x < NF + 2) {
+            const uint32_t c = s_next[threadIdx.x];
+            if (c) atomicAdd(&S.cnt[prev_tile + threadIdx.x], c);
+            s_next[threadIdx.x] = 0u;
+        }
+        const uint64_t base = (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(cur.off >> 32)) << 32 |
+                              __builtin_amdgcn_readfirstlane((uint32_t)cur.off);
+        prev_tile = base / TILE;
+        // survivors of the waves before, and of the tile
+        static_assert(NW == 8, "eight sums in the first lanes");
+        uint32_t ws = l < NW ? s_wave[parity][l] : 0u;
+        ws += dpp_from<0x111, 0xF>(0u, ws);
+        ws += dpp_from<0x112, 0xF>(0u, ws);
+        ws += dpp_from<0x114, 0xF>(0u, ws);
+        const uint32_t n_out = __builtin_amdgcn_readlane(ws, NW - 1);
+        uint32_t ex = incl - mine + (w ? __builtin_amdgcn_readlane(ws, w ? w - 1 : 0u) : 0u);
 #pragma unroll
-            for (int k = 0; k < PPT; ++k) {
-                if (((mask >> (k * NF)) & ((1u << NF) - 1u)) == 0u) continue;
+        for (uint32_t k = 0; k < PPT; ++k) {
+            if (!mk_[k]) continue;
+            const uint32_t p = threadIdx.x * PPT + k;
+            s_par[p] = make_uint2(tri[k], first[k]);
 #pragma unroll
-                for (int j = 0; j < NF; ++j) {
-                    if (!((mask >> (k * NF + j)) & 1u)) continue;
-                    if (at < TILE_OUT) {
-                        s_tri[at] = tri[k];
-                        s_node[at] = first[k] + (uint32_t)j;
-                    }
-                    ++at;
+            for (uint32_t c = 0; c < NF; ++c)
+                if ((mk_[k] >> c) & 1u) s_item[ex++] = (uint16_t)(16u * p + c);
+        }
+        __syncthreads();
+        if (n_out == 0u) continue;
+        if constexpr (TEST && STAGED) {
+            const uint32_t it = s_item[0];
+            const uint32_t node = __builtin_amdgcn_readfirstlane(s_par[it >> 4].y + (it & 15u));
+            if (node - wlo >= wlen) {
+                // the frame's nodes on both levels, and its levels
+                uint32_t pb = 0u, pc = n1, cb = 0u, cc = n2, levels = nl;
+                if constexpr (BATCH) {
+                    const uint32_t f = frame_of_node(bd, (uint32_t)parent_level - 2, node);
+                    pb = bd.fm[f].level_base[parent_level - 2];
+                    pc = bd.fm[f].level_cnt[parent_level - 2];
+                    cb = bd.fm[f].level_base[parent_level - 3];
+                    cc = bd.fm[f].level_cnt[parent_level - 3];
+                    levels = bd.fm[f].n_levels;
+                }
+                uint32_t run = 1;               // a top-level node's descendants on the level written
+                for (uint32_t k = 0; k + parent_level - 1 < levels && run <= WP; ++k) run *= F;
+                wlen = wfull = 0u;
+                if (run <= WP && node >= pb && node - pb < pc) {
+                    wlo = pb + (node - pb) / run * run;
+                    wlen = min(WP / run * run, pb + pc - wlo);
+                    const uint32_t c0 = (wlo - pb) * F;
+                    wend = cc - c0;
+                    wfull = F == NF ? min(wlen, wend / NF) : 0u;
+                    for (uint32_t r = 0; r < F; ++r)
+                        for (uint32_t i = threadIdx.x; i < wlen; i += STEP_THREADS) {
+                            const uint32_t c = i * F + r;
+                            if (c >= wend) continue;
+                            const uint32_t g = off2 + cb + c0 + c;
+                            s_wa[r * WP + i] = na[g];
+                            s_wb[r * WP + i] = nb[g];
+                            s_ws[r * WP + i] = ns[g];
+                        }
+                    __syncthreads();
                 }
             }
         }
-        __syncthreads();
-        const uint32_t n_out = min(total, TILE_OUT);
-        for (uint32_t i = threadIdx.x; i < n_out; i += LEVEL_THREADS) {
-            const uint64_t at = base + i;
-            if (at < out.cap) pair_put<PACKED>(out, at, s_tri[i], s_node[i]);
+        // what fits the storage; stores past it are dropped by their range
+        const uint32_t n_put = base < out.cap ? (uint32_t)min(out.cap - base, (uint64_t)n_out) : 0u;
+        const __amdgpu_buffer_rsrc_t ot = make_rsrc(out.tri + base, n_put * 4u);
+        const __amdgpu_buffer_rsrc_t on = make_rsrc(PACKED ? out.tri : out.node + base, n_put * 4u);
+        const __amdgpu_buffer_rsrc_t om = make_rsrc(mask_out + base, n_put * (uint32_t)sizeof(mask_t));
+        for (uint32_t i0 = w * WAVE; i0 < n_put; i0 += STEP_THREADS) {
+            const uint32_t i = i0 + l;
+            const uint32_t it = s_item[i < n_put ? i : 0u];
+            const uint2 pr = s_par[it >> 4];
+            const uint32_t node = pr.y + (it & 15u);
+            if constexpr (PACKED) {
+                __builtin_amdgcn_raw_buffer_store_b32(node << CRSH_PACKED_TRI_BITS | (pr.x - out.tri_base), ot, i * 4u, 0, 0);
+            } else {
+                __builtin_amdgcn_raw_buffer_store_b32(pr.x, ot, i * 4u, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b32(node, on, i * 4u, 0, 0);
+            }
+            if constexpr (TEST) {
+                const float4 sp = tsph[pr.x < m ? pr.x : 0u];
+                const f3 pc = mk(sp.x, sp.y, sp.z);
+                const uint64_t live = n_put - i0 >= WAVE ? ~0ull : (1ull << (n_put - i0)) - 1ull;
+                const uint32_t pl = node - wlo;
+                uint64_t pass[NF];
+                // every pair's children in the copy, all F = NF of them: no
+                // looking further (a lane past the end repeats the first pair)
+                if (STAGED && ballot(pl >= wfull) == 0) {
+#pragma unroll
+                    for (uint32_t r = 0; r < NF; ++r)
+                        pass[r] = packed_meets_mask(s_wa[r * WP + pl], s_wb[r * WP + pl], s_ws[r * WP + pl], pc, sp.w) & live;
+                    tests64 += (uint64_t)__popcll(live) * NF;
+                } else {
+                    const bool inw = STAGED && pl < wlen;
+                    const uint32_t ps = inw ? pl : 0u;
+                    uint32_t n = inw && i < n_put ? min(F, wend - pl * F) : 0u;
+#pragma unroll
+                    for (uint32_t r = 0; r < NF; ++r) {
+                        pass[r] = 0u;
+                        if constexpr (STAGED)
+                            pass[r] = packed_meets_mask(s_wa[r * WP + ps], s_wb[r * WP + ps], s_ws[r * WP + ps], pc, sp.w) &
+                                      ballot(r < n);
+                    }
+                    // pairs outside the copy: children from the node arrays
+                    if (ballot(!inw && i < n_put) != 0) {
+                        uint32_t c = node * F, k = c < n2 ? min(F, n2 - c) : 0u;
+                        if constexpr (BATCH) {
+                            c = node < n1 ? bd.node_first[off1 + node] : 0u;
+                            k = node < n1 ? bd.node_info[off1 + node] & INFO_COUNT_MASK : 0u;
+                            k = c < n2 ? min(k, n2 - c) : 0u;
+                        }
+                        k = !inw && i < n_put ? k : 0u;
+                        n += k;
+#pragma unroll
+                        for (uint32_t r = 0; r < NF; ++r) {
+                            const uint32_t g = off2 + (r < k ? c + r : 0u);
+                            pass[r] |= packed_meets_mask(na[g], nb[g], ns[g], pc, sp.w) & ballot(r < k);
+                        }
+                    }
+#pragma unroll
+                    for (uint32_t r = 0; r < NF; ++r) tests64 += (uint64_t)__popcll(ballot(r < n));
+                }
+                // the pair's pass bits, and the survivors of the lanes in the
+                // first of the (at most two) next-level tiles they lie in
+                const uint64_t p0 = base + i0;
+                const uint32_t left = TILE - (uint32_t)(p0 % TILE);
+                const uint64_t in_first = left >= WAVE ? ~0ull : (1ull << left) - 1ull;
+                uint32_t bits = 0u, ca = 0u, cb = 0u;
+#pragma unroll
+                for (int r = NF - 1; r >= 0; --r) {
+                    bits = bits + bits + (__builtin_amdgcn_inverse_ballot_w64(pass[r]) ? 1u : 0u);
+                    ca += (uint32_t)__popcll(pass[r] & in_first);
+                    cb += (uint32_t)__popcll(pass[r] & ~in_first);
+                }
+                if constexpr (sizeof(mask_t) == 1)
+                    __builtin_amdgcn_raw_buffer_store_b8((uint8_t)bits, om, i, 0, 0);
+                else
+                    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)bits, om, i * 2u, 0, 0);
+                const uint32_t k = (uint32_t)(p0 / TILE - prev_tile);
+                if (l == 0 && ca) atomicAdd(&s_next[k], ca);
+                if (l == 0 && cb) atomicAdd(&s_next[k + 1], cb);
+            }
         }
-        __syncthreads();                         // LDS is reused by the next tile
+    }
+    if constexpr (TEST) {
+        __syncthreads();
+        if (threadIdx.x < NF + 2) {
+            const uint32_t c = s_next[threadIdx.x];
+            if (c) atomicAdd(&S.cnt[prev_tile + threadIdx.x], c);
+        }
+        __shared__ uint64_t s_tests[NW];
+        if (l == 0) s_tests[w] = tests64;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint64_t sum = 0;
+            for (uint32_t k = 0; k < NW; ++k) sum += s_tests[k];
+            S.part[blockIdx.x] += sum;
+        }
     }
 }
 
@@ -760,9 +1063,13 @@ __global__ __launch_bounds__(LEVEL_THREADS) void k_level_emit(int32_t parent_lev
 // There are few tiles (SCAN_TILE items each).
 // A batch's top-level pass (batch_top = its level, 1-based) scans bd_top[0]
 // items and appends after the bd_top[1] pairs already on that level.
-__global__ __launch_bounds__(SCAN_THREADS) void k_scan_items(int32_t parent_level, uint32_t n_mesh, pair_levels P,
-                                                             trav_scratch S, crsh_meta *meta, uint32_t batch_top,
-                                                             const uint64_t *bd_top)
+// Level scans clear the counts they read (the next step adds into them), and
+// the first tile adds the workgroups' sums of the launch before to meta:
+// three counts of the top-level count, or node tests.
+__global__ __launch_bounds__(SCAN_THREADS) void k_scan_items(int32_t parent_level, uint32_t n_mesh, uint32_t tile_pairs,
+                                                             pair_levels P, trav_scratch S, crsh_meta *meta,
+                                                             uint32_t batch_top, const uint64_t *bd_top,
+                                                             uint32_t blocks)
 {
     __shared__ uint32_t s_tile;
     __shared__ uint64_t s_excl;
@@ -770,21 +1077,23 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_items(int32_t parent_leve
     const uint32_t nl = meta->n_levels;
     if (nl == 0) return;
     if (batch_top > nl) return;
-    const uint64_t n = batch_top ? bd_top[0] : level_items(meta, parent_level, n_mesh, P);
+    const bool top = parent_level == 0;
+    const uint64_t n = batch_top ? bd_top[0] : level_items(meta, parent_level, n_mesh, P, tile_pairs);
     const uint64_t base = batch_top ? bd_top[1] : 0u;
-    const uint32_t out_level = batch_top ? batch_top - 1 : (parent_level == 0 ? nl - 1 : (uint32_t)parent_level - 2);
+    const uint32_t out_level = batch_top ? batch_top - 1 : (top ? nl - 1 : (uint32_t)parent_level - 2);
     const uint64_t ntiles = (n + SCAN_TILE - 1) / SCAN_TILE;
     if (blockIdx.x >= ntiles) return;       // only ntiles blocks take a tile
     if (threadIdx.x == 0) s_tile = atomicAdd(S.scan_ctr, 1u);
     __syncthreads();
     const uint32_t tile = s_tile;
     if (tile >= ntiles) return;
+    uint32_t *const cnt = top ? S.cnt_top : S.cnt;
     const uint64_t first = (uint64_t)tile * SCAN_TILE + (uint64_t)threadIdx.x * SCAN_ITEMS;
     uint64_t v[SCAN_ITEMS];
     uint64_t sum = 0;
 #pragma unroll
     for (uint32_t k = 0; k < SCAN_ITEMS; ++k) {
-        v[k] = first + k < n ? S.cnt[first + k] : 0u;
+        v[k] = first + k < n ? cnt[first + k] : 0u;
         sum += v[k];
     }
     uint64_t total;
@@ -797,13 +1106,45 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_items(int32_t parent_leve
     uint64_t run = s_excl + ex;
 #pragma unroll
     for (uint32_t k = 0; k < SCAN_ITEMS; ++k) {
-        if (first + k < n) S.off[first + k] = base + run;
+        if (first + k < n) {
+            S.off[first + k] = base + run;
+            if (!top) cnt[first + k] = 0u;
+        }
         run += v[k];
     }
     if (tile == ntiles - 1 && threadIdx.x == SCAN_THREADS - 1) {
         meta->pairs[out_level] = base + run;
         atomicAdd((unsigned long long *)&meta->hits[out_level], (unsigned long long)run);
         if (base + run > P.p[out_level].cap) atomicOr(&meta->status, CRSH_OVERFLOW_PAIRS);
+    }
+    if (tile != 0) return;
+    // the launch before's workgroup sums (three for the top-level count)
+    const uint32_t kinds = top ? 3u : 1u;
+    for (uint32_t k = 0; k < kinds; ++k) {
+        uint64_t c = 0;
+        for (uint32_t i = threadIdx.x; i < blocks; i += SCAN_THREADS) {
+            if (top) {
+                c += S.top_part[3 * i + k];
+            } else {
+                c += S.part[i];
+                S.part[i] = 0u;
+            }
+        }
+        c = wave_sum(c);
+        __syncthreads();
+        if (lane_id() == 0) s_scan[threadIdx.x / WAVE] = c;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            c = s_scan[0] + s_scan[1] + s_scan[2] + s_scan[3];
+            if (!top)
+                meta->tests[out_level] += c;
+            else if (k == 0)
+                meta->tests[out_level] += c;
+            else if (k == 1)
+                meta->mesh_hits += c;
+            else
+                meta->mesh_tests += c;
+        }
     }
 }
 
@@ -831,25 +1172,24 @@ __global__ __launch_bounds__(256) void k_batch_top_plan(batch_dev bd, crsh_meta 
     }
 }
 
-__global__ void k_no_storage(crsh_meta *meta, uint32_t levels_given)
-{
-    if (meta->n_levels > levels_given) atomicOr(&meta->status, CRSH_OVERFLOW_PAIRS);
-}
-
 }  // namespace crsh
 
 using namespace crsh;
 
 namespace crsh {
 
-void node_pack_launch(const crsh_nodes *nodes, crsh_meta *meta, float4 *na, float4 *nb, float *ns, bool clear_pairs,
-                      hipStream_t stream)
+void trav_prep_launch(const crsh_scene *scene, uint32_t tri_begin, uint32_t tri_end, float4 *tsph,
+                      const crsh_nodes *nodes, crsh_meta *meta, float4 *na, float4 *nb, float *ns,
+                      const trav_scratch &S, uint64_t n_cnt, uint32_t levels, hipStream_t stream)
 {
-    node_arrays nd{nodes->cx, nodes->cy, nodes->cz, nodes->r, nodes->ax, nodes->ay, nodes->az,
-                   nodes->c, nodes->tan, nodes->sec};
-    uint32_t g = std::min<uint32_t>((nodes->capacity + 255) / 256, 2048);
-    if (g == 0) g = 1;
-    k_node_pack<<<g, 256, 0, stream>>>(nd, meta, na, nb, ns, clear_pairs);
+    const node_arrays nd{nodes->cx, nodes->cy, nodes->cz, nodes->r, nodes->ax, nodes->ay, nodes->az,
+                         nodes->c, nodes->tan, nodes->sec};
+    tri_verts V;
+    for (int k = 0; k < 9; ++k) V.v[k] = scene->v[k];
+    uint64_t items = std::max(std::max<uint64_t>(nodes->capacity, n_cnt), (uint64_t)(tri_end - tri_begin));
+    items = std::max<uint64_t>(items, TRAV_PARTS);
+    const uint32_t g = (uint32_t)std::min<uint64_t>((items + 255) / 256, 4096);
+    k_trav_prep<<<g, 256, 0, stream>>>(V, tri_begin, tri_end, tsph, nd, meta, na, nb, ns, S, n_cnt, levels);
 }
 
 // Blocks of a persistent grid-stride kernel that fit the device at once.  Its
@@ -869,7 +1209,7 @@ static uint32_t resident_blocks(K kernel, uint32_t threads)
 
 void level_count_launch(int32_t parent_level, int32_t merge, const float4 *na, const float4 *nb, const float *ns,
                         const float4 *tsph, uint32_t m, const pair_levels &P, const trav_scratch &S, crsh_meta *meta,
-                        const batch_dev *bd, uint64_t tiles_cap, uint32_t top_levels, hipStream_t stream, bool packed)
+                        const batch_dev *bd, uint64_t tiles_cap, uint32_t top_levels, hipStream_t stream)
 {
     const batch_dev b = bd ? *bd : batch_dev{};
     const uint32_t Fu = (uint32_t)merge;
@@ -884,45 +1224,34 @@ void level_count_launch(int32_t parent_level, int32_t merge, const float4 *na, c
     prof_scope ps("k_level", stream);
     // a persistent grid of one round of resident blocks (at most one block
     // per step of COUNT_TPS tiles)
-#define CRSH_COUNT_ONE(NF, BT, PK, ST)                                                                       \
+#define CRSH_COUNT_ONE(NF, BT, ST)                                                                           \
     {                                                                                                        \
-        const uint32_t rb = resident_blocks(k_level_count_lanes<NF, BT, PK, ST>, COUNT_THREADS);             \
+        const uint32_t rb = resident_blocks(k_level_count_lanes<NF, BT, ST>, COUNT_THREADS);                 \
         const uint64_t want = std::max<uint64_t>((tiles_cap + COUNT_TPS - 1) / COUNT_TPS, 1);                \
         const uint32_t gl = (uint32_t)std::min<uint64_t>(want, rb ? rb : 2048);                              \
-        k_level_count_lanes<NF, BT, PK, ST><<<gl, COUNT_THREADS, 0, stream>>>(L, Fu, na, nb, ns, tsph, m, P, S, \
-                                                                            meta, b);                       \
+        k_level_count_lanes<NF, BT, ST><<<gl, COUNT_THREADS, 0, stream>>>(L, Fu, na, nb, ns, tsph, m, P, S,  \
+                                                                        meta, b);                           \
     }
-#define CRSH_COUNT_ST(NF, BT, PK)                                                                            \
+#define CRSH_COUNT_ST(NF, BT)                                                                                \
     if (st)                                                                                                  \
-        CRSH_COUNT_ONE(NF, BT, PK, true)                                                                     \
+        CRSH_COUNT_ONE(NF, BT, true)                                                                         \
     else                                                                                                     \
-        CRSH_COUNT_ONE(NF, BT, PK, false)
-#define CRSH_COUNT_NF(BT, PK)                                                                                \
+        CRSH_COUNT_ONE(NF, BT, false)
+#define CRSH_COUNT_NF(BT)                                                                                    \
     switch (nf) {                                                                                            \
-    case 2: CRSH_COUNT_ST(2, BT, PK) break;                                                                  \
-    case 4: CRSH_COUNT_ST(4, BT, PK) break;                                                                  \
-    case 8: CRSH_COUNT_ST(8, BT, PK) break;                                                                  \
-    default: CRSH_COUNT_ST(16, BT, PK) break;                                                                \
+    case 2: CRSH_COUNT_ST(2, BT) break;                                                                      \
+    case 4: CRSH_COUNT_ST(4, BT) break;                                                                      \
+    case 8: CRSH_COUNT_ST(8, BT) break;                                                                      \
+    default: CRSH_COUNT_ST(16, BT) break;                                                                    \
     }
     if (bd) {
-        CRSH_COUNT_NF(true, false)
-    } else if (packed) {
-        CRSH_COUNT_NF(false, true)
+        CRSH_COUNT_NF(true)
     } else {
-        CRSH_COUNT_NF(false, false)
+        CRSH_COUNT_NF(false)
     }
 #undef CRSH_COUNT_NF
 #undef CRSH_COUNT_ST
 #undef CRSH_COUNT_ONE
-}
-
-void tri_spheres_launch(const crsh_scene *scene, uint32_t b, uint32_t e, float4 *out, hipStream_t stream)
-{
-    const float *const *v = scene->v;
-    if (e > b) {
-        uint32_t g = std::min<uint32_t>((e - b + 255) / 256, 2048);
-        k_tri_sph<<<g, 256, 0, stream>>>(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], v[8], b, e, out);
-    }
 }
 
 // lowest: the lowest level produced (1, or 2 when crsh_leaf_hit forms the
@@ -978,8 +1307,8 @@ static crsh_status traverse_run(const crsh_nodes *nodes, const crsh_scene *scene
         set_error("crsh_traverse: workspace too small (%zu < %zu)", ws_bytes, need);
         return CRSH_ERR_INVALID;
     }
-    const uint64_t level_tiles = (max_pairs + LEVEL_TILE - 1) / LEVEL_TILE;
-    const uint64_t items = std::max(top_items, level_tiles) + 1;
+    const uint64_t tiles = max_pairs / STEP_THREADS + 2;       // at least step_tile pairs each
+    const uint64_t items = std::max(top_items, tiles) + 1;
     char *w = (char *)ws;
     float4 *tsph = (float4 *)w;
     w += align256((size_t)scene->m * 16);
@@ -989,104 +1318,144 @@ static crsh_status traverse_run(const crsh_nodes *nodes, const crsh_scene *scene
     w += align256((size_t)nodes->capacity * 16);
     float *ns = (float *)w;
     w += align256((size_t)nodes->capacity * 4);
-    trav_scratch S;
+    trav_scratch S{};
+    S.cnt_top = (uint32_t *)w;
+    w += align256(top_items * 4 + 4);
     S.cnt = (uint32_t *)w;
-    w += align256(items * 4);
+    w += align256(tiles * 4);
     S.off = (uint64_t *)w;
     w += align256(items * 8);
-    S.mask = (uint32_t *)w;
-    w += align256(level_tiles * LEVEL_THREADS * 4 + 4);
+    S.mask[0] = w;
+    w += align256(max_pairs * 2 + 2);
+    S.mask[1] = w;
+    w += align256(max_pairs * 2 + 2);
     S.scan_flags = (uint64_t *)w;
+    S.n_flags = (uint32_t)(items / SCAN_TILE + 2);
     w += align256((items / SCAN_TILE + 2) * 8);
     S.scan_ctr = (uint32_t *)w;
+    w += align256(4);
+    S.part = (uint64_t *)w;
+    S.top_part = S.part + TRAV_PARTS;
 
     int nf = 2;
     while (nf < merge) nf *= 2;
+    const uint32_t tile_pairs = step_tile(nf);
     const batch_dev b = bd ? *bd : batch_dev{};
-    tri_spheres_launch(scene, tri_begin, tri_end, tsph, stream);
-    node_pack_launch(nodes, meta, na, nb, ns, true, stream);
-    k_no_storage<<<1, 1, 0, stream>>>(meta, (uint32_t)levels);
+    trav_prep_launch(scene, tri_begin, tri_end, tsph, nodes, meta, na, nb, ns, S, max_pairs / tile_pairs + 1,
+                     (uint32_t)levels, stream);
     const uint32_t scan_grid = (uint32_t)std::min<uint64_t>((items + SCAN_TILE - 1) / SCAN_TILE, 1u << 20);
-    const uint32_t top_grid = (uint32_t)std::max<uint64_t>(std::min<uint64_t>((top_items + 3) / 4, 2048), 1);
+    // one wave per top-level item, for the items that a hierarchy with as many
+    // levels as there is storage for has (more items loop)
+    uint64_t top_est = top_items;
+    if (!bd) {
+        uint64_t n = nodes->capacity;
+        for (int k = 1; k < levels && n > 1; ++k) n = (n + merge - 1) / merge;
+        top_est = n * scene->n_mesh;
+    }
+    const uint32_t top_grid = (uint32_t)std::min<uint64_t>(std::max<uint64_t>((top_est + 3) / 4, 256), 2048);
+    static_assert(TRAV_PARTS >= 2048, "a sum per workgroup of the top-level passes");
     const uint32_t Fu = (uint32_t)merge;
+#define CRSH_NF(DO)              \
+    switch (nf) {                \
+    case 2: DO(2); break;        \
+    case 4: DO(4); break;        \
+    case 8: DO(8); break;        \
+    default: DO(16); break;      \
+    }
 
     // top-level pass: plain (L = 0, the one top level) or a batch level L
     auto top_pass_launch = [&](uint32_t L) {
-        if (bd) {
-            k_batch_top_plan<<<1, 256, 0, stream>>>(b, meta, L);
-            {
-                prof_scope ps("k_top_count", stream);
+        if (bd) k_batch_top_plan<<<1, 256, 0, stream>>>(b, meta, L);
+        {
+            prof_scope ps("k_top_count", stream);
+            if (bd)
                 k_top_count<true><<<top_grid, 256, 0, stream>>>(na, nb, ns, tsph, scene->mesh_first,
                                                                 scene->mesh_count, scene->msph, scene->n_mesh,
                                                                 tri_begin, tri_end, P, S, meta, b, L);
-            }
-            k_scan_items<<<scan_grid, SCAN_THREADS, 0, stream>>>(0, scene->n_mesh, P, S, meta, L, b.top);
-            {
-                prof_scope ps("k_top_emit", stream);
-                k_top_emit<true><<<top_grid, 256, 0, stream>>>(na, nb, ns, tsph, scene->mesh_first,
-                                                               scene->mesh_count, scene->msph, scene->n_mesh,
-                                                               tri_begin, tri_end, P, S, meta, b, L);
-            }
-        } else {
-            {
-                prof_scope ps("k_top_count", stream);
+            else
                 k_top_count<false><<<top_grid, 256, 0, stream>>>(na, nb, ns, tsph, scene->mesh_first,
                                                                  scene->mesh_count, scene->msph, scene->n_mesh,
-                                                                 tri_begin, tri_end, P, S, meta, b, 0);
-            }
-            k_scan_items<<<scan_grid, SCAN_THREADS, 0, stream>>>(0, scene->n_mesh, P, S, meta, 0, nullptr);
-            {
-                prof_scope ps("k_top_emit", stream);
-                if (packed)
-                    k_top_emit<false, true><<<top_grid, 256, 0, stream>>>(na, nb, ns, tsph, scene->mesh_first,
-                                                                          scene->mesh_count, scene->msph,
-                                                                          scene->n_mesh, tri_begin, tri_end, P, S,
-                                                                          meta, b, 0);
-                else
-                    k_top_emit<false><<<top_grid, 256, 0, stream>>>(na, nb, ns, tsph, scene->mesh_first,
-                                                                    scene->mesh_count, scene->msph, scene->n_mesh,
-                                                                    tri_begin, tri_end, P, S, meta, b, 0);
-            }
+                                                                 tri_begin, tri_end, P, S, meta, b, L);
         }
+        k_scan_items<<<scan_grid, SCAN_THREADS, 0, stream>>>(0, scene->n_mesh, tile_pairs, P, S, meta, L, b.top,
+                                                             top_grid);
+        prof_scope ps("k_top_emit", stream);
+#define CRSH_TOP(NF, BT, PK)                                                                                      \
+    k_top_emit<NF, BT, PK><<<top_grid, 256, 0, stream>>>(na, nb, ns, tsph, scene->mesh_first, scene->mesh_count,  \
+                                                         scene->msph, scene->n_mesh, tri_begin, tri_end, Fu,      \
+                                                         (uint32_t)lowest, P, S, meta, b, L)
+#define CRSH_TOP_BATCH(NF) CRSH_TOP(NF, true, false)
+#define CRSH_TOP_PACKED(NF) CRSH_TOP(NF, false, true)
+#define CRSH_TOP_PLAIN(NF) CRSH_TOP(NF, false, false)
+        if (bd) {
+            CRSH_NF(CRSH_TOP_BATCH)
+        } else if (packed) {
+            CRSH_NF(CRSH_TOP_PACKED)
+        } else {
+            CRSH_NF(CRSH_TOP_PLAIN)
+        }
+#undef CRSH_TOP_BATCH
+#undef CRSH_TOP_PACKED
+#undef CRSH_TOP_PLAIN
+#undef CRSH_TOP
     };
-    // one level pass: pairs of level L (1-based parent) -> level L - 1
-    auto level_pass_launch = [&](int L) {
-        const uint64_t tiles = (P.p[L - 1].cap + LEVEL_TILE - 1) / LEVEL_TILE;
-        uint32_t g = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(tiles, 1), 4096);
-#define CRSH_EMIT(NF, BT, PK)                                                                              \
-    k_level_emit<NF, emit_ppt(NF), BT, PK><<<g, LEVEL_THREADS, 0, stream>>>(L, Fu, P, S, meta, b)
-#define CRSH_EMIT_NF(BT, PK)                                                                               \
-    switch (nf) {                                                                                          \
-    case 2: CRSH_EMIT(2, BT, PK); break;                                                                   \
-    case 4: CRSH_EMIT(4, BT, PK); break;                                                                   \
-    case 8: CRSH_EMIT(8, BT, PK); break;                                                                   \
-    default: CRSH_EMIT(16, BT, PK); break;                                                                 \
+    // one level step: pairs of level L (1-based parent) -> level L - 1, tested
+    // against level L - 2 if another step follows
+    const uint32_t top_levels = (uint32_t)(bd ? batch_levels : levels);
+    uint32_t parts = top_grid;               // workgroups that may have left a sum of node tests
+    auto level_step_launch = [&](int L) {
+        k_scan_items<<<scan_grid, SCAN_THREADS, 0, stream>>>(L, scene->n_mesh, tile_pairs, P, S, meta, 0, nullptr,
+                                                             parts);
+        const uint64_t want = std::max<uint64_t>((P.p[L - 1].cap + tile_pairs - 1) / tile_pairs, 1);
+        const bool test = L - 1 > lowest;
+        // a top-level node's descendants on the level written, in a hierarchy
+        // of at most top_levels levels: the copying kernel if their children
+        // fit the copy
+        uint64_t run = (uint64_t)nf;
+        for (int k = L - 1; k < (int)top_levels && run <= COUNT_WINDOW; ++k) run *= Fu;
+        const bool st = run <= COUNT_WINDOW;
+        prof_scope ps("k_level", stream);
+#define CRSH_STEP(NF, BT, PK, TE, ST)                                                                             \
+    {                                                                                                             \
+        const uint32_t rb = resident_blocks(k_level_step<NF, BT, PK, TE, ST>, STEP_THREADS);                      \
+        const uint32_t g = (uint32_t)std::min<uint64_t>(want, std::min(rb ? rb : 512u, TRAV_PARTS));              \
+        parts = std::max(parts, g);                                                                               \
+        k_level_step<NF, BT, PK, TE, ST><<<g, STEP_THREADS, 0, stream>>>(L, Fu, na, nb, ns, tsph, scene->m, P, S, \
+                                                                         meta, b);                               \
     }
-        level_count_launch(L, merge, na, nb, ns, tsph, scene->m, P, S, meta, bd, tiles,
-                           (uint32_t)(bd ? batch_levels : levels), stream, packed);
-        k_scan_items<<<scan_grid, SCAN_THREADS, 0, stream>>>(L, scene->n_mesh, P, S, meta, 0, nullptr);
-        {
-            prof_scope ps("k_level_emit", stream);
-            if (bd) {
-                CRSH_EMIT_NF(true, false)
-            } else if (packed) {
-                CRSH_EMIT_NF(false, true)
-            } else {
-                CRSH_EMIT_NF(false, false)
-            }
+#define CRSH_STEP_T(NF, BT, PK)                  \
+    if (!test)                                   \
+        CRSH_STEP(NF, BT, PK, false, false)      \
+    else if (st)                                 \
+        CRSH_STEP(NF, BT, PK, true, true)        \
+    else                                         \
+        CRSH_STEP(NF, BT, PK, true, false)
+#define CRSH_STEP_BATCH(NF) CRSH_STEP_T(NF, true, false)
+#define CRSH_STEP_PACKED(NF) CRSH_STEP_T(NF, false, true)
+#define CRSH_STEP_PLAIN(NF) CRSH_STEP_T(NF, false, false)
+        if (bd) {
+            CRSH_NF(CRSH_STEP_BATCH)
+        } else if (packed) {
+            CRSH_NF(CRSH_STEP_PACKED)
+        } else {
+            CRSH_NF(CRSH_STEP_PLAIN)
         }
-#undef CRSH_EMIT_NF
-#undef CRSH_EMIT
+#undef CRSH_STEP_BATCH
+#undef CRSH_STEP_PACKED
+#undef CRSH_STEP_PLAIN
+#undef CRSH_STEP_T
+#undef CRSH_STEP
     };
     if (bd) {
         for (int L = batch_levels; L >= 1; --L) {
-            if (L < batch_levels && L >= lowest) level_pass_launch(L + 1);
+            if (L < batch_levels && L >= lowest) level_step_launch(L + 1);
             top_pass_launch((uint32_t)L);
         }
     } else {
         top_pass_launch(0);
-        for (int L = levels; L >= lowest + 1; --L) level_pass_launch(L);
+        for (int L = levels; L >= lowest + 1; --L) level_step_launch(L);
     }
+#undef CRSH_NF
     return hip_check(hipGetLastError(), "crsh_traverse launch");
 }
 
