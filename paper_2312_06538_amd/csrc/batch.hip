@@ -35,7 +35,7 @@ static batch_layout layout(uint32_t ray_cap, uint64_t pixels, uint32_t m, uint32
     L.first = 0;
     L.info = L.first + align256((size_t)node_cap * 4 + 4);
     L.top = L.info + align256((size_t)node_cap * 4 + 4);
-    L.stage = L.top + align256(2 * sizeof(uint64_t));
+    L.stage = L.top + align256(3 * sizeof(uint64_t));
     size_t st = std::max(sort_ws_bytes(ray_cap), hash_ws_bytes(pixels));
     st = std::max(st, trav_ws_bytes(m, node_cap, top_items, max_pairs));
     const uint32_t slots = hit_slots(ray_cap, true);

@@ -20,7 +20,7 @@ struct batch_dev {
     uint32_t *node_first;        // per packed node: first sorted ray (level 1) or first child (level-local)
     uint32_t *node_info;         // per packed node: count in bits 0-7, frame in bits 8-15
     const uint32_t *ray_frame;   // frame of every ray id
-    uint64_t *top;               // [0] items of the current top-level pass, [1] its append base
+    uint64_t *top;               // [0] items of the current top-level pass, [1] its append base, [2] parts per item
     uint64_t top_cap;            // capacity for top-level items
     const uint32_t *mat_flags;
     const float *mat_ior;

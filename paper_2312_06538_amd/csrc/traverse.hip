@@ -70,13 +70,31 @@ __global__ void k_trav_prep(tri_verts V, uint32_t b, uint32_t e, float4 *tsph, n
     }
 }
 
+// Parts that a top-level (node, mesh) item is cut into, its triangles in equal
+// shares: an item of 1,280 triangles takes a wave 20 steps of about 1.5 us
+// each, and a 128x72 frame has 6 items (top emit 32 us; 9 us in 16 parts).
+// Up to a wave per SIMD: with 4,096 items the scan over them and the look-ups
+// cost a 128x128 frame 6 us more than the parts save it.
+__device__ __forceinline__ uint32_t top_parts(uint64_t items, uint64_t cap)
+{
+    uint32_t s = 1;
+    while (s < 16 && items * s * 2 <= 1024 && items * s * 2 <= cap) s *= 2;
+    return s;
+}
+
 // number of work items of a level: top level (parent_level 0) = top nodes x
-// meshes, lower levels = tiles of `tile` parent pairs
+// meshes x parts (top_parts), lower levels = tiles of `tile` parent pairs
 __device__ __forceinline__ uint64_t level_items(const crsh_meta *meta, int32_t parent_level, uint32_t n_mesh,
-                                                const pair_levels &P, uint32_t tile)
+                                                const pair_levels &P, uint32_t tile, uint64_t top_cap,
+                                                uint32_t &parts)
 {
     const uint32_t nl = meta->n_levels;
-    if (parent_level == 0) return nl ? (uint64_t)meta->level_cnt[nl - 1] * n_mesh : 0;
+    parts = 1;
+    if (parent_level == 0) {
+        const uint64_t items = nl ? (uint64_t)meta->level_cnt[nl - 1] * n_mesh : 0;
+        parts = top_parts(items, top_cap);
+        return items * parts;
+    }
     if ((uint32_t)parent_level > nl || parent_level < 2) return 0;
     uint64_t nin = meta->pairs[parent_level - 1];
     const uint64_t cap = P.p[parent_level - 1].cap;
@@ -100,13 +118,14 @@ __device__ __forceinline__ void clear_scan(const trav_scratch &S)
 // the other by the whole wave, their values taken from the lane that has
 // them.
 template <bool BATCH>
-__device__ __forceinline__ void top_item(uint64_t item, uint32_t n_mesh, uint32_t top, uint32_t off,
+__device__ __forceinline__ void top_item(uint64_t item_part, uint32_t parts, uint32_t n_mesh, uint32_t top, uint32_t off,
                                          const batch_dev &bd, const float4 *na, const float4 *nb, const float *ns,
                                          const float *msph, const uint32_t *mesh_first, const uint32_t *mesh_count,
                                          uint32_t tri_begin, uint32_t tri_end, float4 &A, float4 &Bv, float &S,
                                          uint32_t &i, uint32_t &b, uint32_t &e, bool &pass)
 {
     uint32_t m;
+    const uint64_t item = item_part / parts;
     if constexpr (BATCH) {
         const uint32_t f = frame_of_item(bd, item);
         const uint64_t local = item - bd.fm[f].item_base;
@@ -129,6 +148,9 @@ __device__ __forceinline__ void top_item(uint64_t item, uint32_t n_mesh, uint32_
         b = max(mesh_first[m], tri_begin);
         e = min(mesh_first[m] + mesh_count[m], tri_end);
         if (e < b) e = b;
+        const uint32_t part = (uint32_t)(item_part - item * parts), n = e - b;
+        e = b + (uint32_t)((uint64_t)n * (part + 1) / parts);
+        b += (uint32_t)((uint64_t)n * part / parts);
     }
 }
 
@@ -149,7 +171,8 @@ __device__ __forceinline__ uint64_t from_lane(uint64_t v, uint32_t src)
 // top level of this pass (0-based) and its number of items
 template <bool BATCH>
 __device__ __forceinline__ bool top_pass(const crsh_meta *meta, const batch_dev &bd, uint32_t L, uint32_t n_mesh,
-                                         const pair_levels &P, uint32_t &top, uint64_t &n_items)
+                                         const pair_levels &P, uint64_t top_cap, uint32_t &top, uint64_t &n_items,
+                                         uint32_t &parts)
 {
     const uint32_t nl = meta->n_levels;
     if (nl == 0) return false;
@@ -157,9 +180,10 @@ __device__ __forceinline__ bool top_pass(const crsh_meta *meta, const batch_dev 
         if (L > nl) return false;
         top = L - 1;
         n_items = bd.top[0];
+        parts = (uint32_t)bd.top[2];
     } else {
         top = nl - 1;
-        n_items = level_items(meta, 0, n_mesh, P, 1u);
+        n_items = level_items(meta, 0, n_mesh, P, 1u, top_cap, parts);
     }
     return true;
 }
@@ -174,10 +198,10 @@ __global__ __launch_bounds__(256) void k_top_count(const float4 *__restrict__ na
                                                    trav_scratch S, crsh_meta *meta, batch_dev bd, uint32_t L)
 {
     __shared__ uint64_t s_red[3][256 / WAVE];
-    uint32_t top;
+    uint32_t top, parts;
     uint64_t n_items;
     clear_scan(S);
-    if (!top_pass<BATCH>(meta, bd, L, n_mesh, P, top, n_items)) return;
+    if (!top_pass<BATCH>(meta, bd, L, n_mesh, P, S.top_cap, top, n_items, parts)) return;
     const uint32_t off = meta->level_off[top];
     const uint32_t l = lane_id();
     const uint64_t wave = (uint64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
@@ -190,10 +214,11 @@ __global__ __launch_bounds__(256) void k_top_count(const float4 *__restrict__ na
         float lS;
         uint32_t i, lb, le;
         bool pass;
-        top_item<BATCH>(real ? it : it0, n_mesh, top, off, bd, na, nb, ns, msph, mesh_first, mesh_count, tri_begin,
+        top_item<BATCH>(real ? it : it0, parts, n_mesh, top, off, bd, na, nb, ns, msph, mesh_first, mesh_count, tri_begin,
                         tri_end, lA, lB, lS, i, lb, le, pass);
-        items += (uint64_t)__popcll(ballot(real));
-        mhits += (uint64_t)__popcll(ballot(real && pass));
+        const bool whole = real && it % parts == 0;     // an item counts with its first part
+        items += (uint64_t)__popcll(ballot(whole));
+        mhits += (uint64_t)__popcll(ballot(whole && pass));
         if (real) tests += le - lb;
         if (real && le == lb) S.cnt_top[it] = 0u;
         for (uint64_t todo = ballot(real && le > lb); todo; todo &= todo - 1u) {
@@ -259,10 +284,10 @@ __global__ __launch_bounds__(256) void k_top_emit(const float4 *__restrict__ na,
     __shared__ float4 s_ca[256 / WAVE][NF], s_cb[256 / WAVE][NF];   // a wave's item: children of its node
     __shared__ float s_cs[256 / WAVE][NF];
     const uint32_t wib = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-    uint32_t top;
+    uint32_t top, parts;
     uint64_t n_items;
     clear_scan(S);
-    if (!top_pass<BATCH>(meta, bd, L, n_mesh, P, top, n_items)) return;
+    if (!top_pass<BATCH>(meta, bd, L, n_mesh, P, S.top_cap, top, n_items, parts)) return;
     const pairs_dev out = P.p[top];
     if (out.tri == nullptr) return;
     const bool test = top >= lowest;         // level top + 1 (1-based) >= lowest + 1
@@ -283,7 +308,7 @@ __global__ __launch_bounds__(256) void k_top_emit(const float4 *__restrict__ na,
         uint32_t li, lb, le;
         bool pass;
         const uint64_t use = some ? it : it0 + (uint64_t)__builtin_ctzll(todo) * nwaves;
-        top_item<BATCH>(use, n_mesh, top, off, bd, na, nb, ns, msph, mesh_first, mesh_count, tri_begin, tri_end,
+        top_item<BATCH>(use, parts, n_mesh, top, off, bd, na, nb, ns, msph, mesh_first, mesh_count, tri_begin, tri_end,
                         lA, lB, lS, li, lb, le, pass);
         const uint64_t lpos = S.off[use];
         // the node's children
@@ -460,7 +485,8 @@ __global__ __launch_bounds__(COUNT_THREADS) void k_level_count_lanes(int32_t par
     __shared__ float s_ws[WN];
     const uint32_t nl = meta->n_levels;
     if ((uint32_t)parent_level > nl || parent_level < 2) return;
-    const uint64_t ntiles = level_items(meta, parent_level, 0, P, LEVEL_TILE);
+    uint32_t parts;
+    const uint64_t ntiles = level_items(meta, parent_level, 0, P, LEVEL_TILE, 0, parts);
     const pairs_dev in = P.p[parent_level - 1];
     if (in.tri == nullptr || P.p[parent_level - 2].tri == nullptr) return;
     uint64_t nin = meta->pairs[parent_level - 1];
@@ -1078,7 +1104,8 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_items(int32_t parent_leve
     if (nl == 0) return;
     if (batch_top > nl) return;
     const bool top = parent_level == 0;
-    const uint64_t n = batch_top ? bd_top[0] : level_items(meta, parent_level, n_mesh, P, tile_pairs);
+    uint32_t parts;
+    const uint64_t n = batch_top ? bd_top[0] : level_items(meta, parent_level, n_mesh, P, tile_pairs, S.top_cap, parts);
     const uint64_t base = batch_top ? bd_top[1] : 0u;
     const uint32_t out_level = batch_top ? batch_top - 1 : (top ? nl - 1 : (uint32_t)parent_level - 2);
     const uint64_t ntiles = (n + SCAN_TILE - 1) / SCAN_TILE;
@@ -1167,7 +1194,9 @@ __global__ __launch_bounds__(256) void k_batch_top_plan(batch_dev bd, crsh_meta 
             atomicOr(&meta->status, CRSH_OVERFLOW_ITEMS);
             total = 0;
         }
-        bd.top[0] = total;
+        const uint32_t parts = top_parts(total, bd.top_cap);
+        bd.top[0] = total * parts;
+        bd.top[2] = parts;
         bd.top[1] = L >= 1 ? meta->pairs[L - 1] : 0u;
     }
 }
@@ -1319,6 +1348,7 @@ static crsh_status traverse_run(const crsh_nodes *nodes, const crsh_scene *scene
     float *ns = (float *)w;
     w += align256((size_t)nodes->capacity * 4);
     trav_scratch S{};
+    S.top_cap = top_items;
     S.cnt_top = (uint32_t *)w;
     w += align256(top_items * 4 + 4);
     S.cnt = (uint32_t *)w;
