@@ -9,9 +9,10 @@
 //                 is the same for every key; it also routes the remaining
 //                 passes through the output / alternate buffers so that the
 //                 last pass writes the output;
-//   k_sort_pass   one launch per digit: 8192-key tiles ranked in LDS with
-//                 wave ballots (stable), a decoupled look-back across tiles
-//                 per digit, then a coalesced scatter staged through LDS.
+//   k_sort_pass   one launch per digit: tiles of 8192 keys (4096 for few keys)
+//                 ranked in LDS with wave ballots (stable), a decoupled
+//                 look-back across tiles per digit, then a coalesced scatter
+//                 staged through LDS.
 #include "common.hpp"
 
 namespace crsh {
@@ -30,6 +31,17 @@ constexpr uint32_t PASS_TILE = PASS_THREADS * PASS_ITEMS;  // keys per pass tile
 #define CRSH_SORT_HIST_BLOCKS 1024
 #endif
 constexpr uint32_t SORT_HIST_BLOCKS = CRSH_SORT_HIST_BLOCKS;  // most blocks of the histogram kernel
+#ifndef CRSH_SORT_FEW_THREADS
+#define CRSH_SORT_FEW_THREADS 1024
+#endif
+#ifndef CRSH_SORT_FEW_ITEMS
+#define CRSH_SORT_FEW_ITEMS 4
+#endif
+#ifndef CRSH_SORT_FEW
+#define CRSH_SORT_FEW (1u << 18)
+#endif
+constexpr uint32_t FEW_THREADS = CRSH_SORT_FEW_THREADS, FEW_ITEMS = CRSH_SORT_FEW_ITEMS;
+constexpr uint32_t FEW = CRSH_SORT_FEW;   // capacities up to here take tiles of FEW_THREADS * FEW_ITEMS keys
 
 // look-back words: flag in bits 31-30 (1 tile count, 2 inclusive prefix)
 constexpr uint32_t SLB_AGG = 1u << 30;
@@ -39,6 +51,11 @@ constexpr uint32_t SLB_MASK = (1u << 30) - 1;
 // The batched form adds a fifth, most significant digit: the frame of the
 // ray, read through the value (ray id) from a per-ray frame table.
 constexpr uint32_t MAX_PASSES = SORT_PASSES + 1;
+
+#ifndef CRSH_SORT_LOOK
+#define CRSH_SORT_LOOK 4
+#endif
+constexpr int32_t LOOK = CRSH_SORT_LOOK;   // look-back words read at once
 
 // plan codes for the source / destination of each pass
 enum : uint32_t { BUF_IN = 0, BUF_OUT = 1, BUF_ALT = 2, BUF_SKIP = 3 };
@@ -50,16 +67,14 @@ struct sort_ctl {
     uint32_t n;
 };
 
-__global__ void k_sort_clear(uint32_t *hist, sort_ctl *ctl, uint32_t *flags, const crsh_meta *meta,
+__global__ __launch_bounds__(256) void k_sort_clear(uint32_t *hist, sort_ctl *ctl, uint32_t *flags, const crsh_meta *meta,
                              uint32_t tiles_cap, uint32_t cap)
 {
     uint32_t n = min(meta->n_rays, cap);
     uint32_t tiles = (n + SORT_TILE - 1) / SORT_TILE;
-    uint64_t nflag = (uint64_t)MAX_PASSES * tiles_cap * 256;
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < nflag;
-         i += (uint64_t)gridDim.x * blockDim.x) {
-        uint32_t tile = (uint32_t)((i / 256) % tiles_cap);
-        if (tile < tiles) flags[i] = 0;
+    for (uint32_t row = blockIdx.x; row < MAX_PASSES * tiles; row += gridDim.x) {
+        const uint32_t p = row / tiles;
+        flags[((uint64_t)p * tiles_cap + (row - p * tiles)) * 256 + threadIdx.x] = 0;
     }
     uint32_t g = blockIdx.x * blockDim.x + threadIdx.x;
     if (g < MAX_PASSES * 256) hist[g] = 0;
@@ -70,20 +85,23 @@ __global__ void k_sort_clear(uint32_t *hist, sort_ctl *ctl, uint32_t *flags, con
 // tiles of SORT_TILE keys (grid-stride), counting in LDS, and add their
 // counts to the global histograms once at the end: one global atomic per
 // bin per block, not per tile (every block's atomics go to the same few
-// cache lines).  A tile's keys are all loaded before any is counted.
+// cache lines).  A tile's keys are all loaded before any is counted.  (The
+// plan by the last of these blocks instead of a launch costs more than the
+// launch: the fences it needs take 38 us over 1,024 blocks.)
+template <uint32_t PER>
 __global__ __launch_bounds__(SORT_THREADS) void k_sort_hist(const uint32_t *keys, const uint32_t *vals,
                                                             const uint32_t *frame_of, const crsh_meta *meta,
                                                             uint32_t *hist, uint32_t cap)
 {
-    constexpr uint32_t PER = SORT_TILE / SORT_THREADS;
+    constexpr uint32_t HTILE = PER * SORT_THREADS;
     __shared__ uint32_t h[MAX_PASSES * 256];
     const uint32_t n = min(meta->n_rays, cap);
-    const uint32_t ntiles = (n + SORT_TILE - 1) / SORT_TILE;
+    const uint32_t ntiles = (n + HTILE - 1) / HTILE;
     if (blockIdx.x >= ntiles) return;
     for (uint32_t i = threadIdx.x; i < MAX_PASSES * 256; i += SORT_THREADS) h[i] = 0;
     __syncthreads();
     for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const uint32_t base = tile * SORT_TILE;
+        const uint32_t base = tile * HTILE;
         uint32_t k[PER], f[PER];
 #pragma unroll
         for (uint32_t r = 0; r < PER; ++r) {
@@ -116,10 +134,16 @@ __global__ __launch_bounds__(256) void k_sort_plan(uint32_t *hist, sort_ctl *ctl
     __shared__ uint32_t skip[MAX_PASSES];
     uint32_t n = min(meta->n_rays, cap);
     uint32_t d = threadIdx.x;
+    uint32_t cnt[MAX_PASSES];
+#pragma unroll
+    for (uint32_t p = 0; p < MAX_PASSES; ++p)
+        cnt[p] = p < passes ? hist[p * 256 + d] : 0u;
     if (d < MAX_PASSES) skip[d] = (n == 0) || d >= passes;
     __syncthreads();
-    for (uint32_t p = 0; p < passes; ++p) {
-        uint32_t c = hist[p * 256 + d];
+#pragma unroll
+    for (uint32_t p = 0; p < MAX_PASSES; ++p) {
+        if (p >= passes) break;
+        const uint32_t c = cnt[p];
         if (c == n) skip[p] = 1;    // one digit value holds every key
         uint32_t total;
         uint32_t ex = block_excl_scan<uint32_t, 256 / WAVE>(c, scratch, total);
@@ -293,17 +317,32 @@ __device__ __forceinline__ void sort_tile(pass_lds<THREADS, ITEMS> &S, const uin
         }
         uint32_t excl = 0;
         if (tile > 0) {
+            // LOOK predecessors' words are requested at once: tiles start
+            // together, so there are many to walk back over, and a word
+            // takes about a microsecond
             int32_t j = (int32_t)tile - 1;
-            while (j >= 0) {
-                uint32_t f = __hip_atomic_load(&fl[(size_t)j * 256 + d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                uint32_t fl2 = f & ~SLB_MASK;
-                if (fl2 == 0) {
-                    __builtin_amdgcn_s_sleep(1);
-                    continue;
+            bool found = false;
+            while (!found) {
+                uint32_t f[LOOK];
+#pragma unroll
+                for (int32_t i = 0; i < LOOK; ++i)
+                    f[i] = j >= i ? __hip_atomic_load(&fl[(size_t)(j - i) * 256 + d], __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT)
+                                  : SLB_INC;
+                bool ready = true;      // false from the first word that is not there yet
+                int32_t got = 0;
+#pragma unroll
+                for (int32_t i = 0; i < LOOK; ++i) {
+                    const uint32_t fl2 = f[i] & ~SLB_MASK;
+                    ready = ready && !found && fl2 != 0;
+                    if (ready) {
+                        excl += f[i] & SLB_MASK;
+                        found = fl2 == SLB_INC;
+                        ++got;
+                    }
                 }
-                excl += f & SLB_MASK;
-                if (fl2 == SLB_INC) break;
-                --j;
+                j -= got;
+                if (got == 0) __builtin_amdgcn_s_sleep(1);
             }
             __hip_atomic_store(&fl[(size_t)tile * 256 + d], SLB_INC | (excl + run), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
@@ -353,7 +392,7 @@ __device__ __forceinline__ void sort_tile(pass_lds<THREADS, ITEMS> &S, const uin
 template <bool FRAME, uint32_t THREADS, uint32_t ITEMS>
 __global__ __launch_bounds__(THREADS) void k_sort_pass(sort_bufs bufs, const uint32_t *offsets, sort_ctl *ctl,
                                                        uint32_t *flags, uint32_t pass, uint32_t tiles_cap,
-                                                       const uint32_t *frame_of)
+                                                       const uint32_t *frame_of, bool last)
 {
     constexpr uint32_t TILE = THREADS * ITEMS;
     static_assert(THREADS >= 256 && THREADS % 256 == 0, "one thread per digit");
@@ -361,9 +400,16 @@ __global__ __launch_bounds__(THREADS) void k_sort_pass(sort_bufs bufs, const uin
     __shared__ pass_lds<THREADS, ITEMS> S;
 
     const uint32_t src = ctl->src[pass];
-    if (src == BUF_SKIP) return;
     const uint32_t dst = ctl->dst[pass];
     const uint32_t n = ctl->n;
+    if (src == BUF_SKIP) {
+        if (!last || !ctl->copy_through) return;
+        for (uint32_t i = blockIdx.x * THREADS + threadIdx.x; i < n; i += gridDim.x * THREADS) {
+            bufs.kout[i] = bufs.kin[i];
+            bufs.vout[i] = bufs.vin[i];
+        }
+        return;
+    }
     const uint32_t ntiles = (n + TILE - 1) / TILE;
     if (threadIdx.x == 0) S.tile = atomicAdd(&ctl->tile_ctr[pass], 1u);
     for (uint32_t i = threadIdx.x; i < THREADS / WAVE * 256; i += THREADS) S.wcnt[i] = 0;
@@ -377,17 +423,6 @@ __global__ __launch_bounds__(THREADS) void k_sort_pass(sort_bufs bufs, const uin
     uint32_t *vout = pick_dst(bufs, dst, false);
     uint32_t *fl = flags + ((size_t)pass * tiles_cap) * 256;
     sort_tile<FRAME, THREADS, ITEMS>(S, kin, vin, kout, vout, offsets, fl, pass, n, tile, frame_of);
-}
-
-__global__ void k_sort_copy(const uint32_t *kin, const uint32_t *vin, uint32_t *kout, uint32_t *vout,
-                            const sort_ctl *ctl)
-{
-    if (!ctl->copy_through) return;
-    uint32_t n = ctl->n;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        kout[i] = kin[i];
-        vout[i] = vin[i];
-    }
 }
 
 }  // namespace crsh
@@ -430,25 +465,35 @@ crsh_status sort_launch(const uint32_t *keys_in, const uint32_t *ids_in, const u
     uint32_t *flags = (uint32_t *)w;
     const uint32_t passes = frame_of ? MAX_PASSES : SORT_PASSES;
 
-    k_sort_clear<<<1024, 256, 0, stream>>>(hist, ctl, flags, meta, tiles_cap, capacity);
+    const bool few = capacity <= FEW;
+    k_sort_clear<<<std::min<uint32_t>(MAX_PASSES * tiles_cap, 1024), 256, 0, stream>>>(hist, ctl, flags, meta,
+                                                                                       tiles_cap, capacity);
     {
         prof_scope ps("k_sort_hist", stream);
-        k_sort_hist<<<std::min<uint32_t>(tiles_cap, SORT_HIST_BLOCKS), SORT_THREADS, 0, stream>>>(
-            keys_in, ids_in, frame_of, meta, hist, capacity);
+        // few keys: 4 a thread, so that there are blocks enough
+        if (few)
+            k_sort_hist<4><<<std::max<uint32_t>((capacity + 4 * SORT_THREADS - 1) / (4 * SORT_THREADS), 1),
+                             SORT_THREADS, 0, stream>>>(keys_in, ids_in, frame_of, meta, hist, capacity);
+        else
+            k_sort_hist<SORT_TILE / SORT_THREADS><<<std::min<uint32_t>(tiles_cap, SORT_HIST_BLOCKS), SORT_THREADS, 0,
+                                                    stream>>>(keys_in, ids_in, frame_of, meta, hist, capacity);
     }
     k_sort_plan<<<1, 256, 0, stream>>>(hist, ctl, meta, capacity, passes);
     sort_bufs b{keys_in, ids_in, keys_out, ids_out, kalt, valt};
-    const uint32_t pass_tiles = (capacity + PASS_TILE - 1) / PASS_TILE;
+    const uint32_t pass_tile = few ? FEW_THREADS * FEW_ITEMS : PASS_TILE;
+    const uint32_t pass_tiles = (capacity + pass_tile - 1) / pass_tile;
     for (uint32_t p = 0; p < passes; ++p) {
         prof_scope ps("k_sort_pass", stream);
-        if (p < SORT_PASSES)
-            k_sort_pass<false, PASS_THREADS, PASS_ITEMS><<<pass_tiles, PASS_THREADS, 0, stream>>>(
-                b, hist, ctl, flags, p, tiles_cap, nullptr);
+        const uint32_t *fr = p < SORT_PASSES ? nullptr : frame_of;
+        const bool last = p + 1 == passes;
+#define CRSH_PASS(FRAME, T, I) \
+    k_sort_pass<FRAME, T, I><<<pass_tiles, T, 0, stream>>>(b, hist, ctl, flags, p, tiles_cap, fr, last)
+        if (few)
+            fr ? CRSH_PASS(true, FEW_THREADS, FEW_ITEMS) : CRSH_PASS(false, FEW_THREADS, FEW_ITEMS);
         else
-            k_sort_pass<true, PASS_THREADS, PASS_ITEMS><<<pass_tiles, PASS_THREADS, 0, stream>>>(
-                b, hist, ctl, flags, p, tiles_cap, frame_of);
+            fr ? CRSH_PASS(true, PASS_THREADS, PASS_ITEMS) : CRSH_PASS(false, PASS_THREADS, PASS_ITEMS);
+#undef CRSH_PASS
     }
-    k_sort_copy<<<256, 256, 0, stream>>>(keys_in, ids_in, keys_out, ids_out, ctl);
     return hip_check(hipGetLastError(), "crsh_sort launch");
 }
 
