@@ -1,19 +1,20 @@
 // Stage 3: hierarchy creation (Sec. 3.3.6, Eq. 1-8).
 //
-// k_build_info  node counts of every level from the ray count (device side,
-//               so the frame needs no host round trip);
 // k_permute     rays gathered into sorted order (coalesced writes); the leaf
-//               kernel and the final tests then read them contiguously;
+//               kernel and the final tests then read them contiguously; one
+//               thread takes the node counts of every level from the ray
+//               count (device side, so the frame needs no host round trip);
 // k_build_leaf  one thread per level-1 node: the compact cone of its B rays
 //               added one at a time in sorted order (Eq. 1-4) and the sphere
 //               of their origins as a balanced pairwise tree (Eq. 7-8);
 // k_build_up    one thread per upper node: balanced pairwise trees of its F
-//               children's spheres (Eq. 7-8) and cones (Eq. 5-6).
+//               children's spheres (Eq. 7-8) and cones (Eq. 5-6);
+// k_build_tail  the levels of at most UP_TAIL nodes, one block for all of them.
 // Trees are unrolled over a power-of-two slot count, so every slot index is a
 // compile-time constant and the nodes stay in registers.
 //
 // Batched form: k_batch_levels sizes every frame's levels (the same rule as
-// k_build_info, per frame) and lays each level out frame by frame; the leaf
+// the plain one, per frame) and lays each level out frame by frame; the leaf
 // and upper kernels find their frame and take their rays / children from the
 // frame's ranges, and record each node's first ray or child and its count
 // (with the frame) for the traversal and the final tests.
@@ -43,8 +44,8 @@ __device__ __forceinline__ void put_node(const nodes_dev &nd, uint32_t i, const 
     nd.sec[i] = open ? 1.0f / k.c : 0.0f;
 }
 
-__global__ void k_build_info(crsh_meta *meta, uint32_t B, uint32_t F, uint32_t levels, uint32_t node_cap,
-                             uint32_t ray_cap)
+__device__ __forceinline__ void build_info(crsh_meta *meta, uint32_t B, uint32_t F, uint32_t levels,
+                                           uint32_t node_cap, uint32_t ray_cap)
 {
     uint32_t n = min(meta->n_rays, ray_cap);
     meta->n_rays = n;
@@ -143,10 +144,13 @@ struct rays_out {
     uint32_t *pix;
 };
 
-__global__ void k_permute(rays_in in, const uint32_t *sorted_ids, rays_out out, const crsh_meta *meta,
-                          uint32_t cap)
+// levels != 0: the level counts too (not in a batch, which has them already);
+// the one thread that writes the ray count writes what every thread takes.
+__global__ void k_permute(rays_in in, const uint32_t *sorted_ids, rays_out out, crsh_meta *meta, uint32_t cap,
+                          uint32_t B, uint32_t F, uint32_t levels, uint32_t node_cap)
 {
-    uint32_t n = meta->n_rays;
+    uint32_t n = min(meta->n_rays, cap);
+    if (levels && blockIdx.x == 0 && threadIdx.x == 0) build_info(meta, B, F, levels, node_cap, cap);
     for (uint32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < n; s += gridDim.x * blockDim.x) {
         uint32_t id = sorted_ids[s];
         if (id >= cap) id = 0;      // ids come from the sort: never taken
@@ -209,11 +213,9 @@ __global__ __launch_bounds__(256) void k_build_leaf(const float *__restrict__ ox
 }
 
 template <int NF, bool BATCH>
-__global__ __launch_bounds__(256) void k_build_up(uint32_t lv, uint32_t F, nodes_dev nd, const crsh_meta *meta,
-                                                  batch_dev bd)
+__device__ __forceinline__ void build_up(uint32_t lv, uint32_t j, uint32_t F, const nodes_dev &nd,
+                                         const crsh_meta *meta, const batch_dev &bd)
 {
-    const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (lv >= meta->n_levels || j >= meta->level_cnt[lv]) return;
     const uint32_t below = meta->level_off[lv - 1];
     uint32_t b, k;
     if constexpr (BATCH) {
@@ -251,6 +253,31 @@ __global__ __launch_bounds__(256) void k_build_up(uint32_t lv, uint32_t F, nodes
         }
     }
     put_node(nd, meta->level_off[lv] + j, sp[0], kc[0]);
+}
+
+template <int NF, bool BATCH>
+__global__ __launch_bounds__(256) void k_build_up(uint32_t lv, uint32_t F, nodes_dev nd, const crsh_meta *meta,
+                                                  batch_dev bd)
+{
+    const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
+    if (lv >= meta->n_levels || j >= meta->level_cnt[lv]) return;
+    build_up<NF, BATCH>(lv, j, F, nd, meta, bd);
+}
+
+// Levels lv0 and up, each of at most UP_TAIL nodes: a thread per node, a
+// barrier between levels.  A node's chain of square roots and divisions takes
+// 2 to 4 us and a launch as long again, so the upper levels of a small frame
+// are one launch instead of one each.
+constexpr uint32_t UP_TAIL = 512;
+template <int NF, bool BATCH>
+__global__ __launch_bounds__(UP_TAIL) void k_build_tail(uint32_t lv0, uint32_t F, nodes_dev nd, const crsh_meta *meta,
+                                                        batch_dev bd)
+{
+    const uint32_t nl = meta->n_levels;
+    for (uint32_t lv = lv0; lv < nl; ++lv) {
+        if (threadIdx.x < meta->level_cnt[lv]) build_up<NF, BATCH>(lv, threadIdx.x, F, nd, meta, bd);
+        __syncthreads();
+    }
 }
 
 static int pow2_at_least(int x)
@@ -298,9 +325,6 @@ crsh_status build_launch(const crsh_rays *rays, const uint32_t *sorted_ids, int3
     if (bd)
         k_batch_levels<<<1, 256, 0, stream>>>(b, meta, (uint32_t)bundle, (uint32_t)merge, (uint32_t)levels,
                                                nodes->capacity, rays->capacity);
-    else
-        k_build_info<<<1, 1, 0, stream>>>(meta, (uint32_t)bundle, (uint32_t)merge, (uint32_t)levels,
-                                          nodes->capacity, rays->capacity);
     rays_in ri{rays->ox, rays->oy, rays->oz, rays->dx, rays->dy, rays->dz, rays->tmax, rays->pix};
     rays_out ro{sorted->ox, sorted->oy, sorted->oz, sorted->dx, sorted->dy, sorted->dz, sorted->tmax, sorted->pix};
     uint32_t cap = rays->capacity;
@@ -308,7 +332,8 @@ crsh_status build_launch(const crsh_rays *rays, const uint32_t *sorted_ids, int3
     if (pb == 0) pb = 1;
     {
         prof_scope ps("k_permute", stream);
-        k_permute<<<pb, 256, 0, stream>>>(ri, sorted_ids, ro, meta, cap);
+        k_permute<<<pb, 256, 0, stream>>>(ri, sorted_ids, ro, meta, cap, (uint32_t)bundle, (uint32_t)merge,
+                                          bd ? 0u : (uint32_t)levels, nodes->capacity);
     }
     nodes_dev nd{nodes->cx, nodes->cy, nodes->cz, nodes->r, nodes->ax, nodes->ay, nodes->az,
                  nodes->c, nodes->s, nodes->tan, nodes->sec, nodes->capacity};
@@ -334,10 +359,14 @@ crsh_status build_launch(const crsh_rays *rays, const uint32_t *sorted_ids, int3
 #undef CRSH_LEAF
     int nf = pow2_at_least(merge);
 #define CRSH_UP(NF)                                                                                        \
-    (bd ? k_build_up<NF, true><<<g, 256, 0, stream>>>(lv, merge, nd, meta, b)                             \
-        : k_build_up<NF, false><<<g, 256, 0, stream>>>(lv, merge, nd, meta, b))
+    (tail ? (bd ? k_build_tail<NF, true><<<1, UP_TAIL, 0, stream>>>(lv, merge, nd, meta, b)               \
+                : k_build_tail<NF, false><<<1, UP_TAIL, 0, stream>>>(lv, merge, nd, meta, b))             \
+          : (bd ? k_build_up<NF, true><<<g, 256, 0, stream>>>(lv, merge, nd, meta, b)                     \
+                : k_build_up<NF, false><<<g, 256, 0, stream>>>(lv, merge, nd, meta, b)))
     for (int lv = 1; lv < levels; ++lv) {
         cnt = (cnt + merge - 1) / merge + extra;
+        // cnt bounds this level, and the ones above it have no more
+        const bool tail = cnt <= UP_TAIL;
         g = (uint32_t)std::min<uint64_t>((cnt + 255) / 256, 1u << 22);
         if (g == 0) g = 1;
         switch (nf) {
@@ -346,7 +375,7 @@ crsh_status build_launch(const crsh_rays *rays, const uint32_t *sorted_ids, int3
         case 8: CRSH_UP(8); break;
         default: CRSH_UP(16); break;
         }
-        if (!bd && cnt <= 1) break;
+        if (tail) break;
     }
 #undef CRSH_UP
     return hip_check(hipGetLastError(), "crsh_build launch");
