@@ -7,7 +7,8 @@
 // k_hit        persistent workgroups over the level-1 pairs: a chunk of pairs
 //              is binned by leaf in LDS, each leaf's rays are tested against
 //              its triangles with matrix instructions, and what that filter
-//              cannot reject goes through the test as written.  A hit lowers
+//              cannot reject goes through the test as written (the fused form
+//              reads level-2 pairs and the pass bits of their children).  A hit lowers
 //              the ray's 64-bit (order-mapped t, triangle) key with an atomic
 //              minimum: the closest hit, ties to the lower triangle id.
 // k_hit_final  one thread per sorted ray: decode the key, recompute u, v with
@@ -139,80 +140,14 @@ __global__ void k_hit_pack(tri_verts V, uint32_t m, hit_tris_ws tri, sorted_rays
     for (uint32_t t = gid; t <= m; t += stride) put_tri(V, t, m, tri);
 }
 
-// One step of the final tests for a wave: each lane group holds a pair --
-// its triangle (a, b, c: v0, e1, e2 packed), the triangle id, the byte
-// offsets of the leaf's first ray slot and first direction, and the interval
-// start of the pair's frame -- and lane j of the group tests ray j of the
-// leaf.  `live` is the wave mask of the lanes whose test is one of the
-// pair's.  A lane outside it may still read a ray: that of a slot past the
-// leaf's rays, or a zero ray (a padded slot, or an offset past the arrays'
-// ends, which reads zeros); a zero ray has a zero determinant and fails the
-// first half, so only the lanes j >= B of a group wider than the bundle need
-// the mask.  COUNT: the step counts its tests (the lanes of `live`, less the
-// padded slots of the batched form); without it the caller counts them.
-// Hits go to the slot keys.  Called by every lane of the wave.
-template <bool BATCH, bool COUNT>
-__device__ __forceinline__ void hit_step(const __amdgpu_buffer_rsrc_t &org_r, const __amdgpu_buffer_rsrc_t &dir_r,
-                                         const float4 &a, const float4 &b, float tc, uint32_t tri_id,
-                                         uint32_t ray_off, float t_min, uint64_t live, uint32_t j,
-                                         unsigned long long *keys, uint64_t &tests, uint64_t &upass,
-                                         uint64_t &uvpass)
-{
-    const uint32_t ro = ray_off + j * 16u;
-    const float4 ro4 = buf_load4(org_r, ro);
-    const float4 di = buf_load4(dir_r, ro);
-    const f3 D = mk(di.x, di.y, di.z);
-    tri_t tr;
-    tr.v0 = mk(a.x, a.y, a.z);
-    tr.e1 = mk(a.w, b.x, b.y);
-    tr.e2 = mk(b.z, b.w, tc);
-    if constexpr (COUNT) {
-        // a padded slot's NaN t_min accepts nothing; it only must not count
-        // as a test
-        if (BATCH) live &= ballot(__float_as_uint(ro4.w) != PAD_SLOT);
-        tests += (uint64_t)__popcll(live);
-    }
-    mt_head h;
-    const uint64_t mm = mt_first_half(mk(ro4.x, ro4.y, ro4.z), D, tr, h) & live;
-    // a wave-uniform branch: the wave runs the second half only if one of
-    // its lanes needs it (every lane computes it; the masks keep the lanes
-    // that needed it)
-    if (mm != 0) {
-        float th;
-        uint64_t pu, puv, hit;
-        mt_second_half(D, t_min, ro4.w, tr, h, th, pu, puv, hit);
-        upass += (uint64_t)__popcll(pu & mm);
-        uvpass += (uint64_t)__popcll(puv & mm);
-        if (__builtin_amdgcn_inverse_ballot_w64(hit & mm)) atomicMin(&keys[ro >> 4], hit_key(th, tri_id));
-    }
-}
-
-// The wave totals of a final-test kernel added to meta (s_red: [3][waves]).
-template <uint32_t NW>
-__device__ __forceinline__ void hit_counts(uint64_t (*s_red)[NW], uint32_t wib, uint32_t l, uint64_t tests,
-                                           uint64_t upass, uint64_t uvpass, crsh_meta *meta)
-{
-    if (l == 0) {
-        s_red[0][wib] = tests;
-        s_red[1][wib] = upass;
-        s_red[2][wib] = uvpass;
-    }
-    __syncthreads();
-    if (threadIdx.x < 3) {
-        uint64_t tot = 0;
-        for (uint32_t i = 0; i < blockDim.x / WAVE; ++i) tot += s_red[threadIdx.x][i];
-        unsigned long long *dst = threadIdx.x == 0 ? (unsigned long long *)&meta->final_tests
-                                : threadIdx.x == 1 ? (unsigned long long *)&meta->final_u_pass
-                                                   : (unsigned long long *)&meta->final_uv_pass;
-        if (tot) atomicAdd(dst, (unsigned long long)tot);
-    }
-}
-
 // Slots in use: the plain form's sorted rays, or B per level-1 node.  PACKED:
 // the level-1 pairs are packed words in ptri (node above the low
 // CRSH_PACKED_TRI_BITS, triangle minus tri_base below; pnode unused).
 // Batched form: the build's per-node record of a leaf (bd.node_info) holds
 // its ray count and frame, and the frame its interval start.
+//
+// FUSED: the level-1 pairs are not stored; they are the children that the pass
+// bits of the level-2 pairs keep, placed in the leaf runs straight from there.
 //
 // A workgroup takes a chunk of consecutive pairs.  Pairs of one top-level
 // node name a few hundred leaves in triangle order, so a chunk holds many
@@ -242,6 +177,11 @@ __device__ __forceinline__ void hit_counts(uint64_t (*s_red)[NW], uint32_t wib, 
 // triangle entries through LDS (a third of the L1 accesses, but more
 // instructions and fewer workgroups) 8.3 ms; the filter's outcome as wave masks
 // instead of shifted sign bits 9.4 ms.
+// Fused (640x360 mixed rays, 144 M level-2 pairs, 2.8 G tests): 5.4 ms with a
+// lane per (child, ray), 1.85 ms so.  A chunk of 2,048 level-2 pairs has 2,500
+// children there; 1,536 1.96 ms, 1,792 1.91, 2,560 2.17, 3,072 2.18 (more
+// chunks overflow and are taken in halves); parts of what is expected to fit
+// instead of equal ones 2.06 (a small rest each).
 constexpr uint32_t HIT_THREADS = 256;
 constexpr uint32_t HIT_WAVES = HIT_THREADS / WAVE;
 constexpr uint32_t HIT_PPT = 16;                            // pairs per thread of a chunk
@@ -253,6 +193,17 @@ constexpr uint32_t HIT_QUEUE = 128;                         // queued items of a
 constexpr uint32_t HIT_WAVES_PER_SIMD = 4;                  // registers for 4 workgroups per compute unit
 // block word: first triangle (13 bits), triangles - 1 (5 bits), leaf bin (10 bits)
 static_assert(HIT_CHUNK <= 1u << 13 && HIT_BINS <= 1u << 10 && CRSH_MAX_BUNDLE <= 32, "block word");
+
+// What the pairs are.  Fused: level-2 pairs and a pass bit per child (the
+// level-1 pairs are never stored): pair q keeps child j (leaf first + j, first
+// = node * F or the build's record) when bit q * nf + j of `mask` is set.
+// parts: workgroups of the launch before, whose counts stay.
+enum { HIT_STORED, HIT_PACKED, HIT_FUSED };
+struct fused_in {
+    const uint32_t *mask;
+    uint32_t nf, F, parts;
+};
+constexpr uint32_t HIT_FUSED_PPT = 8;                   // level-2 pairs per thread of a chunk
 
 typedef float mfma4 __attribute__((ext_vector_type(4)));
 
@@ -323,14 +274,17 @@ __device__ __forceinline__ void filter_all(const float4 &f0, const float4 &f1, c
     }
 }
 
-template <int LG, bool BATCH, bool PACKED>
+template <int LG, bool BATCH, int IN>
 __global__ __launch_bounds__(HIT_THREADS, HIT_WAVES_PER_SIMD) void k_hit(hit_slots_ws hs, const float4 *__restrict__ tri,
                                                      const float4 *__restrict__ ftri,
                                                      const uint32_t *__restrict__ ptri,
                                                      const uint32_t *__restrict__ pnode, uint64_t cap1, uint32_t B,
                                                      unsigned long long *keys, crsh_meta *meta, uint32_t m,
-                                                     uint32_t tri_base, batch_dev bd, float t_min, uint32_t chunk_max)
+                                                     uint32_t tri_base, batch_dev bd, float t_min, uint32_t chunk_max,
+                                                     fused_in fu)
 {
+    constexpr bool PACKED = IN == HIT_PACKED, FUSED = IN == HIT_FUSED;
+    constexpr uint32_t PPT = FUSED ? HIT_FUSED_PPT : HIT_PPT;
     constexpr uint32_t G = 1u << LG;                // lanes, and triangles of a block, per group
     constexpr uint32_t GPW = WAVE / G;              // groups of a wave
     constexpr uint32_t NONE = 0xFFFFFFFFu;
@@ -341,8 +295,9 @@ __global__ __launch_bounds__(HIT_THREADS, HIT_WAVES_PER_SIMD) void k_hit(hit_slo
     __shared__ uint2 s_scan[HIT_WAVES], s_lohi[HIT_WAVES];
     __shared__ uint64_t s_red[3][HIT_WAVES];
     const uint32_t ns = BATCH ? batch_slots(meta, B, hs.slots) : min(meta->n_rays, hs.slots);
-    uint64_t np = meta->n_levels ? meta->pairs[0] : 0;
+    uint64_t np = meta->n_levels > (FUSED ? 1u : 0u) ? meta->pairs[FUSED ? 1 : 0] : 0;
     np = np < cap1 ? np : cap1;
+    const uint32_t off2 = FUSED ? meta->level_off[1] : 0u, np2 = FUSED ? meta->level_cnt[1] : 0u;
     // no slots, no tests
     const uint32_t last_leaf = ns ? (ns - 1u) / B : 0u;
     np = ns ? np : 0u;
@@ -392,27 +347,94 @@ __global__ __launch_bounds__(HIT_THREADS, HIT_WAVES_PER_SIMD) void k_hit(hit_slo
     const float rounds = ceilf((float)np / ((float)gridDim.x * (float)chunk_max));
     uint32_t cs = rounds > 0.0f ? (uint32_t)((float)np / (rounds * (float)gridDim.x)) + 1u : 1u;
     cs = min(max((cs + 63u) & ~63u, HIT_MIN_CHUNK), chunk_max);
-    for (uint64_t c0 = (uint64_t)blockIdx.x * cs; c0 < np; c0 += (uint64_t)gridDim.x * cs) {
-        const uint32_t cn = (uint32_t)min(np - c0, (uint64_t)cs);
+    // pass bits of the four pairs from q on (q a multiple of 4), pair q + i in
+    // the bits from i * nf on
+    auto load_bits = [&](uint64_t q, uint2 &w, uint32_t &sh) {
+        const uint64_t bit = q * fu.nf;
+        w.x = fu.mask[bit >> 5];
+        w.y = fu.nf > 8u ? fu.mask[(bit >> 5) + 1] : 0u;
+        sh = (uint32_t)bit & 31u;
+    };
+    auto bits_of = [&](uint2 w, uint32_t sh, uint32_t i) {
+        const uint32_t at = sh + i * fu.nf;
+        return (at < 32u ? w.x >> at : w.y >> (at - 32u)) & ((1u << fu.nf) - 1u);
+    };
+    for (uint64_t chunk = (uint64_t)blockIdx.x * cs; chunk < np; chunk += (uint64_t)gridDim.x * cs) {
+    const uint32_t chunk_n = (uint32_t)min(np - chunk, (uint64_t)cs);
+    // (once; fused: as many pairs at a time as have survivors that fit)
+    for (uint32_t done = 0, cn; done < chunk_n; done += cn) {
+        const uint64_t c0 = chunk + done;
+        cn = chunk_n - done;
+        if constexpr (FUSED) {
+            // equal parts of the rest as long as the survivors do not fit
+            // (those of 256 pairs always do)
+            for (;;) {
+                uint32_t kids = 0u;
+#pragma unroll
+                for (uint32_t k = 0; k < PPT; k += 4) {
+                    const uint32_t q = k * HIT_THREADS + 4 * threadIdx.x;
+                    if (q >= cn) continue;
+                    uint2 w;
+                    uint32_t sh;
+                    load_bits(c0 + q, w, sh);
+#pragma unroll
+                    for (uint32_t i = 0; i < 4; ++i) kids += q + i < cn ? (uint32_t)__popc(bits_of(w, sh, i)) : 0u;
+                }
+                kids = wave_reduce(kids, 0u, [](uint32_t a, uint32_t b) { return a + b; });
+                if (l == 0) s_lohi[wib].x = kids;
+                __syncthreads();
+                kids = 0u;
+#pragma unroll
+                for (uint32_t w = 0; w < HIT_WAVES; ++w) kids += s_lohi[w].x;
+                __syncthreads();                    // s_lohi is written again
+                kids = __builtin_amdgcn_readfirstlane(kids);
+                if (kids <= HIT_CHUNK) break;
+                const uint32_t parts = (kids - 1u) / HIT_CHUNK + 1u;        // at least 2
+                cn = ((cn - 1u) / parts + 64u) & ~63u;
+            }
+        }
         uint32_t from = 0u;                         // first leaf not binned yet
         for (bool more = true; more;) {
             uint32_t tid = threadIdx.x;
             asm volatile("" : "+v"(tid));           // nothing of a round is kept over the next
-            uint32_t my_t[HIT_PPT], my_leaf[HIT_PPT];
-#pragma unroll
-            for (uint32_t k = 0; k < HIT_PPT; k += 4) {     // four consecutive pairs a load
-                load4(ptri + c0, k * HIT_THREADS + 4 * tid, cn, &my_t[k]);
-                if constexpr (!PACKED) load4(pnode + c0, k * HIT_THREADS + 4 * tid, cn, &my_leaf[k]);
-            }
+            // my_leaf: the pair's leaf (fused: the first child of its node)
+            uint32_t my_t[PPT], my_leaf[PPT], my_bits[FUSED ? PPT : 1];
             uint32_t lo = NONE, hi = 0u;            // the leaves still to do: smallest and largest
 #pragma unroll
-            for (uint32_t k = 0; k < HIT_PPT; ++k) {
+            for (uint32_t k = 0; k < PPT; k += 4) {     // four consecutive pairs a load
+                const uint32_t q = k * HIT_THREADS + 4 * tid;
+                load4(ptri + c0, q, cn, &my_t[k]);
+                if constexpr (!PACKED) load4(pnode + c0, q, cn, &my_leaf[k]);
+                if constexpr (FUSED) {
+                    uint2 w = make_uint2(0u, 0u);
+                    uint32_t sh = 0u;
+                    if (q < cn) load_bits(c0 + q, w, sh);
+#pragma unroll
+                    for (uint32_t i = 0; i < 4; ++i) my_bits[k + i] = bits_of(w, sh, i);
+                }
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < PPT; ++k) {
+                const uint32_t q = k / 4 * 4 * HIT_THREADS + 4 * tid + k % 4;
+                if constexpr (FUSED) {
+                    // the leaves from `from` on that have rays; a pair out of range has none
+                    const uint32_t node = my_leaf[k];
+                    uint32_t b = q < cn && my_t[k] < m && node < np2 ? my_bits[k] : 0u;
+                    uint32_t f = node * fu.F;
+                    if constexpr (BATCH) f = b ? bd.node_first[off2 + node] : 0u;
+                    b = f <= last_leaf ? b & (uint32_t)((1ull << min(last_leaf - f + 1u, 16u)) - 1ull) : 0u;
+                    b = f < from ? b >> min(from - f, 31u) << min(from - f, 31u) : b;
+                    my_bits[k] = b;
+                    my_leaf[k] = f;
+                    lo = b ? min(lo, f + (uint32_t)__builtin_ctz(b)) : lo;
+                    hi = b ? max(hi, f + 31u - (uint32_t)__builtin_clz(b)) : hi;
+                    continue;
+                }
                 if constexpr (PACKED) {
                     my_leaf[k] = my_t[k] >> CRSH_PACKED_TRI_BITS;
                     my_t[k] = tri_base + (my_t[k] & ((1u << CRSH_PACKED_TRI_BITS) - 1u));
                 }
                 // a pair out of range has no tests
-                const uint32_t q = k / 4 * 4 * HIT_THREADS + 4 * tid + k % 4;
                 const bool ok = q < cn && my_t[k] < m && my_leaf[k] <= last_leaf && my_leaf[k] >= from;
                 hi = ok ? max(hi, my_leaf[k]) : hi;
                 my_leaf[k] = ok ? my_leaf[k] : NONE;
@@ -435,8 +457,17 @@ __global__ __launch_bounds__(HIT_THREADS, HIT_WAVES_PER_SIMD) void k_hit(hit_slo
             more = base != NONE && hi - base >= HIT_BINS;
             from = base + HIT_BINS;
             // pairs per leaf; each pair's bin and its place in the leaf's run
+            // (fused: the place is taken when the triangle is put there)
+            if constexpr (FUSED) {
+                for (uint32_t c = 0; c < fu.nf; ++c)
 #pragma unroll
-            for (uint32_t k = 0; k < HIT_PPT; ++k) {
+                    for (uint32_t k = 0; k < PPT; ++k) {
+                        const uint32_t bin = my_leaf[k] + c - base;
+                        if ((my_bits[k] >> c & 1u) != 0u && bin < HIT_BINS) atomicAdd(&s_cnt[bin], 1u);
+                    }
+            } else
+#pragma unroll
+            for (uint32_t k = 0; k < PPT; ++k) {
                 const uint32_t bin = my_leaf[k] - base;
                 const bool ok = bin < HIT_BINS && my_leaf[k] != NONE;
                 my_leaf[k] = NONE;
@@ -482,8 +513,16 @@ __global__ __launch_bounds__(HIT_THREADS, HIT_WAVES_PER_SIMD) void k_hit(hit_slo
                 tests += (uint64_t)c[k] * rays;
             }
             __syncthreads();
+            if constexpr (FUSED) {
+                for (uint32_t c = 0; c < fu.nf; ++c)
 #pragma unroll
-            for (uint32_t k = 0; k < HIT_PPT; ++k)
+                    for (uint32_t k = 0; k < PPT; ++k) {
+                        const uint32_t bin = my_leaf[k] + c - base;
+                        if ((my_bits[k] >> c & 1u) != 0u && bin < HIT_BINS) s_tri[atomicAdd(&s_cnt[bin], 1u)] = my_t[k];
+                    }
+            } else
+#pragma unroll
+            for (uint32_t k = 0; k < PPT; ++k)
                 if (my_leaf[k] != NONE) s_tri[s_cnt[my_leaf[k] % HIT_BINS] + my_leaf[k] / HIT_BINS] = my_t[k];
             __syncthreads();
             for (uint32_t b0 = wib * GPW; b0 < nblk; b0 += HIT_WAVES * GPW) {
@@ -524,6 +563,7 @@ __global__ __launch_bounds__(HIT_THREADS, HIT_WAVES_PER_SIMD) void k_hit(hit_slo
             }
         }
     }
+    }
     if (qn) {
         __builtin_amdgcn_wave_barrier();
         const uint2 it = queue[l];
@@ -541,121 +581,9 @@ __global__ __launch_bounds__(HIT_THREADS, HIT_WAVES_PER_SIMD) void k_hit(hit_slo
     if (threadIdx.x < 3) {
         uint64_t tot = 0;
         for (uint32_t w = 0; w < HIT_WAVES; ++w) tot += s_red[threadIdx.x][w];
-        hs.part[3 * blockIdx.x + threadIdx.x] = tot;
+        uint64_t *const part = &hs.part[3 * blockIdx.x + threadIdx.x];
+        *part = tot + (FUSED && blockIdx.x < fu.parts ? *part : 0u);
     }
-}
-
-// Final tests of the level-1 pairs that the level-2 pairs and the level-1
-// pass masks describe (the fused last level: the level-1 pairs are never
-// stored).  Level-2 pair q keeps child j (leaf first(q) + j, first = node * F
-// or the build's record) when bit q * nf + j of `mask` is set (nf: F rounded
-// up to a power of two), the layout the level count writes.  A wave takes
-// runs of 64 level-2 pairs: each lane reads one pair, its pass bits and its
-// triangle into the wave's LDS records, the run's (pair, child) items are
-// listed in LDS in (pair, child) order -- the order of the level-1 pairs the
-// emit would have written -- and tested 64 / G items at a time as k_hit
-// tests pairs, up to MASKED_ITEMS items per round.
-// (240 items keep a 256-thread block under 20 KiB of LDS: eight blocks per
-// compute unit, the one round of blocks the launch assumes)
-constexpr uint32_t MASKED_ITEMS = 240;
-template <bool BATCH>
-__global__ __launch_bounds__(256) void k_hit_masked(const float4 *__restrict__ RO, const float4 *__restrict__ RD,
-                                                    const float4 *__restrict__ tri,
-                                                    const uint32_t *__restrict__ ptri2,
-                                                    const uint32_t *__restrict__ pnode2, uint64_t cap2,
-                                                    const uint32_t *__restrict__ mask, uint32_t nf, uint32_t F,
-                                                    uint32_t B, uint32_t log2G, unsigned long long *keys,
-                                                    crsh_meta *meta, uint32_t slot_cap, uint32_t m, batch_dev bd,
-                                                    float t_min)
-{
-    __shared__ uint64_t s_red[3][256 / WAVE];
-    __shared__ float4 s_rec[256 / WAVE][3][WAVE];           // [wave][record word][pair of the run]
-    __shared__ uint2 s_item[256 / WAVE][MASKED_ITEMS];     // [wave][item]: pair of the run, leaf
-    const uint32_t ns = BATCH ? batch_slots(meta, B, slot_cap) : min(meta->n_rays, slot_cap);
-    uint64_t n2 = meta->n_levels >= 2 ? meta->pairs[1] : 0;
-    n2 = n2 < cap2 ? n2 : cap2;
-    const uint32_t n1 = meta->level_cnt[0];
-    const uint32_t off2 = meta->level_off[1];
-    const uint32_t np2 = meta->level_cnt[1];
-    const uint32_t l = lane_id();
-    const uint32_t G = 1u << log2G;
-    const uint32_t slot = l >> log2G;        // item of this lane within a step
-    const uint32_t j = l & (G - 1);          // ray of the leaf
-    const uint32_t per_wave = WAVE >> log2G;
-    const uint32_t wib = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-    const uint64_t wave = (uint64_t)blockIdx.x * (blockDim.x / WAVE) + wib;
-    const uint64_t nwaves = (uint64_t)gridDim.x * (blockDim.x / WAVE);
-    const __amdgpu_buffer_rsrc_t org_r = make_rsrc(RO, (uint64_t)ns * 16u);
-    const __amdgpu_buffer_rsrc_t dir_r = make_rsrc(RD, (uint64_t)ns * 16u);
-    const __amdgpu_buffer_rsrc_t tris_r = make_rsrc(tri, (uint64_t)m * 48u);
-    const uint32_t nfm = nf >= 32 ? ~0u : (1u << nf) - 1u;
-    float4(*rec)[WAVE] = s_rec[wib];
-    uint2 *items = s_item[wib];
-    uint64_t tests = 0, upass = 0, uvpass = 0;   // wave-wide counts
-    for (uint64_t c0 = wave * WAVE; c0 < n2; c0 += nwaves * WAVE) {
-        const uint32_t cn = __builtin_amdgcn_readfirstlane((uint32_t)min(n2 - c0, (uint64_t)WAVE));
-        uint32_t my_t = 0u, bits = 0u, first = 0u;
-        float my_tmin = t_min;                    // batched form: the pair's frame's
-        if (l < cn) {
-            const uint64_t q = c0 + l;
-            my_t = ptri2[q];
-            const uint32_t node = pnode2[q];
-            const uint64_t bit = q * nf;          // nf divides 32: the bits lie in one word
-            bits = (mask[bit >> 5] >> (uint32_t)(bit & 31u)) & nfm;
-            if constexpr (BATCH) {
-                first = node < np2 ? bd.node_first[off2 + node] : 0u;
-                const uint32_t f = node < np2 ? bd.node_info[off2 + node] >> INFO_FRAME_SHIFT : bd.n_frames;
-                my_tmin = f < bd.n_frames ? bd.frames[f].t_min : 0.0f;
-                if (node >= np2) bits = 0u;
-            } else {
-                first = node * F;
-            }
-            if (my_t >= m) bits = 0u;
-        }
-        const uint32_t tb = bits ? my_t * 48u : 0u;
-        const float4 ta = buf_load4(tris_r, tb);
-        const float4 tbv = buf_load4(tris_r, tb + 16u);
-        const float tc = buf_load1(tris_r, tb + 32u);
-        const uint32_t cnt = (uint32_t)__popc(bits);
-        const uint32_t incl = wave_incl_scan(cnt);
-        const uint32_t excl = incl - cnt;
-        const uint32_t total = __builtin_amdgcn_readlane(incl, WAVE - 1);
-        __builtin_amdgcn_wave_barrier();          // the previous run's reads come first
-        rec[0][l] = ta;
-        rec[1][l] = tbv;
-        rec[2][l] = make_float4(tc, __uint_as_float(my_t), my_tmin, 0.0f);
-        for (uint32_t rb = 0; rb < total; rb += MASKED_ITEMS) {
-            // this round's items: the lane's (pair, child) items with index
-            // in [rb, rb + MASKED_ITEMS), in (pair, child) order
-            __builtin_amdgcn_wave_barrier();      // the previous round's reads come first
-            // an item holds the pair's lane and the leaf's ray count (bits 8
-            // and up), and the byte offset of the leaf's first ray slot (slots
-            // below 2^27: 32-bit arithmetic)
-            uint32_t bl = bits, idx = excl;
-            while (bl) {
-                const uint32_t leaf = first + (uint32_t)__builtin_ctz(bl);
-                bl &= bl - 1u;
-                const uint32_t fs = leaf * B;
-                const uint32_t rc = leaf < n1 && fs < ns ? min(B, ns - fs) : 0u;
-                if (idx - rb < MASKED_ITEMS) items[idx - rb] = make_uint2(l | (rc << 8), rc ? fs * 16u : 0u);
-                ++idx;
-            }
-            __builtin_amdgcn_wave_barrier();
-            const uint32_t nit = min(MASKED_ITEMS, total - rb);
-            for (uint32_t k = 0; k < nit; k += per_wave) {
-                const uint32_t src = k + slot;
-                const uint2 it = items[src < nit ? src : 0u];
-                const uint32_t p = it.x & 63u;
-                const float4 a = rec[0][p];
-                const float4 b = rec[1][p];
-                const float4 c = rec[2][p];
-                const uint32_t cnt = src < nit ? it.x >> 8 : 0u;
-                hit_step<BATCH, true>(org_r, dir_r, a, b, c.x, __float_as_uint(c.y), it.y, c.z,
-                                      ballot(j < cnt), j, keys, tests, upass, uvpass);
-            }
-        }
-    }
-    hit_counts<256 / WAVE>(s_red, wib, l, tests, upass, uvpass, meta);
 }
 
 struct hit_out {
@@ -765,44 +693,39 @@ void hit_pack_launch(const crsh_scene *scene, const hit_tris_ws &tri, const crsh
                                                  batch_dev{}, hs);
 }
 
-template <int LG>
-static uint32_t k_hit_launch(const hit_slots_ws &hs, const hit_tris_ws &tri, const crsh_pairs *level1, uint32_t B,
-                         crsh_hits *hits, crsh_meta *meta, uint32_t m, uint32_t tri_base, const batch_dev *bd,
-                         float t_min, uint32_t chunk, bool packed, hipStream_t stream)
+template <int LG, int IN>
+static uint32_t k_hit_launch(const hit_slots_ws &hs, const hit_tris_ws &tri, const crsh_pairs *pairs, uint32_t B,
+                             crsh_hits *hits, crsh_meta *meta, uint32_t m, uint32_t tri_base, const batch_dev *bd,
+                             float t_min, uint32_t chunk, const fused_in &fu, hipStream_t stream)
 {
     // one round of resident workgroups, at most one per smallest chunk
-    const uint64_t want = std::max<uint64_t>((level1->capacity + HIT_MIN_CHUNK - 1) / HIT_MIN_CHUNK, 1);
+    const uint64_t want = std::min<uint64_t>(
+        std::max<uint64_t>((pairs->capacity + HIT_MIN_CHUNK - 1) / HIT_MIN_CHUNK, 1), HIT_MAX_GRID);
     uint32_t g;
-    if (bd) {
-        g = resident_grid((const void *)k_hit<LG, true, false>, HIT_THREADS, std::min<uint64_t>(want, HIT_MAX_GRID));
-        k_hit<LG, true, false><<<g, HIT_THREADS, 0, stream>>>(hs, tri.tri, tri.ftri, level1->tri, level1->node,
-                                                              level1->capacity, B, hs.keys, meta, m, 0u, *bd, 0.0f,
-                                                              chunk);
-    } else if (packed) {
-        g = resident_grid((const void *)k_hit<LG, false, true>, HIT_THREADS, std::min<uint64_t>(want, HIT_MAX_GRID));
-        k_hit<LG, false, true><<<g, HIT_THREADS, 0, stream>>>(hs, tri.tri, tri.ftri, level1->tri, nullptr,
-                                                              level1->capacity, B, hits->tkey, meta, m, tri_base,
-                                                              batch_dev{}, t_min, chunk);
-    } else {
-        g = resident_grid((const void *)k_hit<LG, false, false>, HIT_THREADS, std::min<uint64_t>(want, HIT_MAX_GRID));
-        k_hit<LG, false, false><<<g, HIT_THREADS, 0, stream>>>(hs, tri.tri, tri.ftri, level1->tri, level1->node,
-                                                               level1->capacity, B, hits->tkey, meta, m, 0u,
-                                                               batch_dev{}, t_min, chunk);
+    if constexpr (IN != HIT_PACKED) {
+        if (bd) {
+            g = resident_grid((const void *)k_hit<LG, true, IN>, HIT_THREADS, want);
+            k_hit<LG, true, IN><<<g, HIT_THREADS, 0, stream>>>(hs, tri.tri, tri.ftri, pairs->tri, pairs->node,
+                                                               pairs->capacity, B, hs.keys, meta, m, 0u, *bd, 0.0f,
+                                                               chunk, fu);
+            return g;
+        }
     }
+    g = resident_grid((const void *)k_hit<LG, false, IN>, HIT_THREADS, want);
+    k_hit<LG, false, IN><<<g, HIT_THREADS, 0, stream>>>(hs, tri.tri, tri.ftri, pairs->tri, pairs->node,
+                                                        pairs->capacity, B, hits->tkey, meta, m, tri_base,
+                                                        batch_dev{}, t_min, chunk, fu);
     return g;
 }
 
-uint32_t hit_pairs_launch(const hit_tris_ws &tri, const hit_slots_ws &hs,
-                      const crsh_pairs *level1, int32_t bundle, const crsh_scene *scene, float t_min,
-                      crsh_hits *hits, crsh_meta *meta, const batch_dev *bd, int32_t hit_block, hipStream_t stream,
-                      bool packed, uint32_t tri_base)
+template <int IN>
+static uint32_t k_hit_launch(const hit_slots_ws &hs, const hit_tris_ws &tri, const crsh_pairs *pairs, uint32_t B,
+                             crsh_hits *hits, crsh_meta *meta, uint32_t m, uint32_t tri_base, const batch_dev *bd,
+                             float t_min, uint32_t chunk, const fused_in &fu, hipStream_t stream)
 {
-    if (!level1->capacity) return 0u;
-    const uint32_t B = (uint32_t)bundle;
-    const uint32_t chunk = (uint32_t)hit_block * (HIT_CHUNK / 256u);
     prof_scope ps("k_hit", stream);
 #define CRSH_HIT(LG) \
-    return k_hit_launch<LG>(hs, tri, level1, B, hits, meta, scene->m, tri_base, bd, t_min, chunk, packed, stream)
+    return k_hit_launch<LG, IN>(hs, tri, pairs, B, hits, meta, m, tri_base, bd, t_min, chunk, fu, stream)
     if (B <= 4)
         CRSH_HIT(2);
     else if (B <= 8)
@@ -814,28 +737,32 @@ uint32_t hit_pairs_launch(const hit_tris_ws &tri, const hit_slots_ws &hs,
 #undef CRSH_HIT
 }
 
-void hit_masked_launch(const crsh_rays *sorted, const float4 *tri, const hit_slots_ws &hs, const crsh_pairs *level2,
-                       const uint32_t *mask, int32_t merge, int32_t bundle, const crsh_scene *scene, float t_min,
-                       crsh_hits *hits, crsh_meta *meta, const batch_dev *bd, int32_t hit_block, hipStream_t stream)
+uint32_t hit_pairs_launch(const hit_tris_ws &tri, const hit_slots_ws &hs,
+                      const crsh_pairs *level1, int32_t bundle, const crsh_scene *scene, float t_min,
+                      crsh_hits *hits, crsh_meta *meta, const batch_dev *bd, int32_t hit_block, hipStream_t stream,
+                      bool packed, uint32_t tri_base)
 {
-    (void)sorted;
+    if (!level1->capacity) return 0u;
+    const uint32_t chunk = (uint32_t)hit_block * (HIT_CHUNK / 256u);
+    return packed ? k_hit_launch<HIT_PACKED>(hs, tri, level1, (uint32_t)bundle, hits, meta, scene->m, tri_base, bd,
+                                             t_min, chunk, fused_in{}, stream)
+                  : k_hit_launch<HIT_STORED>(hs, tri, level1, (uint32_t)bundle, hits, meta, scene->m, tri_base, bd,
+                                             t_min, chunk, fused_in{}, stream);
+}
+
+// level-2 pairs with the pass bits of their children; `parts` workgroups of
+// the launch before keep their counts.  Returns the workgroups that have counts.
+uint32_t hit_masked_launch(const hit_tris_ws &tri, const hit_slots_ws &hs, const crsh_pairs *level2,
+                           const uint32_t *mask, int32_t merge, int32_t bundle, const crsh_scene *scene, float t_min,
+                           crsh_hits *hits, crsh_meta *meta, const batch_dev *bd, int32_t hit_block, uint32_t parts,
+                           hipStream_t stream)
+{
     uint32_t nf = 2;
     while (nf < (uint32_t)merge) nf *= 2;
-    uint32_t log2G = 0;
-    while ((1u << log2G) < (uint32_t)bundle) ++log2G;
-    const uint32_t grid = 2048u * 256u / (uint32_t)hit_block;
-    const batch_dev b = bd ? *bd : batch_dev{};
-    prof_scope ps("k_hit", stream);
-    if (bd)
-        k_hit_masked<true><<<grid, hit_block, 0, stream>>>(hs.org, hs.dir, tri, level2->tri, level2->node,
-                                                           level2->capacity, mask, nf, (uint32_t)merge,
-                                                           (uint32_t)bundle, log2G, hs.keys, meta, hs.slots,
-                                                           scene->m, b, 0.0f);
-    else
-        k_hit_masked<false><<<grid, hit_block, 0, stream>>>(hs.org, hs.dir, tri, level2->tri, level2->node,
-                                                            level2->capacity, mask, nf, (uint32_t)merge,
-                                                            (uint32_t)bundle, log2G, hits->tkey, meta, hs.slots,
-                                                            scene->m, b, t_min);
+    const uint32_t chunk = (uint32_t)hit_block * HIT_FUSED_PPT;
+    const uint32_t g = k_hit_launch<HIT_FUSED>(hs, tri, level2, (uint32_t)bundle, hits, meta, scene->m, 0u, bd, t_min,
+                                               chunk, fused_in{mask, nf, (uint32_t)merge, parts}, stream);
+    return std::max(g, parts);
 }
 
 void hit_final_launch(const crsh_rays *sorted, const uint32_t *sorted_ids, const float4 *tri,

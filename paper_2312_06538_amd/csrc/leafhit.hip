@@ -6,8 +6,7 @@
 // count pass of the traversal runs on the level-2 pairs (its pass bits, one
 // per (parent pair, child), land in the workspace) and the final-test kernel
 // reads the level-2 pairs with their pass bits instead of level-1 pairs,
-// listing each run's (pair, child) items in LDS: the level-1 pairs are never
-// stored, and neither the scan nor the emit of level 1 runs.  The counters
+// binning the children by leaf in LDS: the level-1 pairs are never stored, and neither the scan nor the emit of level 1 runs.  The counters
 // are those of the stage order (level-1 node tests, level-1 pairs formed,
 // ray-triangle tests and how far they got) and so are the closest hits (the
 // same tests, the same minimum).  Level-1 pairs that a top-level pass wrote (a
@@ -125,9 +124,9 @@ crsh_status leaf_hit_launch(const crsh_rays *sorted, const uint32_t *sorted_ids,
     const uint32_t gs = (uint32_t)std::max<uint64_t>(std::min<uint64_t>((lh_tiles(level2->capacity) + 255) / 256,
                                                                         1024), 1);
     k_lh_survivors<<<gs, 256, 0, stream>>>(L.S, meta, level2->capacity);
-    hit_masked_launch(sorted, L.tri.tri, L.hs, level2, L.S.bits, merge, bundle, scene, t_min, hits, meta, bd,
-                      hit_block, stream);
-    hit_final_launch(sorted, sorted_ids, L.tri.tri, L.hs, bundle, scene, t_min, hits, meta, bd, parts, stream);
+    const uint32_t all = hit_masked_launch(L.tri, L.hs, level2, L.S.bits, merge, bundle, scene, t_min, hits, meta, bd,
+                                           hit_block, parts, stream);
+    hit_final_launch(sorted, sorted_ids, L.tri.tri, L.hs, bundle, scene, t_min, hits, meta, bd, all, stream);
     return hip_check(hipGetLastError(), "crsh_leaf_hit launch");
 }
 
