@@ -1091,12 +1091,14 @@ __global__ __launch_bounds__(STEP_THREADS, NF == 16 ? 4 : 6) void k_level_step(i
 // the pair count of the output level.  Tiles take their index from an atomic
 // counter in launch order, so every tile waited on in the look-back has
 // started and publishes its sum without waiting: the look-back always ends.
-// There are few tiles (SCAN_TILE items each).
+// There are few tiles (SCAN_TILE items each); a grid for every tile that the
+// storage could hold would be thousands of blocks with nothing to do.
 // A batch's top-level pass (batch_top = its level, 1-based) scans bd_top[0]
 // items and appends after the bd_top[1] pairs already on that level.
 // Level scans clear the counts they read (the next step adds into them), and
-// the first tile adds the workgroups' sums of the launch before to meta:
-// three counts of the top-level count, or node tests.
+// one more block adds the workgroups' sums of the launch before to meta:
+// three counts of the top-level count, or node tests.  A chain of latencies
+// (ticket, counts, look-back) bounds it: 16 bytes of counts a thread.
 __global__ __launch_bounds__(SCAN_THREADS) void k_scan_items(int32_t parent_level, uint32_t n_mesh, uint32_t tile_pairs,
                                                              pair_levels P, trav_scratch S, crsh_meta *meta,
                                                              uint32_t batch_top, const uint64_t *bd_top,
@@ -1104,7 +1106,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_items(int32_t parent_leve
 {
     __shared__ uint32_t s_tile;
     __shared__ uint64_t s_excl;
-    __shared__ uint64_t s_scan[SCAN_THREADS / WAVE];
+    __shared__ uint64_t s_scan[3][SCAN_THREADS / WAVE];
     const uint32_t nl = meta->n_levels;
     if (nl == 0) return;
     if (batch_top > nl) return;
@@ -1114,69 +1116,90 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_items(int32_t parent_leve
     const uint64_t base = batch_top ? bd_top[1] : 0u;
     const uint32_t out_level = batch_top ? batch_top - 1 : (top ? nl - 1 : (uint32_t)parent_level - 2);
     const uint64_t ntiles = (n + SCAN_TILE - 1) / SCAN_TILE;
-    if (blockIdx.x >= ntiles) return;       // only ntiles blocks take a tile
-    if (threadIdx.x == 0) s_tile = atomicAdd(S.scan_ctr, 1u);
-    __syncthreads();
-    const uint32_t tile = s_tile;
-    if (tile >= ntiles) return;
-    uint32_t *const cnt = top ? S.cnt_top : S.cnt;
-    const uint64_t first = (uint64_t)tile * SCAN_TILE + (uint64_t)threadIdx.x * SCAN_ITEMS;
-    uint64_t v[SCAN_ITEMS];
-    uint64_t sum = 0;
-#pragma unroll
-    for (uint32_t k = 0; k < SCAN_ITEMS; ++k) {
-        v[k] = first + k < n ? cnt[first + k] : 0u;
-        sum += v[k];
-    }
-    uint64_t total;
-    const uint64_t ex = block_excl_scan<uint64_t, SCAN_THREADS / WAVE>(sum, s_scan, total);
-    if (threadIdx.x < WAVE) {
-        const uint64_t e = lookback_wave(S.scan_flags, tile, total);
-        if (threadIdx.x == 0) s_excl = e;
-    }
-    __syncthreads();
-    uint64_t run = s_excl + ex;
-#pragma unroll
-    for (uint32_t k = 0; k < SCAN_ITEMS; ++k) {
-        if (first + k < n) {
-            S.off[first + k] = base + run;
-            if (!top) cnt[first + k] = 0u;
-        }
-        run += v[k];
-    }
-    if (tile == ntiles - 1 && threadIdx.x == SCAN_THREADS - 1) {
-        meta->pairs[out_level] = base + run;
-        atomicAdd((unsigned long long *)&meta->hits[out_level], (unsigned long long)run);
-        if (base + run > P.p[out_level].cap) atomicOr(&meta->status, CRSH_OVERFLOW_PAIRS);
-    }
-    if (tile != 0) return;
-    // the launch before's workgroup sums (three for the top-level count)
-    const uint32_t kinds = top ? 3u : 1u;
-    for (uint32_t k = 0; k < kinds; ++k) {
-        uint64_t c = 0;
+    // the last block: the launch before's workgroup sums (three for the
+    // top-level count)
+    if (blockIdx.x == gridDim.x - 1) {
+        if (n == 0) return;                 // the sums are of a level further down
+        uint64_t c[3] = {0, 0, 0};
         for (uint32_t i = threadIdx.x; i < blocks; i += SCAN_THREADS) {
             if (top) {
-                c += S.top_part[3 * i + k];
+                for (uint32_t k = 0; k < 3; ++k) c[k] += S.top_part[3 * i + k];
             } else {
-                c += S.part[i];
+                c[0] += S.part[i];
                 S.part[i] = 0u;
             }
         }
-        c = wave_sum(c);
-        __syncthreads();
-        if (lane_id() == 0) s_scan[threadIdx.x / WAVE] = c;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            c = s_scan[0] + s_scan[1] + s_scan[2] + s_scan[3];
-            if (!top)
-                meta->tests[out_level] += c;
-            else if (k == 0)
-                meta->tests[out_level] += c;
-            else if (k == 1)
-                meta->mesh_hits += c;
-            else
-                meta->mesh_tests += c;
+        const uint32_t kinds = top ? 3u : 1u;
+        for (uint32_t k = 0; k < kinds; ++k) {
+            c[k] = wave_sum(c[k]);
+            if (lane_id() == 0) s_scan[k][threadIdx.x / WAVE] = c[k];
         }
+        __syncthreads();
+        if (threadIdx.x < kinds) {
+            uint64_t t = 0;
+            for (uint32_t w = 0; w < SCAN_THREADS / WAVE; ++w) t += s_scan[threadIdx.x][w];
+            uint64_t *const dst = threadIdx.x == 0 ? &meta->tests[out_level]
+                                : threadIdx.x == 1 ? &meta->mesh_hits : &meta->mesh_tests;
+            *dst += t;
+        }
+        return;
+    }
+    if (blockIdx.x >= ntiles) return;       // only ntiles blocks take a tile
+    uint32_t *const cnt = top ? S.cnt_top : S.cnt;
+    for (;;) {
+        uint32_t tile = 0;
+        if (ntiles > 1) {
+            if (threadIdx.x == 0) s_tile = atomicAdd(S.scan_ctr, 1u);
+            __syncthreads();
+            tile = s_tile;
+            if (tile >= ntiles) return;
+        }
+        const uint64_t first = (uint64_t)tile * SCAN_TILE + (uint64_t)threadIdx.x * SCAN_ITEMS;
+        static_assert(SCAN_ITEMS == 4, "16 bytes of counts per thread");
+        uint32_t v[SCAN_ITEMS] = {0u, 0u, 0u, 0u};
+        const bool whole = first + SCAN_ITEMS <= n;
+        if (whole) {
+            const uint4 x = *(const uint4 *)(cnt + first);
+            v[0] = x.x, v[1] = x.y, v[2] = x.z, v[3] = x.w;
+        } else {
+#pragma unroll
+            for (uint32_t k = 0; k < SCAN_ITEMS; ++k)
+                if (first + k < n) v[k] = cnt[first + k];
+        }
+        const uint64_t sum = ((uint64_t)v[0] + v[1]) + ((uint64_t)v[2] + v[3]);
+        uint64_t total;
+        const uint64_t ex = block_excl_scan<uint64_t, SCAN_THREADS / WAVE>(sum, s_scan[0], total);
+        if (ntiles > 1) {
+            if (threadIdx.x < WAVE) {
+                const uint64_t e = lookback_wave(S.scan_flags, tile, total);
+                if (threadIdx.x == 0) s_excl = e;
+            }
+            __syncthreads();
+        }
+        uint64_t run = base + ex + (ntiles > 1 ? s_excl : 0u);
+        if (tile == ntiles - 1 && threadIdx.x == SCAN_THREADS - 1) {
+            const uint64_t end = run + sum;
+            meta->pairs[out_level] = end;
+            atomicAdd((unsigned long long *)&meta->hits[out_level], (unsigned long long)(end - base));
+            if (end > P.p[out_level].cap) atomicOr(&meta->status, CRSH_OVERFLOW_PAIRS);
+        }
+        if (whole) {
+            const uint64_t o1 = run + v[0], o2 = o1 + v[1], o3 = o2 + v[2];
+            typedef uint64_t v2 __attribute__((ext_vector_type(2)));
+            *(v2 *)(S.off + first) = v2{run, o1};
+            *(v2 *)(S.off + first + 2) = v2{o2, o3};
+            if (!top) *(uint4 *)(cnt + first) = make_uint4(0u, 0u, 0u, 0u);
+        } else {
+#pragma unroll
+            for (uint32_t k = 0; k < SCAN_ITEMS; ++k) {
+                if (first + k < n) {
+                    S.off[first + k] = run;
+                    if (!top) cnt[first + k] = 0u;
+                }
+                run += v[k];
+            }
+        }
+        if (ntiles == 1) return;
     }
 }
 
@@ -1378,7 +1401,7 @@ static crsh_status traverse_run(const crsh_nodes *nodes, const crsh_scene *scene
     const batch_dev b = bd ? *bd : batch_dev{};
     trav_prep_launch(scene, tri_begin, tri_end, tsph, nodes, meta, na, nb, ns, S, max_pairs / tile_pairs + 1,
                      (uint32_t)levels, stream);
-    const uint32_t scan_grid = (uint32_t)std::min<uint64_t>((items + SCAN_TILE - 1) / SCAN_TILE, 1u << 20);
+    const uint32_t scan_grid = (uint32_t)std::min<uint64_t>((items + SCAN_TILE - 1) / SCAN_TILE, SCAN_GRID);
     // one wave per top-level item, for the items that a hierarchy with as many
     // levels as there is storage for has (more items loop)
     uint64_t top_est = top_items;
@@ -1412,7 +1435,7 @@ static crsh_status traverse_run(const crsh_nodes *nodes, const crsh_scene *scene
                                                                  scene->mesh_count, scene->msph, scene->n_mesh,
                                                                  tri_begin, tri_end, P, S, meta, b, L);
         }
-        k_scan_items<<<scan_grid, SCAN_THREADS, 0, stream>>>(0, scene->n_mesh, tile_pairs, P, S, meta, L, b.top,
+        k_scan_items<<<scan_grid + 1, SCAN_THREADS, 0, stream>>>(0, scene->n_mesh, tile_pairs, P, S, meta, L, b.top,
                                                              top_grid);
         prof_scope ps("k_top_emit", stream);
 #define CRSH_TOP(NF, BT, PK)                                                                                      \
@@ -1439,7 +1462,7 @@ static crsh_status traverse_run(const crsh_nodes *nodes, const crsh_scene *scene
     const uint32_t top_levels = (uint32_t)(bd ? batch_levels : levels);
     uint32_t parts = top_grid;               // workgroups that may have left a sum of node tests
     auto level_step_launch = [&](int L) {
-        k_scan_items<<<scan_grid, SCAN_THREADS, 0, stream>>>(L, scene->n_mesh, tile_pairs, P, S, meta, 0, nullptr,
+        k_scan_items<<<scan_grid + 1, SCAN_THREADS, 0, stream>>>(L, scene->n_mesh, tile_pairs, P, S, meta, 0, nullptr,
                                                              parts);
         const uint64_t want = std::max<uint64_t>((P.p[L - 1].cap + tile_pairs - 1) / tile_pairs, 1);
         const bool test = L - 1 > lowest;

@@ -64,8 +64,9 @@ struct trav_scratch {
     uint64_t *top_part;    // three counts per workgroup of the top-level count
 };
 
-constexpr uint32_t SCAN_THREADS = 256;
-constexpr uint32_t SCAN_ITEMS = 16;
+constexpr uint32_t SCAN_THREADS = 1024;
+constexpr uint32_t SCAN_ITEMS = 4;
+constexpr uint32_t SCAN_GRID = 128;        // most blocks of a scan
 constexpr uint32_t SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;
 static_assert(SCAN_TILE == SCAN_TILE_ITEMS, "workspace sizing");
 
