@@ -19,6 +19,17 @@ def _p(t):
     return t.data_ptr()
 
 
+def _rows(cap, dev):
+    """The seven ray arrays as rows of one tensor, 256-byte aligned."""
+    return torch.empty((len(RAY_KEYS), (cap + 63) // 64 * 64), dtype=torch.float32, device=dev)
+
+
+def _put_columns(rows, first, x, n):
+    """Columns 0 to 2 of x [n, 3] into rows first, first + 1, first + 2."""
+    x[:, 2]     # an error for fewer columns, which would be broadcast below
+    rows[first:first + 3, :n].copy_(x[:, :3].t())
+
+
 class RayScene:
     """An indexed mesh with its mesh ranges, and the hierarchy parameters,
     for closest hits of caller-given rays.  The vertices come with every
@@ -46,13 +57,16 @@ class RayScene:
         dev = torch.device("cuda")
         cap = max(n, 1)
         e = lambda k, dt: torch.empty(max(int(k), 1), dtype=dt, device=dev)
-        self.rays = {k: e(cap, torch.float32) for k in RAY_KEYS}
+        self._rays = _rows(cap, dev)
+        self._rays[6].fill_(float(np.finfo(np.float32).max))     # tmax
+        self.rays = {k: self._rays[i, :cap] for i, k in enumerate(RAY_KEYS)}
         self.srays = {k: e(cap, torch.float32) for k in RAY_KEYS}
         self.keys, self.ids = e(cap, torch.int32), e(cap, torch.int32)
         self.skeys, self.sids = e(cap, torch.int32), e(cap, torch.int32)
         self.node_cap = node_capacity(cap, self.B, self.F, self.levels)
         self.nodes = {k: e(self.node_cap, torch.float32) for k in NODE_KEYS}
         self.meta = torch.zeros(X.ctypes_sizeof_meta(), dtype=torch.uint8, device=dev)
+        self._tkey = e(cap, torch.int64)
         self._cap = cap
         self._alloc_pairs()
 
@@ -78,18 +92,15 @@ class RayScene:
                                 [_p(a) for a in self.v9], s)
         X.crsh_mesh_spheres([_p(a) for a in self.v9], self.m, _p(self.mesh_first), _p(self.mesh_count),
                             self.n_mesh, _p(self.msph), s)
-        for i, k in enumerate(("ox", "oy", "oz")):
-            self.rays[k][:n].copy_(o[:, i])
-        for i, k in enumerate(("dx", "dy", "dz")):
-            self.rays[k][:n].copy_(d[:, i])
-        self.rays["tmax"][:n].fill_(float(np.finfo(np.float32).max))
+        _put_columns(self._rays, 0, o, n)
+        _put_columns(self._rays, 3, d, n)
         c_rays = X.Rays(*[_p(self.rays[k]) for k in RAY_KEYS], None, self._cap)
         c_srays = X.Rays(*[_p(self.srays[k]) for k in RAY_KEYS], None, self._cap)
         c_nodes = X.Nodes(*[_p(self.nodes[k]) for k in NODE_KEYS], self.node_cap)
         scene = X.Scene((X.vp * 9)(*[_p(a) for a in self.v9]), self.m, _p(self.mesh_first), _p(self.mesh_count),
                         _p(self.msph), self.n_mesh)
         dev = verts.device
-        tkey = torch.empty(self._cap, dtype=torch.int64, device=dev)
+        tkey = self._tkey
         tri = torch.empty(self._cap, dtype=torch.int32, device=dev)
         t, u, v = (torch.empty(self._cap, dtype=torch.float32, device=dev) for _ in range(3))
         hits = X.Hits(_p(tkey), _p(tri), _p(t), _p(u), _p(v), self._cap)
@@ -117,17 +128,15 @@ class RayScene:
         else:
             raise X.CrshError(X.ERR_CAPACITY, "pair capacity still too small")
         self.last_meta = m
-        return tri[:n], t[:n], u[:n], v[:n]
+        return (tri, t, u, v) if n == self._cap else (tri[:n], t[:n], u[:n], v[:n])
 
     def backward(self, verts, o, d, tri, t, u, v, g_t, g_u, g_v):
         n = int(o.shape[0])
         dev = verts.device
-        rays = {k: torch.empty(max(n, 1), dtype=torch.float32, device=dev) for k in RAY_KEYS}
-        for i, k in enumerate(("ox", "oy", "oz")):
-            rays[k][:n].copy_(o[:, i])
-        for i, k in enumerate(("dx", "dy", "dz")):
-            rays[k][:n].copy_(d[:, i])
-        c_rays = X.Rays(*[_p(rays[k]) for k in RAY_KEYS], None, max(n, 1))
+        rays = _rows(max(n, 1), dev)
+        _put_columns(rays, 0, o, n)
+        _put_columns(rays, 3, d, n)
+        c_rays = X.Rays(*[_p(rays) + i * rays.stride(0) * 4 for i in range(len(RAY_KEYS))], None, max(n, 1))
         tri, t, u, v = (x.contiguous() for x in (tri, t, u, v))
         hits = X.Hits(None, _p(tri), _p(t), _p(u), _p(v), max(n, 1))
         g_verts = torch.zeros_like(verts)
@@ -150,7 +159,8 @@ class ClosestHit(torch.autograd.Function):
         o = o.contiguous()
         d = d.contiguous()
         tri, t, u, v = scene.closest_hit(verts, o, d)
-        tri, t, u, v = tri.clone(), t.clone(), u.clone(), v.clone()
+        # parts of longer arrays are copied; whole ones are this call's own
+        tri, t, u, v = (x if x.untyped_storage().nbytes() == x.nbytes else x.clone() for x in (tri, t, u, v))
         ctx.scene = scene
         ctx.save_for_backward(verts, o, d, tri, t, u, v)
         ctx.mark_non_differentiable(tri)

@@ -8,6 +8,8 @@
 
 #include "common.hpp"
 
+#include <vector>
+
 namespace crsh {
 
 static thread_local char g_err[512] = "";
@@ -50,16 +52,29 @@ void prof_end(bool armed, hipStream_t s)
     g_prof.armed = false;
 }
 
+// A constant of the device and the kernel, asked for once per thread: the
+// query takes longer than a launch.
+uint32_t resident_blocks(const void *f, int threads)
+{
+    struct known {
+        int dev, threads;
+        const void *f;
+        uint32_t blocks;
+    };
+    static thread_local std::vector<known> seen;
+    int dev = 0, cus = 0, per_cu = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    for (const known &k : seen)
+        if (k.dev == dev && k.f == f && k.threads == threads) return k.blocks;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, threads, 0) != hipSuccess || per_cu <= 0) return 0;
+    seen.push_back({dev, threads, f, (uint32_t)cus * (uint32_t)per_cu});
+    return seen.back().blocks;
+}
+
 uint32_t resident_grid(const void *f, int threads, uint64_t want)
 {
-    int dev = 0, cus = 0, per_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 1;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-        return 1;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, threads, 0) != hipSuccess || per_cu <= 0)
-        per_cu = 1;
-    uint64_t g = (uint64_t)per_cu * (uint64_t)cus;
-    if (want < g) g = want;
+    const uint64_t g = std::min<uint64_t>(std::max(resident_blocks(f, threads), 1u), want);
     return g ? (uint32_t)g : 1u;
 }
 

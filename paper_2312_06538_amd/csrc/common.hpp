@@ -379,6 +379,10 @@ crsh_status hip_check(hipError_t e, const char *what);
 // Largest grid of `threads`-thread blocks of kernel f that the current device
 // keeps resident at once (occupancy x compute units), capped at `want`.
 uint32_t resident_grid(const void *f, int threads, uint64_t want);
+// Blocks of a persistent grid-stride kernel that fit the device at once.  Its
+// blocks get equal shares of the tiles, so they finish in rounds of this many;
+// a grid of whole rounds leaves no round partly empty.  0 if unknown.
+uint32_t resident_blocks(const void *f, int threads);
 
 // One-shot kernel timer (crsh_profile_next): prof_begin returns true when
 // this launch is the armed one and has recorded the start event.

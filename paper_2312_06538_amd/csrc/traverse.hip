@@ -1249,21 +1249,6 @@ void trav_prep_launch(const crsh_scene *scene, uint32_t tri_begin, uint32_t tri_
     k_trav_prep<<<g, 256, 0, stream>>>(V, tri_begin, tri_end, tsph, nd, meta, na, nb, ns, S, n_cnt, levels);
 }
 
-// Blocks of a persistent grid-stride kernel that fit the device at once.  Its
-// blocks get equal shares of the tiles, so they finish in rounds of this many;
-// a grid of whole rounds leaves no round partly empty.  0 if unknown.
-template <typename K>
-static uint32_t resident_blocks(K kernel, uint32_t threads)
-{
-    int dev = 0, cus = 0, per_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, (int)threads, 0) != hipSuccess || cus < 1 ||
-        per_cu < 1)
-        return 0;
-    return (uint32_t)cus * (uint32_t)per_cu;
-}
-
 void level_count_launch(int32_t parent_level, int32_t merge, const float4 *na, const float4 *nb, const float *ns,
                         const float4 *tsph, uint32_t m, const pair_levels &P, const trav_scratch &S, crsh_meta *meta,
                         const batch_dev *bd, uint64_t tiles_cap, uint32_t top_levels, hipStream_t stream)
@@ -1283,7 +1268,7 @@ void level_count_launch(int32_t parent_level, int32_t merge, const float4 *na, c
     // per step of COUNT_TPS tiles)
 #define CRSH_COUNT_ONE(NF, BT, ST)                                                                           \
     {                                                                                                        \
-        const uint32_t rb = resident_blocks(k_level_count_lanes<NF, BT, ST>, COUNT_THREADS);                 \
+        const uint32_t rb = resident_blocks((const void *)k_level_count_lanes<NF, BT, ST>, COUNT_THREADS);                 \
         const uint64_t want = std::max<uint64_t>((tiles_cap + COUNT_TPS - 1) / COUNT_TPS, 1);                \
         const uint32_t gl = (uint32_t)std::min<uint64_t>(want, rb ? rb : 2048);                              \
         k_level_count_lanes<NF, BT, ST><<<gl, COUNT_THREADS, 0, stream>>>(L, Fu, na, nb, ns, tsph, m, P, S,  \
@@ -1475,7 +1460,7 @@ static crsh_status traverse_run(const crsh_nodes *nodes, const crsh_scene *scene
         prof_scope ps("k_level", stream);
 #define CRSH_STEP(NF, BT, PK, TE, ST)                                                                             \
     {                                                                                                             \
-        const uint32_t rb = resident_blocks(k_level_step<NF, BT, PK, TE, ST>, STEP_THREADS);                      \
+        const uint32_t rb = resident_blocks((const void *)k_level_step<NF, BT, PK, TE, ST>, STEP_THREADS);                      \
         const uint32_t g = (uint32_t)std::min<uint64_t>(want, std::min(rb ? rb : 512u, TRAV_PARTS));              \
         parts = std::max(parts, g);                                                                               \
         k_level_step<NF, BT, PK, TE, ST><<<g, STEP_THREADS, 0, stream>>>(L, Fu, na, nb, ns, tsph, scene->m, P, S, \
