@@ -13,6 +13,7 @@
 //                 ranked in LDS with wave ballots (stable), a decoupled
 //                 look-back across tiles per digit, then a coalesced scatter
 //                 staged through LDS.
+// At most 12,288 keys are one launch of one workgroup (k_sort_one) instead.
 #include "common.hpp"
 
 namespace crsh {
@@ -425,6 +426,109 @@ __global__ __launch_bounds__(THREADS) void k_sort_pass(sort_bufs bufs, const uin
     sort_tile<FRAME, THREADS, ITEMS>(S, kin, vin, kout, vout, offsets, fl, pass, n, tile, frame_of);
 }
 
+// Every pass of at most ONE_THREADS * ONE_ITEMS keys by one workgroup: keys
+// and values stay in registers, ranked as a tile of k_sort_pass is, and change
+// places through LDS.  As launches (8 us a pass, the histogram, its clear and
+// the plan 9 more) such a sort is all latency; as one workgroup it is bound by
+// the ranking's vector instructions, so it pays up to 12,288 keys: whole sorts
+// of 1,024 / 4,096 / 8,192 / 12,288 keys 27 / 31 / 37 / 37 us in launches, 11 /
+// 14 / 23 / 31 so, of 16,384 37 and 42.
+constexpr uint32_t ONE_THREADS = 1024;
+constexpr uint32_t ONE_WAVES = ONE_THREADS / WAVE;
+constexpr uint32_t ONE_ITEMS = 12;                      // most keys per thread
+
+template <uint32_t ITEMS>
+struct one_lds {
+    uint32_t buf[ONE_THREADS * ITEMS];
+    uint32_t wcnt[ONE_WAVES * 256];
+    uint32_t scan[256 / WAVE];
+    uint32_t all_one;                                   // a digit holds every key
+};
+
+// One pass; nothing moves if one digit value holds every key.
+template <bool FRAME, uint32_t ITEMS>
+__device__ __forceinline__ void one_pass(one_lds<ITEMS> &S, uint32_t *key, uint32_t *val, uint32_t n, uint32_t shift,
+                                         const uint32_t *frame_of)
+{
+    const uint32_t w = threadIdx.x / WAVE, l = lane_id(), d = threadIdx.x;
+    const uint32_t base = w * (WAVE * ITEMS);
+    uint32_t slot[ITEMS];
+    for (uint32_t i = d; i < ONE_WAVES * 256; i += ONE_THREADS) S.wcnt[i] = 0u;
+    if (d == 0) S.all_one = 0u;
+    __syncthreads();
+    rank_tile<FRAME, ITEMS>(key, val, base, n, shift, frame_of, S.wcnt, slot);
+    __syncthreads();
+    // thread = digit: its keys per wave, then each wave's first place
+    uint32_t run = 0u;
+    if (d < 256) {
+#pragma unroll
+        for (uint32_t ww = 0; ww < ONE_WAVES; ++ww) {
+            const uint32_t c = S.wcnt[ww * 256 + d];
+            S.wcnt[ww * 256 + d] = run;
+            run += c;
+        }
+        if (run == n) S.all_one = 1u;
+        const uint32_t inc = wave_incl_scan(run);
+        if (l == WAVE - 1) S.scan[w] = inc;
+        run = inc - run;
+    }
+    __syncthreads();
+    if (S.all_one) {
+        __syncthreads();
+        return;
+    }
+    if (d < 256) {
+#pragma unroll
+        for (uint32_t i = 0; i < 256 / WAVE; ++i)
+            if (i < w) run += S.scan[i];
+#pragma unroll
+        for (uint32_t ww = 0; ww < ONE_WAVES; ++ww) S.wcnt[ww * 256 + d] += run;
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t r = 0; r < ITEMS; ++r)
+        if (base + r * WAVE + l < n) {
+            slot[r] = (slot[r] & 0xFFFFu) + S.wcnt[w * 256 + (slot[r] >> 16)];
+            S.buf[slot[r]] = key[r];
+        }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t r = 0; r < ITEMS; ++r) key[r] = S.buf[base + r * WAVE + l];
+    __syncthreads();
+#pragma unroll
+    for (uint32_t r = 0; r < ITEMS; ++r)
+        if (base + r * WAVE + l < n) S.buf[slot[r]] = val[r];
+    __syncthreads();
+#pragma unroll
+    for (uint32_t r = 0; r < ITEMS; ++r) val[r] = S.buf[base + r * WAVE + l];
+}
+
+template <uint32_t ITEMS>
+__global__ __launch_bounds__(ONE_THREADS) void k_sort_one(sort_bufs bufs, const uint32_t *frame_of,
+                                                          const crsh_meta *meta, uint32_t cap)
+{
+    __shared__ one_lds<ITEMS> S;
+    const uint32_t n = min(meta->n_rays, cap);
+    const uint32_t base = threadIdx.x / WAVE * (WAVE * ITEMS) + lane_id();
+    uint32_t key[ITEMS], val[ITEMS];
+#pragma unroll
+    for (uint32_t r = 0; r < ITEMS; ++r) {
+        const uint32_t g = base + r * WAVE;
+        key[r] = g < n ? bufs.kin[g] : 0u;
+        val[r] = g < n ? bufs.vin[g] : 0u;
+    }
+    for (uint32_t p = 0; p < SORT_PASSES; ++p) one_pass<false, ITEMS>(S, key, val, n, 8 * p, nullptr);
+    if (frame_of) one_pass<true, ITEMS>(S, key, val, n, 0, frame_of);
+#pragma unroll
+    for (uint32_t r = 0; r < ITEMS; ++r) {
+        const uint32_t g = base + r * WAVE;
+        if (g < n) {
+            bufs.kout[g] = key[r];
+            bufs.vout[g] = val[r];
+        }
+    }
+}
+
 }  // namespace crsh
 
 using namespace crsh;
@@ -465,6 +569,17 @@ crsh_status sort_launch(const uint32_t *keys_in, const uint32_t *ids_in, const u
     uint32_t *flags = (uint32_t *)w;
     const uint32_t passes = frame_of ? MAX_PASSES : SORT_PASSES;
 
+    sort_bufs b{keys_in, ids_in, keys_out, ids_out, kalt, valt};
+    if (capacity && capacity <= ONE_THREADS * ONE_ITEMS) {
+        prof_scope ps("k_sort_pass", stream);
+        if (capacity <= ONE_THREADS * 4)
+            k_sort_one<4><<<1, ONE_THREADS, 0, stream>>>(b, frame_of, meta, capacity);
+        else if (capacity <= ONE_THREADS * 8)
+            k_sort_one<8><<<1, ONE_THREADS, 0, stream>>>(b, frame_of, meta, capacity);
+        else
+            k_sort_one<ONE_ITEMS><<<1, ONE_THREADS, 0, stream>>>(b, frame_of, meta, capacity);
+        return hip_check(hipGetLastError(), "crsh_sort launch");
+    }
     const bool few = capacity <= FEW;
     k_sort_clear<<<std::min<uint32_t>(MAX_PASSES * tiles_cap, 1024), 256, 0, stream>>>(hist, ctl, flags, meta,
                                                                                        tiles_cap, capacity);
@@ -479,7 +594,6 @@ crsh_status sort_launch(const uint32_t *keys_in, const uint32_t *ids_in, const u
                                                     stream>>>(keys_in, ids_in, frame_of, meta, hist, capacity);
     }
     k_sort_plan<<<1, 256, 0, stream>>>(hist, ctl, meta, capacity, passes);
-    sort_bufs b{keys_in, ids_in, keys_out, ids_out, kalt, valt};
     const uint32_t pass_tile = few ? FEW_THREADS * FEW_ITEMS : PASS_TILE;
     const uint32_t pass_tiles = (capacity + pass_tile - 1) / pass_tile;
     for (uint32_t p = 0; p < passes; ++p) {

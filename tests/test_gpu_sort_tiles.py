@@ -1,5 +1,5 @@
-"""Sort at the edges of its tiles (4,096 keys up to a capacity of 2^18, 8,192
-above) and with passes left out: the stable order of numpy, exactly."""
+"""Sort at the edges of its tiles (one workgroup up to 12,288 keys; 4,096 keys up
+to a capacity of 2^18, 8,192 above) and with passes left out: the stable order of numpy, exactly."""
 import numpy as np
 import pytest
 
@@ -25,6 +25,8 @@ def _keys(kind, n, rng):
 
 @pytest.mark.parametrize("kind", ["all", "one", "top", "middle"])
 @pytest.mark.parametrize("n,cap", [(1, 1), (1023, 1023), (4095, 4096), (4097, 4097), (4097, 1 << 18),
+                                   (64, 4096), (4096, 4096), (8191, 8192), (8193, 8193), (12287, 12288),
+                                   (12288, 12288), (12289, 12289), (0, 12288),
                                    ((1 << 18) - 1, 1 << 18), (1 << 18, 1 << 18), (8193, (1 << 18) + 1),
                                    ((1 << 18) + 1, (1 << 18) + 1), (0, 5000), (0, 1 << 19)])
 def test_sort_tile_edges(kind, n, cap):
@@ -36,3 +38,21 @@ def test_sort_tile_edges(kind, n, cap):
     order = np.argsort(keys, kind="stable")
     assert np.array_equal(gk, keys[order])
     assert np.array_equal(gi, ids[order])
+
+
+def test_small_batch_frame_digit():
+    """A batch of few rays in all: the frame digit too is sorted by the one
+    workgroup; every frame against the oracle."""
+    import dataclasses
+    from conftest import workload
+    from oracle import oracle as O
+    from paper_2312_06538_amd.batch import DeviceBatch
+    wls = [dataclasses.replace(workload("shadow_128", W=w, H=h), B=16, F=4, n=5)
+           for w, h in ((40, 40), (3, 3), (24, 17), (40, 30))]
+    db = DeviceBatch(wls, 16, 4, 5, 256, pair_capacity=1 << 20)
+    assert db.cap <= 12288
+    m = db.run_with_retry()
+    for f, (r, wl) in enumerate(zip(db.frame_results(m, with_pairs=False), wls)):
+        o = O.run_pipeline(wl)
+        assert np.array_equal(r["sorted_ids"], o["sorted_ids"]), f
+        assert np.array_equal(r["hit"][0], o["hits"][0]), f
