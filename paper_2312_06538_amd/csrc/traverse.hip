@@ -816,7 +816,8 @@ __global__ __launch_bounds__(COUNT_THREADS) void k_level_count_lanes(int32_t par
 // a count pass and an emit pass per level, each reading the pair list, took
 // 29.1 ms; 1024x1024 reflections 2.07 ms (2.7), 24 frames of a batch 5.3 (7.4).
 // Requesting a tile's inputs a tile ahead is what pays for the fusion (24 to 28
-// ms without), and 6 waves per SIMD: the compiler's own choice is 4, where only
+// ms without; the next 64 pairs' spheres before these are tested: 21.6 to 21.3
+// in all), and 6 waves per SIMD: the compiler's own choice is 4, where only
 // merge factors above 8 stay (their lists need the LDS of 4).
 template <int NF, bool BATCH, bool PACKED, bool TEST, bool STAGED>
 __global__ __launch_bounds__(STEP_THREADS, NF == 16 ? 4 : 6) void k_level_step(int32_t parent_level, uint32_t F,
@@ -993,19 +994,36 @@ __global__ __launch_bounds__(STEP_THREADS, NF == 16 ? 4 : 6) void k_level_step(i
         const __amdgpu_buffer_rsrc_t ot = make_rsrc(out.tri + base, n_put * 4u);
         const __amdgpu_buffer_rsrc_t on = make_rsrc(PACKED ? out.tri : out.node + base, n_put * 4u);
         const __amdgpu_buffer_rsrc_t om = make_rsrc(mask_out + base, n_put * (uint32_t)sizeof(mask_t));
-        for (uint32_t i0 = w * WAVE; i0 < n_put; i0 += STEP_THREADS) {
-            const uint32_t i = i0 + l;
+        // a written pair: triangle, node and (TEST) sphere; the next 64 are
+        // requested before these are tested
+        struct pair_in {
+            uint32_t tri, node;
+            float4 sp;
+        };
+        auto load_pair = [&](uint32_t i) {
             const uint32_t it = s_item[i < n_put ? i : 0u];
             const uint2 pr = s_par[it >> 4];
-            const uint32_t node = pr.y + (it & 15u);
+            pair_in v;
+            v.tri = pr.x;
+            v.node = pr.y + (it & 15u);
+            if constexpr (TEST) v.sp = tsph[pr.x < m ? pr.x : 0u];
+            return v;
+        };
+        pair_in pn;
+        if (w * WAVE < n_put) pn = load_pair(w * WAVE + l);
+        for (uint32_t i0 = w * WAVE; i0 < n_put; i0 += STEP_THREADS) {
+            const uint32_t i = i0 + l;
+            const pair_in cp = pn;
+            const uint32_t node = cp.node;
+            pn = load_pair(i + STEP_THREADS);
             if constexpr (PACKED) {
-                __builtin_amdgcn_raw_buffer_store_b32(node << CRSH_PACKED_TRI_BITS | (pr.x - out.tri_base), ot, i * 4u, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b32(node << CRSH_PACKED_TRI_BITS | (cp.tri - out.tri_base), ot, i * 4u, 0, 0);
             } else {
-                __builtin_amdgcn_raw_buffer_store_b32(pr.x, ot, i * 4u, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b32(cp.tri, ot, i * 4u, 0, 0);
                 __builtin_amdgcn_raw_buffer_store_b32(node, on, i * 4u, 0, 0);
             }
             if constexpr (TEST) {
-                const float4 sp = tsph[pr.x < m ? pr.x : 0u];
+                const float4 sp = cp.sp;
                 const f3 pc = mk(sp.x, sp.y, sp.z);
                 const uint64_t live = n_put - i0 >= WAVE ? ~0ull : (1ull << (n_put - i0)) - 1ull;
                 const uint32_t pl = node - wlo;
