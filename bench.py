@@ -21,31 +21,29 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-# Peak of the dominant kernel's bound.  The final ray-triangle test is plain
-# float32 VALU arithmetic without fused multiply-add or packed math: one
-# operation per lane per cycle, 64 lanes per CU (4 SIMD x 16), 256 CUs,
-# 2.4 GHz -> 39.3 T operations/s.
+# Peak of the node tests: plain float32 VALU arithmetic without fused
+# multiply-add or packed math: one operation per lane per cycle, 64 lanes per
+# CU (4 SIMD x 16), 256 CUs, 2.4 GHz -> 39.3 T operations/s.
 ALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
-# Algorithmic float32 operations of the Moller-Trumbore test as written
-# (Sec. 3.3.8), with its early exits: every test computes p = D x e2 (9),
-# det = e1 . p (5), checks |det| (1), 1 / det (1), T = O - v0 (3), u (a dot
-# product 5 and the scaling 1) and checks its two bounds (2): 27 operations;
-# a test whose u passes adds q = T x e1 (9), v (6) and its checks (v >= 0,
-# u + v, <= 1: 3): 18 more; a test whose u and v pass adds t (6) and its two
-# bounds (2): 8 more.  The kernels count the tests that pass u and those that
-# pass u and v (crsh_meta.final_u_pass / final_uv_pass).  e1 and e2 are
-# per-triangle precomputation, not per-test work; a test failing the
-# determinant check (a ray parallel to the plane, a vanishing share) is
-# counted as if it reached the u check.
-MT_OPS_ALL, MT_OPS_U, MT_OPS_UV = 27, 18, 8
+# float32 operations of the final tests as k_hit performs them.  Every
+# ray-triangle test goes through the matrix filter: 2 a - det (6 products), det
+# (3) and the threshold (2), 11 multiply-adds, and the 3 operations that compare
+# them: 25.  What the filter cannot reject goes through the Moller-Trumbore
+# test (Sec. 3.3.8), of which only the tests whose u passes are counted (a lower
+# bound): p = D x e2 (9), det (5), its check (1), 1 / det (1), T (3), u (6), its
+# bounds (2), q = T x e1 (9), v (6) and its checks (3): 45 operations; a test
+# whose u and v pass adds t (6) and its two bounds (2).  The kernels count the
+# tests that pass u and those that pass u and v (crsh_meta.final_u_pass /
+# final_uv_pass).
+MT_OPS_ALL, MT_OPS_U, MT_OPS_UV = 25, 45, 8
 # float32 operations of one node-sphere test (Eq. 9) as written: P - C (3),
 # t = (P-C).a (5), (P-C) x a (9), its squared length (5),
 # |t| tan + (d + r) sec (4: two products, two sums), squaring (1),
 # comparison (1), the full-cone check (1).
 NODE_OPS = 29
 HBM_PEAK_GBS = 8000.0
-# MI355X's published float32 vector peak, which counts a fused multiply-add
-# as two operations and packed float32 as two lanes
+# MI355X's published float32 peak, the same for vector and matrix
+# instructions; it counts a multiply-add as two operations: the final tests'
 PUBLISHED_FP32_TFLOPS = 157.3
 
 
@@ -312,20 +310,22 @@ def main():
     torch.cuda.synchronize()
     ev = HipEvents(args.steps)
     # kernels timed on alternate steps: the two heaviest (the final tests and
-    # the level pass that forms level 1, the last k_level launch of a frame)
-    # and the sort and compaction kernels measured against HBM bandwidth (the
-    # second radix pass, the emit that writes level 1)
+    # the level step that tests level 1 while it writes level 2) and the
+    # kernels measured against HBM bandwidth (the second radix pass, the last
+    # level step, which only writes level 1)
     nl = int(m.n_levels)
-    # (fused last level: the first k_hit launch tests the level-1 pairs a
-    # top-level pass stored, none here; the second is the fused one, and no
-    # emit writes level 1)
-    probes = [("k_hit", 1 if fused else 0), ("k_level", max(nl - 2, 0)), ("k_sort_pass", 1)]
-    if not fused:
-        probes.append(("k_level_emit", max(nl - 2, 0)))
+    # k_level launches of a frame: the step from the top level on, one per
+    # level.  (Fused last level: the step that writes level 2 is the last and
+    # tests nothing, the count of level 1 follows; the first k_hit launch tests
+    # the level-1 pairs a top-level pass stored, none here, the second is the
+    # fused one.)
+    at_test, at_emit = (nl - 2, nl - 3) if fused else (nl - 3, nl - 2)
+    probes = [("k_hit", "k_hit", 1 if fused else 0), ("k_sort_pass", "k_sort_pass", 1)]
+    probes += [(label, "k_level", at) for label, at in (("k_level", at_test), ("k_level_emit", at_emit)) if at >= 0]
     t0 = time.perf_counter()
     for k in range(args.steps):
         a, b = ev.pair(k)
-        name, occ = probes[k % len(probes)]
+        _, name, occ = probes[k % len(probes)]
         if not packed:           # packed: one launch per triangle batch, no single kernel to time
             X.crsh_profile_next(name, occ, a, b)
         P.run_frame(fr, bf, packed=packed, leaf_hit=fused)
@@ -348,12 +348,13 @@ def main():
     u_pass, uv_pass = int(m.final_u_pass), int(m.final_uv_pass)
     work = {"k_hit": final * MT_OPS_ALL + u_pass * MT_OPS_U + uv_pass * MT_OPS_UV,
             "k_level": int(m.tests[0]) * NODE_OPS}
+    peak = {"k_hit": PUBLISHED_FP32_TFLOPS, "k_level": ALU_PEAK_TOPS}
     for name in work:
         if durs.get(name):
             avg = sum(durs[name]) / len(durs[name])
             tops = work[name] / (avg * 1e-3) / 1e12
-            kern[name] = {"bound": "alu", "achieved": round(tops, 3), "peak": round(ALU_PEAK_TOPS, 1),
-                          "unit": "TOP/s", "frac": round(tops / ALU_PEAK_TOPS, 4), "traffic": None,
+            kern[name] = {"bound": "alu", "achieved": round(tops, 3), "peak": round(peak[name], 1),
+                          "unit": "TOP/s", "frac": round(tops / peak[name], 4), "traffic": None,
                           "frac_of_published_fp32": round(tops / PUBLISHED_FP32_TFLOPS, 4),
                           "kernel": name, "kernel_ms": round(avg, 4), "ops_per_launch": work[name],
                           "launches_timed": len(durs[name])}
@@ -364,14 +365,15 @@ def main():
                                                                                            else "_" + args.variant))
     other = {k: v for k, v in kern.items() if k != dom}
     # HBM kernels: algorithmic bytes per launch.  Sort pass: key + id read
-    # and written (16 B per key).  Level emit: the pass bits of every parent
-    # pair (one per child slot: the merge factor rounded up to a power of
-    # two), each parent pair with a survivor read (8 B, at most min(in, out)
-    # of them) and every output pair written (8 B).
-    n_in = int(m.hits[1]) if nl >= 2 else 0
-    n_out = int(m.hits[0])
-    nf = 1 << (wl.F - 1).bit_length()
-    hbm_bytes = {"k_sort_pass": 16 * n, "k_level_emit": n_in * nf // 8 + 8 * min(n_in, n_out) + 8 * n_out}
+    # and written (16 B per key).  The step that only writes: the byte of pass
+    # bits (two for merge factors above 8) of every parent pair, each parent
+    # pair with a survivor read (8 B, at most min(in, out) of them) and every
+    # output pair written (8 B).
+    lv = 1 if fused else 0          # level written (0-based)
+    n_in = int(m.hits[lv + 1]) if nl >= lv + 2 else 0
+    n_out = int(m.hits[lv])
+    hbm_bytes = {"k_sort_pass": 16 * n,
+                 "k_level_emit": n_in * (1 if wl.F <= 8 else 2) + 8 * min(n_in, n_out) + 8 * n_out}
     hbm = {}
     for name, nbytes in hbm_bytes.items():
         if durs.get(name) and nbytes:
