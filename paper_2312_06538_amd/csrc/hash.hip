@@ -54,21 +54,36 @@ struct src_dev {
 };
 
 template <int SRC>
-__device__ __forceinline__ pixel_t load_point(const src_dev &src, const raygen_dev &g0, uint32_t p, raygen_dev &g,
-                                              uint32_t &f)
+__device__ __forceinline__ pixel_t load_point(const src_dev &src, const raygen_dev &g, uint32_t p)
 {
-    f = 0;
-    g = g0;
-    if constexpr (SRC == SRC_BATCH) {
-        if (p < src.gb.npix) {
-            f = frame_of_pixel(src.bd, p);
-            g = frame_raygen(src.bd, f);
-        }
-    }
     if constexpr (SRC == SRC_BOUNCE)
         return load_bounce(src.bo, g, p);
     else
         return load_pixel(src.gb, g, p);
+}
+
+// body(ray generation parameters, frame) for thread p.  In a batch the 64
+// pixels of a wave are of one frame, or of few: the wave goes over them one by
+// one, so the search and the parameters (45 words) are scalar.  As a search and
+// loads per thread they took more than the hashing: 24 frames of 2.3 M pixels,
+// count 128 and emit 164 us, 21 and 71 so.
+template <int SRC, typename Body>
+__device__ __forceinline__ void for_frames(const src_dev &src, const raygen_dev &g0, uint32_t p, Body body)
+{
+    if constexpr (SRC == SRC_BATCH) {
+        const uint32_t pw = __builtin_amdgcn_readfirstlane(p);      // the wave's first pixel
+        if (pw >= src.gb.npix) return;
+        const uint32_t f0 = frame_of_pixel(src.bd, pw);
+        const uint32_t f1 = frame_of_pixel(src.bd, min(pw + (WAVE - 1), src.gb.npix - 1));
+        for (uint32_t f = f0; f <= f1; ++f) {
+            const uint32_t end = f + 1 < src.bd.n_frames ? src.bd.frames[f + 1].pix_begin : src.gb.npix;
+            const raygen_dev g = frame_raygen(src.bd, f);
+            // (the first frame of the wave has its pixels before `end` whatever its base)
+            if (p < end && (f == f0 || p >= src.bd.frames[f].pix_begin) && p < src.gb.npix) body(g, f);
+        }
+    } else {
+        body(g0, 0u);
+    }
 }
 
 template <int SRC>
@@ -76,16 +91,15 @@ __global__ __launch_bounds__(HASH_BLOCK) void k_hash_count(src_dev src, raygen_d
 {
     __shared__ uint32_t red[HASH_BLOCK / WAVE];
     uint32_t p = blockIdx.x * HASH_BLOCK + threadIdx.x;
-    uint32_t f;
-    raygen_dev g;
-    const pixel_t px = load_point<SRC>(src, g0, p, g, f);
     uint32_t c = 0;
-    if (px.hit) {
+    for_frames<SRC>(src, g0, p, [&](const raygen_dev &g, uint32_t) {
+        const pixel_t px = load_point<SRC>(src, g, p);
+        if (!px.hit) return;
         for (int s = 0; s < g.n_lights + 2; ++s) {
             ray_t r;
-            c += make_slot(s, px.P, px.N, px.v, px.flags, px.ior, g, r) ? 1u : 0u;
+            c += make_slot<SRC == SRC_BATCH>(s, px.P, px.N, px.v, px.flags, px.ior, g, r) ? 1u : 0u;
         }
-    }
+    });
     c = wave_sum(c);
     if (lane_id() == 0) red[threadIdx.x / WAVE] = c;
     __syncthreads();
@@ -139,40 +153,43 @@ __global__ __launch_bounds__(HASH_BLOCK) void k_hash_emit(src_dev src, raygen_de
 {
     __shared__ uint32_t scratch[HASH_BLOCK / WAVE];
     uint32_t p = blockIdx.x * HASH_BLOCK + threadIdx.x;
-    uint32_t f;
-    raygen_dev g;
-    const pixel_t px = load_point<SRC>(src, g0, p, g, f);
     uint32_t c = 0;
-    if (px.hit) {
+    pixel_t px;
+    px.hit = false;
+    for_frames<SRC>(src, g0, p, [&](const raygen_dev &g, uint32_t) {
+        px = load_point<SRC>(src, g, p);
+        if (!px.hit) return;
         for (int s = 0; s < g.n_lights + 2; ++s) {
             ray_t r;
-            c += make_slot(s, px.P, px.N, px.v, px.flags, px.ior, g, r) ? 1u : 0u;
+            c += make_slot<SRC == SRC_BATCH>(s, px.P, px.N, px.v, px.flags, px.ior, g, r) ? 1u : 0u;
         }
-    }
+    });
     uint32_t total;
     uint32_t id = block_off[blockIdx.x] + block_excl_scan<uint32_t, HASH_BLOCK / WAVE>(c, scratch, total);
-    if constexpr (SRC == SRC_BATCH) {
-        if (p < src.gb.npix && p == src.bd.frames[f].pix_begin) src.bd.fm[f].ray_begin = id;
-    }
-    if (!px.hit || c == 0) return;
-    for (int s = 0; s < g.n_lights + 2; ++s) {
-        ray_t r;
-        if (!make_slot(s, px.P, px.N, px.v, px.flags, px.ior, g, r)) continue;
-        if (id < out.cap) {
-            out.ox[id] = r.o.x;
-            out.oy[id] = r.o.y;
-            out.oz[id] = r.o.z;
-            out.dx[id] = r.d.x;
-            out.dy[id] = r.d.y;
-            out.dz[id] = r.d.z;
-            out.tmax[id] = r.tmax;
-            out.pix[id] = px.pix;
-            keys[id] = r.key;
-            ids[id] = id;
-            if constexpr (SRC == SRC_BATCH) out.frame[id] = f;
+    for_frames<SRC>(src, g0, p, [&](const raygen_dev &g, uint32_t f) {
+        if constexpr (SRC == SRC_BATCH) {
+            if (p == src.bd.frames[f].pix_begin) src.bd.fm[f].ray_begin = id;
         }
-        ++id;
-    }
+        if (!px.hit || c == 0) return;
+        for (int s = 0; s < g.n_lights + 2; ++s) {
+            ray_t r;
+            if (!make_slot<SRC == SRC_BATCH>(s, px.P, px.N, px.v, px.flags, px.ior, g, r)) continue;
+            if (id < out.cap) {
+                out.ox[id] = r.o.x;
+                out.oy[id] = r.o.y;
+                out.oz[id] = r.o.z;
+                out.dx[id] = r.d.x;
+                out.dy[id] = r.d.y;
+                out.dz[id] = r.d.z;
+                out.tmax[id] = r.tmax;
+                out.pix[id] = px.pix;
+                keys[id] = r.key;
+                ids[id] = id;
+                if constexpr (SRC == SRC_BATCH) out.frame[id] = f;
+            }
+            ++id;
+        }
+    });
 }
 
 static raygen_dev to_device(const crsh_raygen *rg)

@@ -164,13 +164,24 @@ __device__ __forceinline__ uint32_t key_bounce(uint32_t type, f3 o, f3 d, const 
 // direction v (shadow rays of lights 0..L-1, reflection, refraction);
 // returns false for a hole.  With CRSH_KEY_TYPE_ONLY the key keeps only the
 // ray type and light: the comparison hierarchy without ray sorting (Sec. 2).
+// LOCAL: g is a local copy, whose lights are chosen, not indexed (indexed, they
+// would lie in scratch memory).
+template <bool LOCAL>
 __device__ __forceinline__ bool make_slot(int s, f3 P, f3 N, f3 v, uint32_t flags, float ior, const raygen_dev &g,
                                           ray_t &r)
 {
     bool ok = false;
     if (s < g.n_lights) {
         if (g.types & CRSH_RAY_SHADOW) {
-            f3 L = mk(g.lx[s], g.ly[s], g.lz[s]);
+            f3 L;
+            if constexpr (LOCAL) {
+                L = mk(g.lx[0], g.ly[0], g.lz[0]);
+#pragma unroll
+                for (int i = 1; i < CRSH_MAX_LIGHTS; ++i)
+                    if (s == i) L = mk(g.lx[i], g.ly[i], g.lz[i]);
+            } else {
+                L = mk(g.lx[s], g.ly[s], g.lz[s]);
+            }
             f3 d0 = P - L;
             float l = len(d0);
             if (l > g.eps_shadow) {
