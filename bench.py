@@ -54,7 +54,10 @@ PUBLISHED_FP32_TFLOPS = 157.3
 TRAFFIC_PROFILES = "profiles/*_hbm_traffic_*.md"
 TRAFFIC_SOURCES = {"k_hit": ["paper_2312_06538_amd/csrc/hit.hip", "paper_2312_06538_amd/csrc/intersect.hpp",
                              "paper_2312_06538_amd/csrc/batch.hpp", "paper_2312_06538_amd/csrc/common.hpp",
-                             "include/crsh.h"]}
+                             "include/crsh.h"],
+                   "k_level": ["paper_2312_06538_amd/csrc/traverse.hip", "paper_2312_06538_amd/csrc/traverse.hpp",
+                               "paper_2312_06538_amd/csrc/bounds.hpp", "paper_2312_06538_amd/csrc/batch.hpp",
+                               "paper_2312_06538_amd/csrc/common.hpp", "include/crsh.h"]}
 
 
 def sources_sha256(kernel):
@@ -360,7 +363,7 @@ def main():
                           "launches_timed": len(durs[name])}
     dom = max(kern, key=lambda k: kern[k]["kernel_ms"]) if kern else None
     roof = kern.get(dom)
-    if roof is not None and dom in TRAFFIC_SOURCES:
+    if roof is not None and dom in TRAFFIC_SOURCES and not (fused and dom == "k_level"):
         roof["traffic"], roof["traffic_source"] = measured_traffic(dom, args.workload + ("" if args.variant == "crsh"
                                                                                            else "_" + args.variant))
     other = {k: v for k, v in kern.items() if k != dom}
