@@ -808,6 +808,15 @@ __global__ __launch_bounds__(COUNT_THREADS) void k_level_count_lanes(int32_t par
 // several consecutive tiles at a time where there are enough, so that a copy
 // lasts.
 //
+// Where a top-level node has more descendants than the copy holds (not STAGED)
+// every child comes from the node arrays, and lanes work in groups of NF: in
+// turn r a group tests the pair of its lane r, a child a lane, so that it reads
+// F consecutive nodes (pair and sphere from that lane).  Each lane reading the
+// children of its own pair instead, 64 unrelated nodes a load, was bound by the
+// vector L1: the step that tests level 1 of 512x512 rays with 4,096 leaves below
+// a top node (bundle 4) 6.0 ms with merge factor 8, the traversal 7.2; so 2.7,
+// and with merge factor 4 the traversal 4.2 and 2.8.
+//
 // What bounds it: the tests' arithmetic (1080p frame of 201,632 triangles, the
 // step that tests level 1: vector ALUs 75 % busy, 175 lane instructions per
 // written pair, about 30 a test); the last step (no test) writes and reads
@@ -890,6 +899,11 @@ __global__ __launch_bounds__(STEP_THREADS, NF == 16 ? 4 : 6) void k_level_step(i
         }
         v.off = S.off[(t < ntiles ? t : 0u) + zero];
     };
+    // nodes of the level below the one written, by 32-bit byte offsets (node
+    // indices stay below 2^28)
+    const __amdgpu_buffer_rsrc_t ra = make_rsrc(na, ((uint64_t)off2 + n2) * 16u);
+    const __amdgpu_buffer_rsrc_t rb = make_rsrc(nb, ((uint64_t)off2 + n2) * 16u);
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(ns, ((uint64_t)off2 + n2) * 4u);
     uint32_t wlo = 0u, wlen = 0u;           // nodes whose children are in LDS (block-uniform)
     uint32_t wend = 0u;                     // children of the copy's frame from the copy's first child on
     uint32_t wfull = 0u;                    // nodes of the copy with NF children each
@@ -1024,58 +1038,106 @@ __global__ __launch_bounds__(STEP_THREADS, NF == 16 ? 4 : 6) void k_level_step(i
             }
             if constexpr (TEST) {
                 const float4 sp = cp.sp;
-                const f3 pc = mk(sp.x, sp.y, sp.z);
-                const uint64_t live = n_put - i0 >= WAVE ? ~0ull : (1ull << (n_put - i0)) - 1ull;
-                const uint32_t pl = node - wlo;
-                uint64_t pass[NF];
-                // every pair's children in the copy, all F = NF of them: no
-                // looking further (a lane past the end repeats the first pair)
-                if (STAGED && ballot(pl >= wfull) == 0) {
-#pragma unroll
-                    for (uint32_t r = 0; r < NF; ++r)
-                        pass[r] = packed_meets_mask(s_wa[r * WP + pl], s_wb[r * WP + pl], s_ws[r * WP + pl], pc, sp.w) & live;
-                    tests64 += (uint64_t)__popcll(live) * NF;
-                } else {
-                    const bool inw = STAGED && pl < wlen;
-                    const uint32_t ps = inw ? pl : 0u;
-                    uint32_t n = inw && i < n_put ? min(F, wend - pl * F) : 0u;
-#pragma unroll
-                    for (uint32_t r = 0; r < NF; ++r) {
-                        pass[r] = 0u;
-                        if constexpr (STAGED)
-                            pass[r] = packed_meets_mask(s_wa[r * WP + ps], s_wb[r * WP + ps], s_ws[r * WP + ps], pc, sp.w) &
-                                      ballot(r < n);
+                // first child and number of children of this lane's pair
+                auto children = [&](uint32_t &c, uint32_t &k) {
+                    c = node * F;
+                    k = c < n2 ? min(F, n2 - c) : 0u;
+                    if constexpr (BATCH) {
+                        c = node < n1 ? bd.node_first[off1 + node] : 0u;
+                        k = node < n1 ? bd.node_info[off1 + node] & INFO_COUNT_MASK : 0u;
+                        k = c < n2 ? min(k, n2 - c) : 0u;
                     }
-                    // pairs outside the copy: children from the node arrays
-                    if (ballot(!inw && i < n_put) != 0) {
-                        uint32_t c = node * F, k = c < n2 ? min(F, n2 - c) : 0u;
-                        if constexpr (BATCH) {
-                            c = node < n1 ? bd.node_first[off1 + node] : 0u;
-                            k = node < n1 ? bd.node_info[off1 + node] & INFO_COUNT_MASK : 0u;
-                            k = c < n2 ? min(k, n2 - c) : 0u;
-                        }
-                        k = !inw && i < n_put ? k : 0u;
-                        n += k;
-#pragma unroll
-                        for (uint32_t r = 0; r < NF; ++r) {
-                            const uint32_t g = off2 + (r < k ? c + r : 0u);
-                            pass[r] |= packed_meets_mask(na[g], nb[g], ns[g], pc, sp.w) & ballot(r < k);
-                        }
-                    }
-#pragma unroll
-                    for (uint32_t r = 0; r < NF; ++r) tests64 += (uint64_t)__popcll(ballot(r < n));
-                }
+                };
                 // the pair's pass bits, and the survivors of the lanes in the
                 // first of the (at most two) next-level tiles they lie in
                 const uint64_t p0 = base + i0;
                 const uint32_t left = TILE - (uint32_t)(p0 % TILE);
-                const uint64_t in_first = left >= WAVE ? ~0ull : (1ull << left) - 1ull;
                 uint32_t bits = 0u, ca = 0u, cb = 0u;
+                if constexpr (STAGED) {
+                    const f3 pc = mk(sp.x, sp.y, sp.z);
+                    const uint64_t live = n_put - i0 >= WAVE ? ~0ull : (1ull << (n_put - i0)) - 1ull;
+                    const uint32_t pl = node - wlo;
+                    uint64_t pass[NF];
+                    // every pair's children in the copy, all F = NF of them: no
+                    // looking further (a lane past the end repeats the first pair)
+                    if (ballot(pl >= wfull) == 0) {
 #pragma unroll
-                for (int r = NF - 1; r >= 0; --r) {
-                    bits = bits + bits + (__builtin_amdgcn_inverse_ballot_w64(pass[r]) ? 1u : 0u);
-                    ca += (uint32_t)__popcll(pass[r] & in_first);
-                    cb += (uint32_t)__popcll(pass[r] & ~in_first);
+                        for (uint32_t r = 0; r < NF; ++r)
+                            pass[r] = packed_meets_mask(s_wa[r * WP + pl], s_wb[r * WP + pl], s_ws[r * WP + pl], pc, sp.w) & live;
+                        tests64 += (uint64_t)__popcll(live) * NF;
+                    } else {
+                        const bool inw = pl < wlen;
+                        const uint32_t ps = inw ? pl : 0u;
+                        uint32_t n = inw && i < n_put ? min(F, wend - pl * F) : 0u;
+#pragma unroll
+                        for (uint32_t r = 0; r < NF; ++r)
+                            pass[r] = packed_meets_mask(s_wa[r * WP + ps], s_wb[r * WP + ps], s_ws[r * WP + ps], pc, sp.w) &
+                                      ballot(r < n);
+                        // pairs outside the copy: children from the node arrays
+                        if (ballot(!inw && i < n_put) != 0) {
+                            uint32_t c, k;
+                            children(c, k);
+                            k = !inw && i < n_put ? k : 0u;
+                            n += k;
+#pragma unroll
+                            for (uint32_t r = 0; r < NF; ++r) {
+                                const uint32_t g = off2 + (r < k ? c + r : 0u);
+                                pass[r] |= packed_meets_mask(na[g], nb[g], ns[g], pc, sp.w) & ballot(r < k);
+                            }
+                        }
+#pragma unroll
+                        for (uint32_t r = 0; r < NF; ++r) tests64 += (uint64_t)__popcll(ballot(r < n));
+                    }
+                    const uint64_t in_first = left >= WAVE ? ~0ull : (1ull << left) - 1ull;
+#pragma unroll
+                    for (int r = NF - 1; r >= 0; --r) {
+                        bits = bits + bits + (__builtin_amdgcn_inverse_ballot_w64(pass[r]) ? 1u : 0u);
+                        ca += (uint32_t)__popcll(pass[r] & in_first);
+                        cb += (uint32_t)__popcll(pass[r] & ~in_first);
+                    }
+                } else {
+                    // lanes in groups of NF: in turn r a group tests the pair of
+                    // its lane r, one child a lane
+                    const uint32_t j = l % NF;
+                    const int grp = (int)((l - j) * 4u);    // byte address of the group's first lane
+                    auto turn = [&](uint32_t v, uint32_t r) {
+                        return (uint32_t)__builtin_amdgcn_ds_bpermute(grp + (int)(4u * r), (int)v);
+                    };
+                    auto turnf = [&](float v, uint32_t r) { return __uint_as_float(turn(__float_as_uint(v), r)); };
+                    uint32_t c, k;
+                    children(c, k);
+                    k = i < n_put ? k : 0u;
+                    constexpr uint32_t K = 2;               // turns whose nodes are read together
+#pragma unroll
+                    for (uint32_t r0 = 0; r0 < NF; r0 += K) {
+                        float4 A[K], Bv[K];
+                        float Sg[K];
+                        uint64_t ok[K];
+#pragma unroll
+                        for (uint32_t t = 0; t < K; ++t) {
+                            const uint32_t first = turn(c, r0 + t);
+                            const bool has = j < turn(k, r0 + t);
+                            const uint32_t g = off2 + (has ? first + j : 0u);
+                            ok[t] = ballot(has);
+                            A[t] = buf_load4(ra, g * 16u);
+                            Bv[t] = buf_load4(rb, g * 16u);
+                            Sg[t] = buf_load1(rs, g * 4u);
+                        }
+#pragma unroll
+                        for (uint32_t t = 0; t < K; ++t) {
+                            const uint32_t r = r0 + t;
+                            const uint64_t m = packed_meets_mask(A[t], Bv[t], Sg[t], mk(turnf(sp.x, r), turnf(sp.y, r),
+                                                                 turnf(sp.z, r)), turnf(sp.w, r)) & ok[t];
+                            tests64 += (uint64_t)__popcll(ok[t]);
+                            ca += (uint32_t)__popcll(m);
+                            bits = j == r ? (uint32_t)(m >> (l - j)) & ((1u << NF) - 1u) : bits;
+                        }
+                    }
+                    if (left < WAVE) {
+                        cb = wave_reduce(l < left ? 0u : (uint32_t)__popc(bits), 0u,
+                                         [](uint32_t a, uint32_t b) { return a + b; });
+                        ca -= cb;
+                    }
                 }
                 if constexpr (sizeof(mask_t) == 1)
                     __builtin_amdgcn_raw_buffer_store_b8((uint8_t)bits, om, i, 0, 0);
