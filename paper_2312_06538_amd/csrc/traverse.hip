@@ -76,28 +76,41 @@ __global__ void k_trav_prep(tri_verts V, uint32_t b, uint32_t e, float4 *tsph, n
 // Up to 1,024 items, a wave per SIMD (with 4,096 the scan over them and the
 // look-ups cost a 128x128 frame 6 us more than the parts save it).  Above
 // 4,096 items, of which a wave then has several and most have nothing to test,
-// 4 parts even out the waves: top count, emit and scan 470 to 405 us on
-// 512x512 reflections of 262,144 items, 866 to 815 on a 1080p frame; 2 parts
-// 402 and 834, 8 parts 505 and 886.
-__device__ __forceinline__ uint32_t top_parts(uint64_t items, uint64_t cap)
+// up to 4 parts (`many`) even out the waves: top count, emit and scan 470 to 405
+// us on 512x512 reflections of 262,144 items, 866 to 815 on a 1080p frame; 2
+// parts 402 and 834, 8 parts 505 and 886.  That holds for meshes of many steps
+// (1,240 and 1,880 triangles on average there).  Smaller ones gain nothing, and
+// every part looks its item up and adds to the count of a tile that many others
+// add to: traversals of 512x512 shadow rays against meshes of 233 triangles on
+// average (180,224 items) 164 us in one part, 316 in four, of 931 (180,224 items)
+// 206 and 337, of 931 (90,112) 161 and 184, of 1,116 (94,208) 157 and 151.  So
+// four parts from a mean of 1,024 triangles (top_many).  Between 1,025 and 4,096
+// items, one to four for a wave, one part each (not measured there).
+__device__ __forceinline__ uint32_t top_parts(uint64_t items, uint64_t cap, uint32_t many)
 {
     uint32_t s = 1;
-    const uint64_t lim = items > 4096 ? 4 * items : 1024u;
+    const uint64_t lim = items > 4096 ? many * items : 1024u;
     while (s < 16 && items * s * 2 <= lim && items * s * 2 <= cap) s *= 2;
     return s;
+}
+
+static uint32_t top_many(uint32_t m, uint32_t n_mesh)
+{
+    const uint32_t mean = m / std::max(n_mesh, 1u);
+    return mean >= 1024u ? 4u : 1u;
 }
 
 // number of work items of a level: top level (parent_level 0) = top nodes x
 // meshes x parts (top_parts), lower levels = tiles of `tile` parent pairs
 __device__ __forceinline__ uint64_t level_items(const crsh_meta *meta, int32_t parent_level, uint32_t n_mesh,
                                                 const pair_levels &P, uint32_t tile, uint64_t top_cap,
-                                                uint32_t &parts)
+                                                uint32_t many, uint32_t &parts)
 {
     const uint32_t nl = meta->n_levels;
     parts = 1;
     if (parent_level == 0) {
         const uint64_t items = nl ? (uint64_t)meta->level_cnt[nl - 1] * n_mesh : 0;
-        parts = top_parts(items, top_cap);
+        parts = top_parts(items, top_cap, many);
         return items * parts;
     }
     if ((uint32_t)parent_level > nl || parent_level < 2) return 0;
@@ -176,7 +189,7 @@ __device__ __forceinline__ uint64_t from_lane(uint64_t v, uint32_t src)
 // top level of this pass (0-based) and its number of items
 template <bool BATCH>
 __device__ __forceinline__ bool top_pass(const crsh_meta *meta, const batch_dev &bd, uint32_t L, uint32_t n_mesh,
-                                         const pair_levels &P, uint64_t top_cap, uint32_t &top, uint64_t &n_items,
+                                         const pair_levels &P, const trav_scratch &S, uint32_t &top, uint64_t &n_items,
                                          uint32_t &parts)
 {
     const uint32_t nl = meta->n_levels;
@@ -188,7 +201,7 @@ __device__ __forceinline__ bool top_pass(const crsh_meta *meta, const batch_dev 
         parts = (uint32_t)bd.top[2];
     } else {
         top = nl - 1;
-        n_items = level_items(meta, 0, n_mesh, P, 1u, top_cap, parts);
+        n_items = level_items(meta, 0, n_mesh, P, 1u, S.top_cap, S.top_many, parts);
     }
     return true;
 }
@@ -206,7 +219,7 @@ __global__ __launch_bounds__(256) void k_top_count(const float4 *__restrict__ na
     uint32_t top, parts;
     uint64_t n_items;
     clear_scan(S);
-    if (!top_pass<BATCH>(meta, bd, L, n_mesh, P, S.top_cap, top, n_items, parts)) return;
+    if (!top_pass<BATCH>(meta, bd, L, n_mesh, P, S, top, n_items, parts)) return;
     const uint32_t off = meta->level_off[top];
     const uint32_t l = lane_id();
     const uint64_t wave = (uint64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
@@ -271,6 +284,12 @@ struct mask_type<16> {
     typedef uint16_t t;
 };
 
+// Many items of one part each come TOP_RUN at a time to a wave, neighbours in the
+// pair list, so that their survivors, most of one tile, are added to its count at
+// once: traversal of 512x512 shadow rays, 180,224 items, 165 us one by one, 118
+// in twos, 100 in fours, 104 in eights (larger meshes, 206, 160, 169, 210).
+constexpr uint32_t TOP_RUN = 4;
+
 // NF: the merge factor rounded up to a power of two.  Top-level pairs written
 // at or above level `lowest` + 1 are tested against their node's children.
 template <int NF, bool BATCH, bool PACKED>
@@ -292,7 +311,7 @@ __global__ __launch_bounds__(256) void k_top_emit(const float4 *__restrict__ na,
     uint32_t top, parts;
     uint64_t n_items;
     clear_scan(S);
-    if (!top_pass<BATCH>(meta, bd, L, n_mesh, P, S.top_cap, top, n_items, parts)) return;
+    if (!top_pass<BATCH>(meta, bd, L, n_mesh, P, S, top, n_items, parts)) return;
     const pairs_dev out = P.p[top];
     if (out.tri == nullptr) return;
     const bool test = top >= lowest;         // level top + 1 (1-based) >= lowest + 1
@@ -303,8 +322,10 @@ __global__ __launch_bounds__(256) void k_top_emit(const float4 *__restrict__ na,
     const uint64_t wave = (uint64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
     const uint64_t nwaves = (uint64_t)gridDim.x * (blockDim.x / WAVE);
     uint64_t tests = 0;
-    for (uint64_t it0 = wave; it0 < n_items; it0 += nwaves * WAVE) {
-        const uint64_t it = it0 + l * nwaves;
+    const uint64_t run = parts == 1 && n_items > 4096 ? TOP_RUN : 1u;
+    const uint64_t lane_it = l / run * nwaves * run + l % run;
+    for (uint64_t it0 = wave * run; it0 < n_items; it0 += nwaves * WAVE) {
+        const uint64_t it = it0 + lane_it;
         const bool some = it < n_items && S.cnt_top[it] != 0;
         uint64_t todo = ballot(some);
         if (todo == 0) continue;
@@ -312,7 +333,8 @@ __global__ __launch_bounds__(256) void k_top_emit(const float4 *__restrict__ na,
         float lS;
         uint32_t li, lb, le;
         bool pass;
-        const uint64_t use = some ? it : it0 + (uint64_t)__builtin_ctzll(todo) * nwaves;
+        const uint32_t one = (uint32_t)__builtin_ctzll(todo);
+        const uint64_t use = some ? it : it0 + one / run * nwaves * run + one % run;
         top_item<BATCH>(use, parts, n_mesh, top, off, bd, na, nb, ns, msph, mesh_first, mesh_count, tri_begin, tri_end,
                         lA, lB, lS, li, lb, le, pass);
         const uint64_t lpos = S.off[use];
@@ -325,6 +347,8 @@ __global__ __launch_bounds__(256) void k_top_emit(const float4 *__restrict__ na,
                 lnch = lfirst < nk ? min(bd.node_info[off + li] & INFO_COUNT_MASK, nk - lfirst) : 0u;
             }
         }
+        uint64_t tile = 0;                       // tile being written, and its survivors so far
+        uint32_t in_tile = 0u;
         for (; todo; todo &= todo - 1u) {
             const uint32_t src = (uint32_t)__builtin_ctzll(todo);
             const float4 A = from_lane(lA, src), Bv = from_lane(lB, src);
@@ -339,8 +363,11 @@ __global__ __launch_bounds__(256) void k_top_emit(const float4 *__restrict__ na,
             }
             __builtin_amdgcn_wave_barrier();
             uint64_t pos = from_lane(lpos, src);
-            uint64_t tile = pos / TILE;          // survivors of the tile being written
-            uint32_t in_tile = 0u;
+            if (pos / TILE != tile) {
+                if (l == 0 && in_tile) atomicAdd(&S.cnt[tile], in_tile);
+                tile = pos / TILE;
+                in_tile = 0u;
+            }
             float4 s_n = b < e ? tsph[min(b + l, e - 1)] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             for (uint32_t t0 = b; t0 < e; t0 += WAVE) {
                 const uint32_t t = t0 + l;
@@ -382,8 +409,8 @@ __global__ __launch_bounds__(256) void k_top_emit(const float4 *__restrict__ na,
                 }
                 pos += (uint32_t)__popcll(mk64);
             }
-            if (l == 0 && in_tile) atomicAdd(&S.cnt[tile], in_tile);
         }
+        if (l == 0 && in_tile) atomicAdd(&S.cnt[tile], in_tile);
     }
     if (l == 0) s_red[threadIdx.x / WAVE] = tests;
     __syncthreads();
@@ -491,7 +518,7 @@ __global__ __launch_bounds__(COUNT_THREADS) void k_level_count_lanes(int32_t par
     const uint32_t nl = meta->n_levels;
     if ((uint32_t)parent_level > nl || parent_level < 2) return;
     uint32_t parts;
-    const uint64_t ntiles = level_items(meta, parent_level, 0, P, LEVEL_TILE, 0, parts);
+    const uint64_t ntiles = level_items(meta, parent_level, 0, P, LEVEL_TILE, 0, 1u, parts);
     const pairs_dev in = P.p[parent_level - 1];
     if (in.tri == nullptr || P.p[parent_level - 2].tri == nullptr) return;
     uint64_t nin = meta->pairs[parent_level - 1];
@@ -1192,7 +1219,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_items(int32_t parent_leve
     if (batch_top > nl) return;
     const bool top = parent_level == 0;
     uint32_t parts;
-    const uint64_t n = batch_top ? bd_top[0] : level_items(meta, parent_level, n_mesh, P, tile_pairs, S.top_cap, parts);
+    const uint64_t n = batch_top ? bd_top[0] : level_items(meta, parent_level, n_mesh, P, tile_pairs, S.top_cap, S.top_many, parts);
     const uint64_t base = batch_top ? bd_top[1] : 0u;
     const uint32_t out_level = batch_top ? batch_top - 1 : (top ? nl - 1 : (uint32_t)parent_level - 2);
     const uint64_t ntiles = (n + SCAN_TILE - 1) / SCAN_TILE;
@@ -1286,7 +1313,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_items(int32_t parent_leve
 // Batch, before the top-level pass of level L: item ranges of the frames
 // whose top is L (one thread per frame), their total, and the pairs already
 // on that level (the append base).  Too many items: flagged, pass skipped.
-__global__ __launch_bounds__(256) void k_batch_top_plan(batch_dev bd, crsh_meta *meta, uint32_t L)
+__global__ __launch_bounds__(256) void k_batch_top_plan(batch_dev bd, crsh_meta *meta, uint32_t L, uint32_t many)
 {
     __shared__ uint64_t scratch[256 / WAVE];
     const uint32_t f = threadIdx.x;
@@ -1302,7 +1329,7 @@ __global__ __launch_bounds__(256) void k_batch_top_plan(batch_dev bd, crsh_meta 
             atomicOr(&meta->status, CRSH_OVERFLOW_ITEMS);
             total = 0;
         }
-        const uint32_t parts = top_parts(total, bd.top_cap);
+        const uint32_t parts = top_parts(total, bd.top_cap, many);
         bd.top[0] = total * parts;
         bd.top[2] = parts;
         bd.top[1] = L >= 1 ? meta->pairs[L - 1] : 0u;
@@ -1442,6 +1469,7 @@ static crsh_status traverse_run(const crsh_nodes *nodes, const crsh_scene *scene
     w += align256((size_t)nodes->capacity * 4);
     trav_scratch S{};
     S.top_cap = top_items;
+    S.top_many = top_many(scene->m, scene->n_mesh);
     S.cnt_top = (uint32_t *)w;
     w += align256(top_items * 4 + 4);
     S.cnt = (uint32_t *)w;
@@ -1488,7 +1516,7 @@ static crsh_status traverse_run(const crsh_nodes *nodes, const crsh_scene *scene
 
     // top-level pass: plain (L = 0, the one top level) or a batch level L
     auto top_pass_launch = [&](uint32_t L) {
-        if (bd) k_batch_top_plan<<<1, 256, 0, stream>>>(b, meta, L);
+        if (bd) k_batch_top_plan<<<1, 256, 0, stream>>>(b, meta, L, S.top_many);
         {
             prof_scope ps("k_top_count", stream);
             if (bd)

@@ -52,6 +52,7 @@ struct node_arrays {
 // per-level scratch carved from the workspace
 struct trav_scratch {
     uint64_t top_cap;      // entries of cnt_top
+    uint32_t top_many;     // most parts per top-level item where there are many items
     uint32_t *cnt_top;     // survivors per top-level item
     uint32_t *cnt;         // surviving children per tile of pairs (cleared by the scan that reads it)
     uint64_t *off;         // exclusive offsets of the items or tiles
