@@ -152,7 +152,8 @@ __global__ void k_hit_pack(tri_verts V, uint32_t m, hit_tris_ws tri, sorted_rays
 // A workgroup takes a chunk of consecutive pairs.  Pairs of one top-level
 // node name a few hundred leaves in triangle order, so a chunk holds many
 // pairs of each of its leaves: they are counted per leaf with LDS atomics
-// (HIT_BINS leaves from the smallest in the chunk; leaves beyond wait for
+// (HIT_BINS bins: the leaves from the smallest on or, where they span more, the
+// leaves that have pairs, numbered by a bitmap; what then has no bin waits for
 // another round over the chunk), scanned, and the triangle ids scattered to
 // their leaf's run in LDS, cut into blocks of at most G triangles (G: the
 // bundle rounded up to a power of two, at least 4) -- the whole blocks
@@ -177,6 +178,10 @@ __global__ void k_hit_pack(tri_verts V, uint32_t m, hit_tris_ws tri, sorted_rays
 // triangle entries through LDS (a third of the L1 accesses, but more
 // instructions and fewer workgroups) 8.3 ms; the filter's outcome as wave masks
 // instead of shifted sign bits 9.4 ms.
+// Where a top-level node has more leaves than there are bins, a chunk's pairs
+// still name few of them (256 of 12,700 spanned on average, 128x72 mixed rays, 2 to
+// a leaf, merge factor 4, 8 levels): in windows of 1,024 leaves it was read 7
+// times, 324 us; by the leaves that have pairs once, 212.
 // Fused (640x360 mixed rays, 144 M level-2 pairs, 2.8 G tests): 5.4 ms with a
 // lane per (child, ray), 1.85 ms so.  A chunk of 2,048 level-2 pairs has 2,500
 // children there; 1,536 1.96 ms, 1,792 1.91, 2,560 2.17, 3,072 2.18 (more
@@ -189,10 +194,17 @@ constexpr uint32_t HIT_CHUNK = HIT_THREADS * HIT_PPT;       // most pairs of a c
 constexpr uint32_t HIT_MIN_CHUNK = 64;                      // fewest
 constexpr uint32_t HIT_BPT = 4;                             // leaf bins per thread
 constexpr uint32_t HIT_BINS = HIT_THREADS * HIT_BPT;        // leaves binned per round
+constexpr uint32_t HIT_SPAN = 1u << 15;                     // leaves that a round's bins can lie in
 constexpr uint32_t HIT_QUEUE = 128;                         // queued items of a wave
-constexpr uint32_t HIT_WAVES_PER_SIMD = 4;                  // registers for 4 workgroups per compute unit
-// block word: first triangle (13 bits), triangles - 1 (5 bits), leaf bin (10 bits)
-static_assert(HIT_CHUNK <= 1u << 13 && HIT_BINS <= 1u << 10 && CRSH_MAX_BUNDLE <= 32, "block word");
+// registers for 5 workgroups per compute unit, 4 for the smallest groups (their
+// block words take the LDS of more)
+constexpr int hit_waves_per_simd(int lg) { return lg > 2 ? 5 : 4; }
+// block word: first triangle (12 bits), triangles - 1 (5 bits), leaf from the round's first on (15 bits)
+static_assert(HIT_CHUNK <= 1u << 12 && HIT_SPAN <= 1u << 15 && CRSH_MAX_BUNDLE <= 32, "block word");
+// bitmap of the leaves and the counts before its words, 16 bits each, in s_tri
+constexpr uint32_t HIT_SPAN_WORDS = HIT_SPAN / 32;
+constexpr uint32_t HIT_SPAN_WPT = HIT_SPAN_WORDS / HIT_THREADS;
+static_assert(HIT_SPAN_WORDS + HIT_SPAN_WORDS / 2 <= HIT_CHUNK && HIT_SPAN_WPT * HIT_THREADS == HIT_SPAN_WORDS, "bitmap");
 
 // What the pairs are.  Fused: level-2 pairs and a pass bit per child (the
 // level-1 pairs are never stored): pair q keeps child j (leaf first + j, first
@@ -275,7 +287,7 @@ __device__ __forceinline__ void filter_all(const float4 &f0, const float4 &f1, c
 }
 
 template <int LG, bool BATCH, int IN>
-__global__ __launch_bounds__(HIT_THREADS, HIT_WAVES_PER_SIMD) void k_hit(hit_slots_ws hs, const float4 *__restrict__ tri,
+__global__ __launch_bounds__(HIT_THREADS, hit_waves_per_simd(LG)) void k_hit(hit_slots_ws hs, const float4 *__restrict__ tri,
                                                      const float4 *__restrict__ ftri,
                                                      const uint32_t *__restrict__ ptri,
                                                      const uint32_t *__restrict__ pnode, uint64_t cap1, uint32_t B,
@@ -290,7 +302,8 @@ __global__ __launch_bounds__(HIT_THREADS, HIT_WAVES_PER_SIMD) void k_hit(hit_slo
     constexpr uint32_t NONE = 0xFFFFFFFFu;
     __shared__ uint32_t s_tri[HIT_CHUNK];           // triangle ids, leaf by leaf
     __shared__ __attribute__((aligned(8))) uint32_t s_cnt[HIT_BINS];            // pairs per leaf, then the leaf's first place
-    __shared__ uint32_t s_blk[HIT_CHUNK / G + HIT_BINS];
+    __shared__ uint32_t s_blk[HIT_CHUNK / G + HIT_BINS];    // first the leaves of the bins, if not consecutive
+    __shared__ uint32_t s_from;
     __shared__ uint2 s_queue[HIT_WAVES][HIT_QUEUE];
     __shared__ uint2 s_scan[HIT_WAVES], s_lohi[HIT_WAVES];
     __shared__ uint64_t s_red[3][HIT_WAVES];
@@ -454,31 +467,129 @@ __global__ __launch_bounds__(HIT_THREADS, HIT_WAVES_PER_SIMD) void k_hit(hit_slo
             }
             const uint32_t base = __builtin_amdgcn_readfirstlane(lo);
             hi = __builtin_amdgcn_readfirstlane(hi);
-            more = base != NONE && hi - base >= HIT_BINS;
-            from = base + HIT_BINS;
-            // pairs per leaf; each pair's bin and its place in the leaf's run
-            // (fused: the place is taken when the triangle is put there)
-            if constexpr (FUSED) {
-                for (uint32_t c = 0; c < fu.nf; ++c)
-#pragma unroll
-                    for (uint32_t k = 0; k < PPT; ++k) {
-                        const uint32_t bin = my_leaf[k] + c - base;
-                        if ((my_bits[k] >> c & 1u) != 0u && bin < HIT_BINS) atomicAdd(&s_cnt[bin], 1u);
-                    }
-            } else
+            const bool wide = base != NONE && hi - base >= HIT_BINS;
+            more = false;
+            // the leaves counted from the round's first on
 #pragma unroll
             for (uint32_t k = 0; k < PPT; ++k) {
-                const uint32_t bin = my_leaf[k] - base;
-                const bool ok = bin < HIT_BINS && my_leaf[k] != NONE;
+                if constexpr (FUSED) {
+                    // (may be below it; the bits of such children are clear)
+                    my_leaf[k] -= base;
+                } else {
+                    my_leaf[k] = my_leaf[k] != NONE ? my_leaf[k] - base : NONE;
+                }
+            }
+            // wide: the bins are the leaves that have pairs, in order, and
+            // my_leaf becomes the bin (fused: of the first child, with a bit for
+            // each child that has a bin in the high half)
+            if (wide) {
+                if constexpr (FUSED) {
+#pragma unroll
+                    for (uint32_t k = 0; k < PPT; ++k) {
+                        const uint32_t sh = 0u - my_leaf[k] < 16u ? 0u - my_leaf[k] : 0u;
+                        my_bits[k] >>= sh;
+                        my_leaf[k] += sh;
+                    }
+                }
+                uint32_t *const map = s_tri;
+                uint16_t *const before = (uint16_t *)(s_tri + HIT_SPAN_WORDS);
+#pragma unroll
+                for (uint32_t k = 0; k < HIT_SPAN_WPT; ++k) map[tid + k * HIT_THREADS] = 0u;
+                __syncthreads();
+#pragma unroll
+                for (uint32_t k = 0; k < PPT; ++k) {
+                    const uint32_t w = my_leaf[k] / 32u;
+                    if constexpr (FUSED) {
+                        const uint64_t b = (uint64_t)my_bits[k] << (my_leaf[k] & 31u);
+                        if ((uint32_t)b != 0u && w < HIT_SPAN_WORDS) atomicOr(&map[w], (uint32_t)b);
+                        if (b >> 32 != 0u && w < HIT_SPAN_WORDS - 1u) atomicOr(&map[w + 1], (uint32_t)(b >> 32));
+                    } else if (w < HIT_SPAN_WORDS) {
+                        atomicOr(&map[w], 1u << (my_leaf[k] & 31u));
+                    }
+                }
+                __syncthreads();
+                uint32_t n = 0u, own[HIT_SPAN_WPT];
+#pragma unroll
+                for (uint32_t k = 0; k < HIT_SPAN_WPT; ++k) {
+                    own[k] = map[HIT_SPAN_WPT * tid + k];
+                    n += (uint32_t)__popc(own[k]);
+                }
+                uint32_t bin = wave_scan_dpp(n), leaves = 0u;
+                if (l == WAVE - 1) s_scan[wib].x = bin;
+                bin -= n;
+                __syncthreads();
+#pragma unroll
+                for (uint32_t w = 0; w < HIT_WAVES; ++w) {
+                    const uint32_t v = s_scan[w].x;
+                    bin += w < wib ? v : 0u;
+                    leaves += v;
+                }
+                leaves = __builtin_amdgcn_readfirstlane(leaves);
+#pragma unroll
+                for (uint32_t k = 0; k < HIT_SPAN_WPT; ++k) {
+                    const uint32_t w = HIT_SPAN_WPT * tid + k;
+                    before[w] = (uint16_t)bin;
+                    for (; own[k] != 0u; own[k] &= own[k] - 1u, ++bin) {
+                        const uint32_t leaf = w * 32u + (uint32_t)__builtin_ctz(own[k]);
+                        if (bin < HIT_BINS) s_blk[bin] = leaf;
+                        if (bin == HIT_BINS) s_from = base + leaf;
+                    }
+                }
+                __syncthreads();
+                // what has no bin waits
+                more = leaves > HIT_BINS || hi - base >= HIT_SPAN;
+                from = leaves > HIT_BINS ? __builtin_amdgcn_readfirstlane(s_from) : base + HIT_SPAN;
+#pragma unroll
+                for (uint32_t k = 0; k < PPT; ++k) {
+                    const uint32_t w = min(my_leaf[k] / 32u, HIT_SPAN_WORDS - 1u), sh = my_leaf[k] & 31u;
+                    const uint32_t bits = map[w], b = before[w] + (uint32_t)__popc(bits & ((1u << sh) - 1u));
+                    const bool in = my_leaf[k] < HIT_SPAN;
+                    if constexpr (FUSED) {
+                        const uint32_t up = w + 1 < HIT_SPAN_WORDS ? map[w + 1] : 0u;
+                        const uint32_t has = (uint32_t)(((uint64_t)up << 32 | bits) >> sh) & 0xFFFFu;
+                        my_bits[k] = in ? my_bits[k] & has : 0u;
+                        my_leaf[k] = b | has << 16;
+                    } else {
+                        my_leaf[k] = in ? b : NONE;
+                    }
+                    if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);     // few in flight: registers
+                }
+            }
+            // fused: body(bin, pair) for every child that has a bin
+            auto children = [&](auto body) {
+                auto each = [&](auto bin_of) {
+                    for (uint32_t c = 0; c < fu.nf; ++c)
+#pragma unroll
+                        for (uint32_t k = 0; k < PPT; ++k) {
+                            const uint32_t bin = bin_of(my_leaf[k], c);
+                            if ((my_bits[k] >> c & 1u) != 0u && bin < HIT_BINS) body(bin, k);
+                        }
+                };
+                if (wide)
+                    each([](uint32_t v, uint32_t c) { return (v & 0xFFFFu) + (uint32_t)__popc((v >> 16) & ((1u << c) - 1u)); });
+                else
+                    each([](uint32_t v, uint32_t c) { return v + c; });
+            };
+            // pairs per leaf; each pair's bin and its place in the leaf's run
+            // (fused: the place is taken when the triangle is put there)
+            if constexpr (FUSED)
+                children([&](uint32_t bin, uint32_t) { atomicAdd(&s_cnt[bin], 1u); });
+            else
+#pragma unroll
+            for (uint32_t k = 0; k < PPT; ++k) {
+                const uint32_t bin = my_leaf[k];
+                const bool ok = bin < HIT_BINS;
                 my_leaf[k] = NONE;
                 if (ok) my_leaf[k] = bin | atomicAdd(&s_cnt[bin], 1u) * HIT_BINS;
             }
             __syncthreads();
             // a thread's bins: places, whole blocks and remainders
-            uint32_t c[HIT_BPT], cnt_part = 0u, fulls = 0u;
+            uint32_t c[HIT_BPT], leaf[HIT_BPT], cnt_part = 0u, fulls = 0u;
 #pragma unroll
             for (uint32_t k = 0; k < HIT_BPT; ++k) {
-                c[k] = s_cnt[HIT_BPT * tid + k];
+                const uint32_t bin = HIT_BPT * tid + k;
+                leaf[k] = wide ? s_blk[bin] : bin;
+                c[k] = s_cnt[bin];
                 cnt_part += c[k] | (c[k] % G != 0u ? 1u << 16 : 0u);
                 fulls += c[k] / G;
             }
@@ -505,22 +616,17 @@ __global__ __launch_bounds__(HIT_THREADS, HIT_WAVES_PER_SIMD) void k_hit(hit_slo
                 s_cnt[bin] = first;
                 if (c[k] == 0u) continue;
                 uint32_t rest = c[k];
-                for (; rest >= G; rest -= G, first += G) s_blk[ex_f++] = first | (G - 1) << 13 | bin << 18;
-                if (rest) s_blk[part++] = first | (rest - 1) << 13 | bin << 18;
+                for (; rest >= G; rest -= G, first += G) s_blk[ex_f++] = first | (G - 1) << 12 | leaf[k] << 17;
+                if (rest) s_blk[part++] = first | (rest - 1) << 12 | leaf[k] << 17;
                 first += rest;
-                uint32_t rays = min(B, ns - (base + bin) * B);
-                if constexpr (BATCH) rays = min(rays, bd.node_info[base + bin] & INFO_COUNT_MASK);
+                uint32_t rays = min(B, ns - (base + leaf[k]) * B);
+                if constexpr (BATCH) rays = min(rays, bd.node_info[base + leaf[k]] & INFO_COUNT_MASK);
                 tests += (uint64_t)c[k] * rays;
             }
             __syncthreads();
-            if constexpr (FUSED) {
-                for (uint32_t c = 0; c < fu.nf; ++c)
-#pragma unroll
-                    for (uint32_t k = 0; k < PPT; ++k) {
-                        const uint32_t bin = my_leaf[k] + c - base;
-                        if ((my_bits[k] >> c & 1u) != 0u && bin < HIT_BINS) s_tri[atomicAdd(&s_cnt[bin], 1u)] = my_t[k];
-                    }
-            } else
+            if constexpr (FUSED)
+                children([&](uint32_t bin, uint32_t k) { s_tri[atomicAdd(&s_cnt[bin], 1u)] = my_t[k]; });
+            else
 #pragma unroll
             for (uint32_t k = 0; k < PPT; ++k)
                 if (my_leaf[k] != NONE) s_tri[s_cnt[my_leaf[k] % HIT_BINS] + my_leaf[k] / HIT_BINS] = my_t[k];
@@ -528,9 +634,9 @@ __global__ __launch_bounds__(HIT_THREADS, HIT_WAVES_PER_SIMD) void k_hit(hit_slo
             for (uint32_t b0 = wib * GPW; b0 < nblk; b0 += HIT_WAVES * GPW) {
                 const uint32_t bi = b0 + l / G;
                 const uint32_t e = s_blk[bi < nblk ? bi : 0u];
-                const uint32_t cnt = bi < nblk ? ((e >> 13) & 31u) + 1u : 0u;
-                const uint32_t slot = (base + (e >> 18)) * B + j;
-                const uint32_t t = j < cnt ? s_tri[(e & 0x1FFFu) + j] : m;
+                const uint32_t cnt = bi < nblk ? ((e >> 12) & 31u) + 1u : 0u;
+                const uint32_t slot = (base + (e >> 17)) * B + j;
+                const uint32_t t = j < cnt ? s_tri[(e & 0xFFFu) + j] : m;
                 const uint64_t cols = ballot(j < cnt);
                 const float4 f0 = buf_load4(ftri_r, t * 48u);
                 const float4 f1 = buf_load4(ftri_r, t * 48u + 16u);
