@@ -284,10 +284,12 @@ struct mask_type<16> {
     typedef uint16_t t;
 };
 
-// Many items of one part each come TOP_RUN at a time to a wave, neighbours in the
+// Many items of small meshes come TOP_RUN at a time to a wave, neighbours in the
 // pair list, so that their survivors, most of one tile, are added to its count at
 // once: traversal of 512x512 shadow rays, 180,224 items, 165 us one by one, 118
-// in twos, 100 in fours, 104 in eights (larger meshes, 206, 160, 169, 210).
+// in twos, 100 in fours, 104 in eights (larger meshes, 206, 160, 169, 210).  Not those
+// of larger meshes that have one part for want of item storage: 128x72 mixed rays,
+// one level, 178 us one by one, 230 in fours.
 constexpr uint32_t TOP_RUN = 4;
 
 // NF: the merge factor rounded up to a power of two.  Top-level pairs written
@@ -322,7 +324,7 @@ __global__ __launch_bounds__(256) void k_top_emit(const float4 *__restrict__ na,
     const uint64_t wave = (uint64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
     const uint64_t nwaves = (uint64_t)gridDim.x * (blockDim.x / WAVE);
     uint64_t tests = 0;
-    const uint64_t run = parts == 1 && n_items > 4096 ? TOP_RUN : 1u;
+    const uint64_t run = S.top_many == 1 && parts == 1 && n_items > 4096 ? TOP_RUN : 1u;
     const uint64_t lane_it = l / run * nwaves * run + l % run;
     for (uint64_t it0 = wave * run; it0 < n_items; it0 += nwaves * WAVE) {
         const uint64_t it = it0 + lane_it;
