@@ -182,6 +182,10 @@ __global__ void k_hit_pack(tri_verts V, uint32_t m, hit_tris_ws tri, sorted_rays
 // still name few of them (256 of 12,700 spanned on average, 128x72 mixed rays, 2 to
 // a leaf, merge factor 4, 8 levels): in windows of 1,024 leaves it was read 7
 // times, 324 us; by the leaves that have pairs once, 212.
+// Where a chunk has at most 256 leaves, each has several bins and the threads of
+// those cut its blocks.  With one bin a leaf, and its one thread to cut up to 1,024
+// blocks, pairs of few leaves took longest: 128x72 mixed rays, 4 to a leaf, 24 M
+// pairs, 4 leaves below a top node 372 us where 1,024 took 150; so 171 and 158.
 // Fused (640x360 mixed rays, 144 M level-2 pairs, 2.8 G tests): 5.4 ms with a
 // lane per (child, ray), 1.85 ms so.  A chunk of 2,048 level-2 pairs has 2,500
 // children there; 1,536 1.96 ms, 1,792 1.91, 2,560 2.17, 3,072 2.18 (more
@@ -195,6 +199,7 @@ constexpr uint32_t HIT_MIN_CHUNK = 64;                      // fewest
 constexpr uint32_t HIT_BPT = 4;                             // leaf bins per thread
 constexpr uint32_t HIT_BINS = HIT_THREADS * HIT_BPT;        // leaves binned per round
 constexpr uint32_t HIT_SPAN = 1u << 15;                     // leaves that a round's bins can lie in
+constexpr uint32_t HIT_COPIES = 8;                          // most bins of a leaf, as a power of two
 constexpr uint32_t HIT_QUEUE = 128;                         // queued items of a wave
 // registers for 5 workgroups per compute unit, 4 for the smallest groups (their
 // block words take the LDS of more)
@@ -468,6 +473,7 @@ __global__ __launch_bounds__(HIT_THREADS, hit_waves_per_simd(LG)) void k_hit(hit
             const uint32_t base = __builtin_amdgcn_readfirstlane(lo);
             hi = __builtin_amdgcn_readfirstlane(hi);
             const bool wide = base != NONE && hi - base >= HIT_BINS;
+            uint32_t used = min(hi - base + 1u, HIT_BINS);      // bins in use
             more = false;
             // the leaves counted from the round's first on
 #pragma unroll
@@ -539,6 +545,7 @@ __global__ __launch_bounds__(HIT_THREADS, hit_waves_per_simd(LG)) void k_hit(hit
                 // what has no bin waits
                 more = leaves > HIT_BINS || hi - base >= HIT_SPAN;
                 from = leaves > HIT_BINS ? __builtin_amdgcn_readfirstlane(s_from) : base + HIT_SPAN;
+                used = min(leaves, HIT_BINS);
 #pragma unroll
                 for (uint32_t k = 0; k < PPT; ++k) {
                     const uint32_t w = min(my_leaf[k] / 32u, HIT_SPAN_WORDS - 1u), sh = my_leaf[k] & 31u;
@@ -555,6 +562,9 @@ __global__ __launch_bounds__(HIT_THREADS, hit_waves_per_simd(LG)) void k_hit(hit
                     if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);     // few in flight: registers
                 }
             }
+            // few leaves: 2^copies bins each, by thread
+            const uint32_t copies = used > HIT_THREADS ? 0u : min((uint32_t)__builtin_clz((used - 1u) | 1u) - 22u, HIT_COPIES);
+            const uint32_t copy = tid & ((1u << copies) - 1u), bins = HIT_BINS >> copies;
             // fused: body(bin, pair) for every child that has a bin
             auto children = [&](auto body) {
                 auto each = [&](auto bin_of) {
@@ -562,7 +572,7 @@ __global__ __launch_bounds__(HIT_THREADS, hit_waves_per_simd(LG)) void k_hit(hit
 #pragma unroll
                         for (uint32_t k = 0; k < PPT; ++k) {
                             const uint32_t bin = bin_of(my_leaf[k], c);
-                            if ((my_bits[k] >> c & 1u) != 0u && bin < HIT_BINS) body(bin, k);
+                            if ((my_bits[k] >> c & 1u) != 0u && bin < bins) body(bin << copies | copy, k);
                         }
                 };
                 if (wide)
@@ -577,51 +587,100 @@ __global__ __launch_bounds__(HIT_THREADS, hit_waves_per_simd(LG)) void k_hit(hit
             else
 #pragma unroll
             for (uint32_t k = 0; k < PPT; ++k) {
-                const uint32_t bin = my_leaf[k];
-                const bool ok = bin < HIT_BINS;
+                const bool ok = my_leaf[k] < bins;
+                const uint32_t bin = my_leaf[k] << copies | copy;
                 my_leaf[k] = NONE;
                 if (ok) my_leaf[k] = bin | atomicAdd(&s_cnt[bin], 1u) * HIT_BINS;
             }
             __syncthreads();
-            // a thread's bins: places, whole blocks and remainders
-            uint32_t c[HIT_BPT], leaf[HIT_BPT], cnt_part = 0u, fulls = 0u;
-#pragma unroll
-            for (uint32_t k = 0; k < HIT_BPT; ++k) {
-                const uint32_t bin = HIT_BPT * tid + k;
-                leaf[k] = wide ? s_blk[bin] : bin;
-                c[k] = s_cnt[bin];
-                cnt_part += c[k] | (c[k] % G != 0u ? 1u << 16 : 0u);
-                fulls += c[k] / G;
-            }
-            uint32_t ex_cp = wave_scan_dpp(cnt_part), ex_f = wave_scan_dpp(fulls);
-            if (l == WAVE - 1) s_scan[wib] = make_uint2(ex_cp, ex_f);
-            ex_cp -= cnt_part;
-            ex_f -= fulls;
-            __syncthreads();
+            // places, whole blocks and remainders of the leaves
             uint32_t nfull = 0u, nblk = 0u;
+            auto count_tests = [&](uint32_t leaf, uint32_t pairs) {
+                uint32_t rays = min(B, ns - (base + leaf) * B);
+                if constexpr (BATCH) rays = min(rays, bd.node_info[base + leaf] & INFO_COUNT_MASK);
+                tests += (uint64_t)pairs * rays;
+            };
+            // exclusive sums over the workgroup of x and y; nfull and nblk: the
+            // totals of y, and of y and the high half of x
+            auto sums = [&](uint32_t &x, uint32_t &y) {
+                const uint32_t x0 = x, y0 = y;
+                x = wave_scan_dpp(x);
+                y = wave_scan_dpp(y);
+                if (l == WAVE - 1) s_scan[wib] = make_uint2(x, y);
+                x -= x0;
+                y -= y0;
+                __syncthreads();
+                nfull = nblk = 0u;
 #pragma unroll
-            for (uint32_t w = 0; w < HIT_WAVES; ++w) {
-                const uint2 v = s_scan[w];
-                ex_cp += w < wib ? v.x : 0u;
-                ex_f += w < wib ? v.y : 0u;
-                nfull += v.y;
-                nblk += v.x >> 16;
-            }
-            nfull = __builtin_amdgcn_readfirstlane(nfull);
-            nblk = __builtin_amdgcn_readfirstlane(nblk) + nfull;
-            uint32_t first = ex_cp & 0xFFFFu, part = nfull + (ex_cp >> 16);
+                for (uint32_t w = 0; w < HIT_WAVES; ++w) {
+                    const uint2 v = s_scan[w];
+                    x += w < wib ? v.x : 0u;
+                    y += w < wib ? v.y : 0u;
+                    nfull += v.y;
+                    nblk += v.x >> 16;
+                }
+                nfull = __builtin_amdgcn_readfirstlane(nfull);
+                nblk = __builtin_amdgcn_readfirstlane(nblk) + nfull;
+            };
+            if (copies) {
+                // a thread's four bins are of one leaf; it cuts the blocks that
+                // begin at their places, and thread x the remainder of leaf x
+                const uint32_t my_id = wide ? s_blk[tid] : tid;
+                uint32_t c[HIT_BPT], at = 0u, ex_f = 0u;
 #pragma unroll
-            for (uint32_t k = 0; k < HIT_BPT; ++k) {
-                const uint32_t bin = HIT_BPT * tid + k;
-                s_cnt[bin] = first;
-                if (c[k] == 0u) continue;
-                uint32_t rest = c[k];
-                for (; rest >= G; rest -= G, first += G) s_blk[ex_f++] = first | (G - 1) << 12 | leaf[k] << 17;
-                if (rest) s_blk[part++] = first | (rest - 1) << 12 | leaf[k] << 17;
-                first += rest;
-                uint32_t rays = min(B, ns - (base + leaf[k]) * B);
-                if constexpr (BATCH) rays = min(rays, bd.node_info[base + leaf[k]] & INFO_COUNT_MASK);
-                tests += (uint64_t)c[k] * rays;
+                for (uint32_t k = 0; k < HIT_BPT; ++k) {
+                    c[k] = s_cnt[HIT_BPT * tid + k];
+                    at += c[k];
+                }
+                sums(at, ex_f);
+                const uint32_t my0 = at;
+#pragma unroll
+                for (uint32_t k = 0; k < HIT_BPT; ++k) {
+                    s_cnt[HIT_BPT * tid + k] = at;
+                    at += c[k];
+                }
+                const uint32_t my1 = at;
+                if (tid == HIT_THREADS - 1) s_from = my1;       // the chunk's pairs
+                __syncthreads();
+                const uint32_t all = s_from, first = tid < bins ? s_cnt[tid << copies] : all;
+                const uint32_t n = (tid + 1u < bins ? s_cnt[(tid + 1u) << copies] : all) - first;
+                uint32_t part = n % G != 0u ? 1u << 16 : 0u;
+                ex_f = n / G;
+                sums(part, ex_f);
+                if (tid < bins) {
+                    s_tri[tid] = ex_f;
+                    s_tri[HIT_THREADS + tid] = first | (n / G) << 16;
+                    s_tri[2 * HIT_THREADS + tid] = my_id;
+                }
+                if (n) count_tests(my_id, n);
+                if (n % G) s_blk[nfull + (part >> 16)] = (first + n / G * G) | (n % G - 1) << 12 | my_id << 17;
+                __syncthreads();
+                const uint32_t x = (HIT_BPT * tid) >> copies, f = s_tri[HIT_THREADS + x], to = s_tri[x];
+                const uint32_t leaf_first = f & 0xFFFFu, leaf_id = s_tri[2 * HIT_THREADS + x];
+                for (uint32_t k = (my0 - leaf_first + G - 1) / G; k < f >> 16 && leaf_first + k * G < my1; ++k)
+                    s_blk[to + k] = (leaf_first + k * G) | (G - 1) << 12 | leaf_id << 17;
+            } else {
+                uint32_t c[HIT_BPT], leaf[HIT_BPT], ex_cp = 0u, ex_f = 0u;
+#pragma unroll
+                for (uint32_t k = 0; k < HIT_BPT; ++k) {
+                    const uint32_t bin = HIT_BPT * tid + k;
+                    leaf[k] = wide ? s_blk[bin] : bin;
+                    c[k] = s_cnt[bin];
+                    ex_cp += c[k] | (c[k] % G != 0u ? 1u << 16 : 0u);
+                    ex_f += c[k] / G;
+                }
+                sums(ex_cp, ex_f);
+                uint32_t first = ex_cp & 0xFFFFu, part = nfull + (ex_cp >> 16);
+#pragma unroll
+                for (uint32_t k = 0; k < HIT_BPT; ++k) {
+                    s_cnt[HIT_BPT * tid + k] = first;
+                    if (c[k] == 0u) continue;
+                    uint32_t rest = c[k];
+                    for (; rest >= G; rest -= G, first += G) s_blk[ex_f++] = first | (G - 1) << 12 | leaf[k] << 17;
+                    if (rest) s_blk[part++] = first | (rest - 1) << 12 | leaf[k] << 17;
+                    first += rest;
+                    count_tests(leaf[k], c[k]);
+                }
             }
             __syncthreads();
             if constexpr (FUSED)

@@ -1,8 +1,9 @@
-"""Final tests of chunks whose pairs lie in leaves far apart: more leaves
+"""Final tests of chunks whose pairs lie in leaves far apart -- more leaves
 between the first and the last than there are bins, so that only the leaves that
-have pairs get one -- at both sides of the number of bins, of the span that a
-round covers and of a chunk, stored, packed, fused and batched; every hit and
-counter exactly the oracle's.  And a bound on what such chunks cost."""
+have pairs get one -- or in few leaves, which get many bins each: at both sides
+of the number of bins, of the span that a round covers and of a chunk, stored,
+packed, fused and batched; every hit and counter exactly the oracle's.  And
+bounds on what such chunks cost."""
 import dataclasses
 
 import numpy as np
@@ -68,6 +69,36 @@ def test_spread_leaves_match_oracle(B, leaves, used, n_pairs):
     assert (int(meta.final_u_pass), int(meta.final_uv_pass)) == (stages["u"], stages["uv"])
 
 
+# leaves in all, those that have pairs; `most`: the share of the pairs in one of them
+@pytest.mark.parametrize("B,leaves,used,most,n_pairs", [
+    (16, 40, 1, 0.0, 9000), (4, 1, 1, 0.0, 5500001), (4, 5, 4, 0.0, 5500000), (2, 5, 5, 0.9, 5500000),
+    (8, 17, 16, 0.0, 5500000), (16, 17, 17, 0.5, 5500000), (1, 70, 64, 0.0, 5400000), (3, 256, 255, 0.99, 5500000),
+    (32, 256, 256, 0.0, 1400000), (4, 257, 257, 0.5, 5500000), (4, 9000, 200, 0.3, 5500000), (4, 40000, 3, 0.0, 70000)])
+def test_few_leaves_match_oracle(B, leaves, used, most, n_pairs):
+    import gpu_util
+    rng = np.random.default_rng(B + leaves)
+    n = leaves * B - (B > 1)
+    sc, rays = _scene(rng, n, 97)
+    some = np.sort(rng.choice(leaves, used, replace=False))
+    some[-1] = leaves - 1
+    node = np.where(rng.random(n_pairs) < most, some[used // 2], some[rng.integers(0, used, n_pairs)])
+    pairs = rng.integers(0, 97, n_pairs).astype(np.uint32), node.astype(np.uint32)
+    ids = rng.permutation(n).astype(np.uint32)
+    print(f"[hit few] B={B} {used} of {leaves} leaves, {n_pairs} pairs", flush=True)
+    stages = {}
+    ref = O.closest_hit(rays, ids, B, pairs, sc, 1e-4, stages=stages)
+    g, meta = gpu_util.gpu_closest_hit(rays, ids, B, pairs, sc, 1e-4)
+    for a, b in zip(g, ref):
+        assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
+    assert int(meta.final_tests) == int(np.minimum(B, n - pairs[1].astype(np.int64) * B).sum())
+    assert (int(meta.final_u_pass), int(meta.final_uv_pass)) == (stages["u"], stages["uv"])
+
+
+@pytest.mark.parametrize("B,F,n", [(4, 4, 1), (8, 4, 2), (2, 2, 3), (32, 8, 2)])
+def test_flat_hierarchies_match_oracle(B, F, n):
+    test_wide_hierarchies_match_oracle(B, F, n)
+
+
 @pytest.mark.parametrize("B,F,n", [(4, 4, 7), (2, 4, 8), (2, 16, 4), (8, 2, 12), (1, 8, 6)])
 def test_wide_hierarchies_match_oracle(B, F, n):
     import gpu_util
@@ -91,13 +122,15 @@ def test_wide_hierarchies_match_oracle(B, F, n):
                 assert np.array_equal(np.asarray(a).view(np.uint32), np.asarray(b).view(np.uint32)), fused
 
 
-def _hit_us(leaves, stride, idx, tri, B=4):
+def _hit_us(leaves, stride, idx, tri, B=4, tmax=None):
     """Final tests of the pairs (tri[i], leaf idx[i] * stride)."""
     import gpu_util
     import torch
     from paper_2312_06538_amd import crsh as X
     n = leaves * stride * B
     sc, rays = _scene(np.random.default_rng(1), n, 500)
+    if tmax is not None:
+        rays["tmax"][:] = tmax
     r = {k: gpu_util.dev_f32(rays[k]) for k in gpu_util.RAY_KEYS}
     c_r = X.Rays(*[r[k].data_ptr() for k in gpu_util.RAY_KEYS], None, n)
     ids = torch.arange(n, dtype=torch.int32, device="cuda")
@@ -134,3 +167,16 @@ def test_spread_leaves_cost():
     near, far = _hit_us(256, 1, idx, tri), _hit_us(256, 64, idx, tri)
     print(f"[hit spans] {near:.0f} us side by side, {far:.0f} us spread", flush=True)
     assert far < 1.7 * near
+
+
+def test_few_leaves_cost():
+    """Pairs of 4 leaves and of 512, with no hits (their minima would meet at the
+    few rays): 1.7 times as long with one bin a leaf, no longer with 256 each."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    k = 16 << 20
+    idx = torch.randint(0, 512, (k,), device="cuda", generator=gen)
+    tri = torch.randint(0, 500, (k,), device="cuda", generator=gen, dtype=torch.int32)
+    many, few = _hit_us(512, 1, idx, tri, tmax=0.0), _hit_us(4, 1, idx // 128, tri, tmax=0.0)
+    print(f"[hit few] {many:.0f} us in 512 leaves, {few:.0f} us in 4", flush=True)
+    assert few < 1.6 * many
