@@ -294,7 +294,7 @@ inline hit_tris_ws carve_hit_tris(void *at, uint32_t m)
 struct hit_slots_ws {
     float4 *org;                 // per slot: origin, tmax
     float4 *dir;                 // per slot: direction, its length
-    float4 *mom;                 // per slot: origin x direction, |origin| |direction|
+    float4 *mom;                 // per slot: the moment o x direction, |o| |direction| (o: the origin from a point of the scene)
     unsigned long long *keys;    // per slot (batched form)
     uint64_t *part;              // per workgroup of k_hit: its three counts
     uint32_t slots;

@@ -15,8 +15,8 @@
 //              the same test, write the result at the ray id.
 // Ray slots: k_hit reads the rays of leaf l at slots l * B + j, j < B, of
 // three packed arrays of 16 bytes a slot: (origin, tmax), (direction, its
-// length) and (origin x direction, |origin| |direction|); the interval start
-// t_min is the frame's.  In the plain form slot s is sorted ray s.  In the
+// length) and, with the origin o taken from a point of the scene, (o x direction,
+// |o| |direction|); the interval start t_min is the frame's.  In the plain form slot s is sorted ray s.  In the
 // batched form a frame's rays are bundled B at a time from its own first ray,
 // so only a frame's last leaf can hold fewer than B rays; its slots are padded
 // (zeros, a length of -1) and the closest-hit keys are kept by slot, so the
@@ -29,34 +29,55 @@ namespace crsh {
 
 // The filter.  The test accepts u = a / det in [0, 1] with
 // a = (O - v0) . (D x e2) and det = e1 . (D x e2), i.e. |2 a - det| <= |det|.
-// With the ray's moment M = O x D both are sums of products of one ray vector
-// and one triangle vector,
-//     2 a - det = M . (2 e2) - D . (2 e2 x v0 + e2 x e1),   det = D . (e2 x e1),
+// With o = O - C and w = v0 - C for a point C of the scene, and the ray's moment
+// M = o x D, both are sums of products of one ray vector and one triangle vector,
+//     2 a - det = M . (2 e2) - D . (2 e2 x w + e2 x e1),   det = D . (e2 x e1),
 // so a leaf's rays against its triangles are a small matrix product.  A pair
 // is rejected when |2 a - det| - |det| > T with
-//     T = 2^-17 |e2| |D| (|O| + |v0| + |e1|).
+//     T = 2^-18 |e2| |D| (|o| + |w| + |e1|).
 // Error bound (u = 2^-24, first order): the two forms above come out within
-// u |e2||D| (19 |O| + 21 |v0| + 10.5 |e1|) and 6.5 u |e1||e2||D|, the test's
-// own a and det within 7.5 u |e2||D| (|O| + |v0|) and 6.5 u |e1||e2||D|, and
-// 16 u |e1||e2||D| more keeps a / det 2^-21 away from 0 and 1, so that the
-// rounded quotient falls on the same side: together at most
-// u |e2||D| (34 |O| + 36 |v0| + 46 |e1|), against T's 128 u.  Where a length
+// u |e2||D| (21 |o| + 23 |w| + 10.5 |e1|), of which rounding o and w is 2 |o| and
+// 2 |w|, and 6.5 u |e1||e2||D|; the test's own a and det within
+// 7.5 u |e2||D| (|o| + |w|) and 6.5 u |e1||e2||D|; and 16 u |e1||e2||D| more keeps
+// a / det 2^-21 away from 0 and 1, so that the rounded quotient falls on the same
+// side: together at most u |e2||D| (36 |o| + 38 |w| + 46 |e1|), against T's 64 u.
+// What T is next to |e2||D||e1| decides how much is rejected: at distances of 2^12
+// edges a few tests in a hundred that fail are made in full, at 2^18 all.  So C
+// keeps a scene far from the origin as cheap as one around it (512x512 reflections,
+// a scene 60 across moved by 10^5: final tests 2.15 ms with C = 0 and T twice as
+// large, 0.88 so, 0.73 around the origin).  Rays from far away stay dearer: shadow
+// rays of a scene 100 across with its light at 10^5 0.43 ms (0.35 with a lane a test
+// and no filter, 0.53 with T twice as large), at 10^6 2.1 (1.3, 2.5).  Where a length
 // is above 2^40, or |D| below 2^-40, or one is a NaN, a product could overflow or
 // underflow: such a triangle has zero vectors and a large T, such a ray a mark,
 // and neither is ever rejected, which takes 1.7 times as long as a test did
 // without the filter.  In these bounds no product of the filter or of the test's
-// a and det exceeds 2^122, and T is at least 2^-17 2^-30 2^-40 (3 2^-30) > 2^-116
+// a and det exceeds 2^122, and T is at least 2^-18 2^-30 2^-40 (3 2^-30) > 2^-117
 // (FLT_TINY), against the at most 2^-122 that products below the normal range
 // lose in the nine terms of 2 a - det and det.
-constexpr float FLT_REL = 0x1p-17f;
+constexpr float FLT_REL = 0x1p-18f;
 constexpr float FLT_TINY = 0x1p-30f;       // added to lengths: their squares may underflow
 constexpr float FLT_LONG = 0x1p40f, FLT_SHORT = 0x1p-40f;
 constexpr float FLT_KEEP = -2.0f;          // |O||D| of a ray that the filter may not reject
 
-// Per triangle: (2 e2, E0), (-(2 e2 x v0 + e2 x e1), E1), (e2 x e1, 0) with
-// T = E0 |O||D| + E1 |D|.  Entry m pads a leaf's last triangles: its T is
+// C: by coordinate the middle one of three vertices of triangles a quarter, half
+// and three quarters through the scene, so that few outliers do not matter.  Any C
+// is right; in a batch of frames it is the same for all.
+__device__ __forceinline__ f3 filter_centre(const tri_verts &V, uint32_t m)
+{
+    if (m == 0u) return mk(0.0f, 0.0f, 0.0f);
+    const uint32_t a = m / 4, b = m / 2, d = m - 1u - m / 4;
+    const f3 c = mk(__builtin_amdgcn_fmed3f(V.v[0][a], V.v[0][b], V.v[0][d]),
+                    __builtin_amdgcn_fmed3f(V.v[1][a], V.v[1][b], V.v[1][d]),
+                    __builtin_amdgcn_fmed3f(V.v[2][a], V.v[2][b], V.v[2][d]));
+    const bool ok = fabsf(c.x) <= FLT_LONG && fabsf(c.y) <= FLT_LONG && fabsf(c.z) <= FLT_LONG;     // no NaN
+    return ok ? c : mk(0.0f, 0.0f, 0.0f);
+}
+
+// Per triangle: (2 e2, E0), (-(2 e2 x w + e2 x e1), E1), (e2 x e1, 0) with
+// T = E0 |o||D| + E1 |D|.  Entry m pads a leaf's last triangles: its T is
 // negative for every ray (rejected).
-__device__ __forceinline__ void put_tri(const tri_verts &V, uint32_t t, uint32_t m, const hit_tris_ws &out)
+__device__ __forceinline__ void put_tri(const tri_verts &V, uint32_t t, uint32_t m, f3 centre, const hit_tris_ws &out)
 {
     float4 *const tri = out.tri + 3 * (size_t)t, *const ftri = out.ftri + 3 * (size_t)t;
     if (t == m) {
@@ -71,11 +92,12 @@ __device__ __forceinline__ void put_tri(const tri_verts &V, uint32_t t, uint32_t
     tri[0] = make_float4(a.x, a.y, a.z, e1.x);
     tri[1] = make_float4(e1.y, e1.z, e2.x, e2.y);
     tri[2] = make_float4(e2.z, 0.0f, 0.0f, 0.0f);
-    const float la = len(a) + FLT_TINY, l1 = len(e1) + FLT_TINY, l2 = len(e2) + FLT_TINY;
+    const f3 ac = a - centre;
+    const float la = len(ac) + FLT_TINY, l1 = len(e1) + FLT_TINY, l2 = len(e2) + FLT_TINY;
     const bool ok = la <= FLT_LONG && l1 <= FLT_LONG && l2 <= FLT_LONG;
     const f3 z = mk(0.0f, 0.0f, 0.0f);
     const f3 n = ok ? cross(e2, e1) : z;
-    const f3 w = ok ? cross(e2, a) * 2.0f + n : z;
+    const f3 w = ok ? cross(e2, ac) * 2.0f + n : z;
     const f3 e = ok ? e2 * 2.0f : z;
     ftri[0] = make_float4(e.x, e.y, e.z, ok ? FLT_REL * l2 : 0.0f);
     ftri[1] = make_float4(-w.x, -w.y, -w.z, ok ? FLT_REL * l2 * (la + l1) : 0x1p60f);
@@ -99,12 +121,13 @@ __device__ __forceinline__ uint32_t batch_slots(const crsh_meta *meta, uint32_t 
 }
 
 // A ray's slot: origin and tmax; direction and the |D| of the filter's T;
-// O x D and the |O||D| of T, or FLT_KEEP in its place.
-__device__ __forceinline__ void put_slot(const hit_slots_ws &hs, uint32_t p, f3 O, f3 D, float tmax)
+// o x D and the |o||D| of T, or FLT_KEEP in its place.
+__device__ __forceinline__ void put_slot(const hit_slots_ws &hs, uint32_t p, f3 O, f3 D, f3 centre, float tmax)
 {
-    const float lo = len(O) + FLT_TINY, ld = len(D);
+    const f3 oc = O - centre;
+    const float lo = len(oc) + FLT_TINY, ld = len(D);
     const bool ok = lo <= FLT_LONG && ld <= FLT_LONG && ld >= FLT_SHORT;
-    const f3 M = cross(O, D);
+    const f3 M = cross(oc, D);
     hs.org[p] = make_float4(O.x, O.y, O.z, tmax);
     hs.dir[p] = make_float4(D.x, D.y, D.z, ok ? ld : 1.0f);
     hs.mom[p] = make_float4(M.x, M.y, M.z, ok ? lo * ld : FLT_KEEP);
@@ -119,6 +142,7 @@ __global__ void k_hit_pack(tri_verts V, uint32_t m, hit_tris_ws tri, sorted_rays
                            uint32_t ray_cap, uint32_t B, batch_dev bd, hit_slots_ws hs)
 {
     const uint32_t stride = gridDim.x * blockDim.x, gid = blockIdx.x * blockDim.x + threadIdx.x;
+    const f3 centre = filter_centre(V, m);
     const uint32_t n = min(meta->n_rays, ray_cap);
     const uint32_t ns = BATCH ? batch_slots(meta, B, hs.slots) : n;
     for (uint32_t p = gid; p < ns; p += stride) {
@@ -133,7 +157,7 @@ __global__ void k_hit_pack(tri_verts V, uint32_t m, hit_tris_ws tri, sorted_rays
             hs.keys[p] = ~0ull;
         }
         if (ok) {
-            put_slot(hs, p, mk(R.ox[s], R.oy[s], R.oz[s]), mk(R.dx[s], R.dy[s], R.dz[s]),
+            put_slot(hs, p, mk(R.ox[s], R.oy[s], R.oz[s]), mk(R.dx[s], R.dy[s], R.dz[s]), centre,
                      BATCH ? slot_tmax(R.tmax[s]) : R.tmax[s]);
         } else {
             hs.org[p] = make_float4(0.0f, 0.0f, 0.0f, __uint_as_float(PAD_SLOT));
@@ -141,7 +165,7 @@ __global__ void k_hit_pack(tri_verts V, uint32_t m, hit_tris_ws tri, sorted_rays
             hs.mom[p] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         }
     }
-    for (uint32_t t = gid; t <= m; t += stride) put_tri(V, t, m, tri);
+    for (uint32_t t = gid; t <= m; t += stride) put_tri(V, t, m, centre, tri);
 }
 
 // Slots in use: the plain form's sorted rays, or B per level-1 node.  PACKED:

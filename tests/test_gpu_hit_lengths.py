@@ -110,3 +110,35 @@ def test_short_and_long_directions_cost():
     unit, short, long = _hit_us(20.0, 1.0, 1.0), _hit_us(20.0, 1.0, 2.0 ** -20), _hit_us(20.0, 1.0, 2.0 ** 30)
     print(f"[hit lengths] {unit:.0f} us, 2^-20 {short:.0f}, 2^30 {long:.0f}", flush=True)
     assert short < 1.5 * unit and long < 1.5 * unit
+
+
+def test_far_scene_cost():
+    """A scene takes no longer 2^20 from the origin than around it, where the
+    filter's bound grew with the distance to more than the scene's size."""
+    near, far = _hit_us(20.0, 2.0, 1.0), _hit_us(20.0, 2.0, 1.0, at=2.0 ** 20)
+    print(f"[hit lengths] at the origin {near:.0f} us, 2^20 from it {far:.0f}", flush=True)
+    assert far < 1.5 * near
+
+
+@pytest.mark.parametrize("at,m,odd", [(3e4, 400, 0), (-1e6, 400, 0), (2.0 ** 39, 400, 0), (5e3, 1, 0), (5e3, 2, 0),
+                                      (5e3, 3, 0), (7e3, 5, 1), (7e3, 400, 1), (7e3, 400, 2), (0.0, 400, 3)])
+def test_far_scenes_match_oracle(at, m, odd):
+    """Scenes far from the origin, of few triangles, and with triangles far from
+    the others, infinite or no numbers where the filter takes its centre from."""
+    import gpu_util
+    B, n, n_pairs = 8, 3000, 30000
+    sc, rays, pairs = _case(m + odd, n, m, n_pairs, B, max(20.0, abs(at) / 4096), max(0.2, abs(at) / 65536), 1.0, at)
+    for k, t in enumerate((m // 4, m // 2, m - 1 - m // 4)):
+        if odd == 1 and k != 1 or odd == 3:
+            sc.tris[t] *= np.float32([1e7, 1e30, -1e7][k])
+        if odd == 2:
+            sc.tris[t, 0, k] = [np.nan, np.inf, -np.inf][k]
+    stages = {}
+    ids = np.arange(n, dtype=np.uint32)
+    with np.errstate(all="ignore"):
+        ref = O.closest_hit(rays, ids, B, pairs, sc, 1e-4, stages=stages)
+    g, meta = gpu_util.gpu_closest_hit(rays, ids, B, pairs, sc, 1e-4)
+    print(f"[hit lengths] at {at} m={m} odd={odd}: u {stages['u']} hits {(ref[0] >= 0).sum()}", flush=True)
+    for a, b in zip(g, ref):
+        assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
+    assert (int(meta.final_u_pass), int(meta.final_uv_pass)) == (stages["u"], stages["uv"])
