@@ -533,10 +533,17 @@ void crsh_graph_destroy(crsh_graph *g);
 
 /* Instrumentation.  Arms a one-shot timer: the `occurrence`-th launch
  * (0-based, counted from this call, in the calling thread) of the library
- * kernel named `kernel` (e.g. "k_hit", "k_level", "k_sort_pass") is
- * bracketed by hipEventRecord(start) and hipEventRecord(stop) on the stream
- * it is launched on.  The events are owned by the caller.  Returns
- * CRSH_ERR_INVALID for a NULL name or event. */
+ * kernel named `kernel` is bracketed by hipEventRecord(start) and
+ * hipEventRecord(stop) on the stream it is launched on.  Names: "k_hash_count",
+ * "k_hash_emit", "k_sort_hist", "k_sort_pass", "k_cs_heads", "k_cs_expand",
+ * "k_build_leaf", "k_top_count", "k_top_emit", "k_level", "k_hit",
+ * "k_hit_final", "k_hit_backward".  A launch that does several kernels' work
+ * answers to each of their names: "k_permute" is k_build_leaf, "k_level_emit" a
+ * "k_level" that writes a level's pairs, and a sort in one launch (capacities of
+ * at most 12,288) is "k_sort_hist" and all of its "k_sort_pass"es.  The timer
+ * stays armed until such a launch comes, or the next call arms another.  The
+ * events are owned by the caller.  Returns CRSH_ERR_INVALID for a NULL name or
+ * event. */
 crsh_status crsh_profile_next(const char *kernel, int32_t occurrence, hipEvent_t start, hipEvent_t stop);
 
 #ifdef __cplusplus

@@ -37,10 +37,13 @@ struct prof_state {
 };
 static thread_local prof_state g_prof = {"", 0, nullptr, nullptr, false};
 
-bool prof_begin(const char *kernel, hipStream_t s)
+bool prof_begin(const char *kernel, hipStream_t s, int32_t launches)
 {
     if (!g_prof.armed || strcmp(kernel, g_prof.name) != 0) return false;
-    if (g_prof.remaining-- > 0) return false;
+    if (g_prof.remaining >= launches) {
+        g_prof.remaining -= launches;
+        return false;
+    }
     (void)hipEventRecord(g_prof.start, s);
     return true;
 }

@@ -397,7 +397,7 @@ crsh_status build_launch(const crsh_rays *rays, const uint32_t *sorted_ids, int3
     uint64_t cnt = ((uint64_t)cap + bundle - 1) / bundle + extra;
     uint32_t g;
     {
-        prof_scope ps("k_build_leaf", stream);
+        prof_scope ps("k_build_leaf", stream), pp("k_permute", stream);
 #define CRSH_LEAF(NB)                                                                                      \
     (g = (uint32_t)std::max<uint64_t>((cnt + LEAF_RAYS / NB - 1) / (LEAF_RAYS / NB), 1),                   \
      bd ? k_build_leaf<NB, true><<<g, LEAF_THREADS, 0, stream>>>(ri, sorted_ids, ro, bundle, merge, levels, nd, meta, \

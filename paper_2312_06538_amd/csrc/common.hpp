@@ -385,14 +385,16 @@ uint32_t resident_grid(const void *f, int threads, uint64_t want);
 uint32_t resident_blocks(const void *f, int threads);
 
 // One-shot kernel timer (crsh_profile_next): prof_begin returns true when
-// this launch is the armed one and has recorded the start event.
-bool prof_begin(const char *kernel, hipStream_t s);
+// this launch is the armed one and has recorded the start event.  A launch that
+// does the work of several counts as that many (launches), and under each of
+// their names in a scope of its own.
+bool prof_begin(const char *kernel, hipStream_t s, int32_t launches = 1);
 void prof_end(bool armed, hipStream_t s);
 
 struct prof_scope {
     bool on;
     hipStream_t s;
-    prof_scope(const char *k, hipStream_t st) : on(prof_begin(k, st)), s(st) {}
+    prof_scope(const char *k, hipStream_t st, int32_t launches = 1) : on(prof_begin(k, st, launches)), s(st) {}
     ~prof_scope() { prof_end(on, s); }
 };
 

@@ -571,7 +571,7 @@ crsh_status sort_launch(const uint32_t *keys_in, const uint32_t *ids_in, const u
 
     sort_bufs b{keys_in, ids_in, keys_out, ids_out, kalt, valt};
     if (capacity && capacity <= ONE_THREADS * ONE_ITEMS) {
-        prof_scope ps("k_sort_pass", stream);
+        prof_scope ps("k_sort_pass", stream, (int32_t)passes), ph("k_sort_hist", stream);
         if (capacity <= ONE_THREADS * 4)
             k_sort_one<4><<<1, ONE_THREADS, 0, stream>>>(b, frame_of, meta, capacity);
         else if (capacity <= ONE_THREADS * 8)

@@ -1567,7 +1567,7 @@ static crsh_status traverse_run(const crsh_nodes *nodes, const crsh_scene *scene
         uint64_t run = (uint64_t)nf;
         for (int k = L - 1; k < (int)top_levels && run <= COUNT_WINDOW; ++k) run *= Fu;
         const bool st = run <= COUNT_WINDOW;
-        prof_scope ps("k_level", stream);
+        prof_scope ps("k_level", stream), pe("k_level_emit", stream);
 #define CRSH_STEP(NF, BT, PK, TE, ST)                                                                             \
     {                                                                                                             \
         const uint32_t rb = resident_blocks((const void *)k_level_step<NF, BT, PK, TE, ST>, STEP_THREADS);                      \
