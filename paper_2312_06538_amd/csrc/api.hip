@@ -8,8 +8,6 @@
 
 #include "common.hpp"
 
-#include <vector>
-
 namespace crsh {
 
 static thread_local char g_err[512] = "";
@@ -56,7 +54,8 @@ void prof_end(bool armed, hipStream_t s)
 }
 
 // A constant of the device and the kernel, asked for once per thread: the
-// query takes longer than a launch.
+// query takes longer than a launch.  A thread keeps the last 64 (a frame has some
+// ten), in place: nothing here may throw.
 uint32_t resident_blocks(const void *f, int threads)
 {
     struct known {
@@ -64,15 +63,19 @@ uint32_t resident_blocks(const void *f, int threads)
         const void *f;
         uint32_t blocks;
     };
-    static thread_local std::vector<known> seen;
+    constexpr uint32_t KEPT = 64;
+    static thread_local known seen[KEPT];
+    static thread_local uint32_t asked = 0;
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
-    for (const known &k : seen)
-        if (k.dev == dev && k.f == f && k.threads == threads) return k.blocks;
+    for (uint32_t k = 0; k < std::min(asked, KEPT); ++k)
+        if (seen[k].f == f && seen[k].dev == dev && seen[k].threads == threads) return seen[k].blocks;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, threads, 0) != hipSuccess || per_cu <= 0) return 0;
-    seen.push_back({dev, threads, f, (uint32_t)cus * (uint32_t)per_cu});
-    return seen.back().blocks;
+    known &k = seen[asked % KEPT];
+    k = known{dev, threads, f, (uint32_t)cus * (uint32_t)per_cu};
+    asked = asked + 1 < 2 * KEPT ? asked + 1 : KEPT;
+    return k.blocks;
 }
 
 uint32_t resident_grid(const void *f, int threads, uint64_t want)
