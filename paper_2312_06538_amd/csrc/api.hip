@@ -80,8 +80,14 @@ uint32_t resident_blocks(const void *f, int threads)
 
 uint32_t resident_grid(const void *f, int threads, uint64_t want)
 {
-    const uint64_t g = std::min<uint64_t>(std::max(resident_blocks(f, threads), 1u), want);
-    return g ? (uint32_t)g : 1u;
+    uint32_t blocks = resident_blocks(f, threads);
+    if (!blocks) {              // occupancy unknown: one per compute unit
+        int dev = 0, cus = 0;
+        if (hipGetDevice(&dev) == hipSuccess &&
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
+            blocks = (uint32_t)cus;
+    }
+    return (uint32_t)std::max<uint64_t>(std::min<uint64_t>(blocks, want), 1u);
 }
 
 size_t sort_ws_bytes(uint32_t cap)

@@ -1,6 +1,7 @@
 """The occupancy of persistent kernels, asked for once per thread, device and
-kernel: kept without allocating (an exception must not cross the C interface)
-and right for more kernels than are kept.  Runs the built library's own lookup on the CPU,
+kernel: kept without allocating (an exception must not cross the C interface),
+right for more kernels than are kept, and a grid of a workgroup per compute unit
+where the occupancy is unknown.  Runs the built library's own lookup on the CPU,
 the HIP queries replaced."""
 import subprocess
 
@@ -28,6 +29,7 @@ int hipDeviceGetAttribute(int *v, int, int) { *v = 256; return 0; }
 int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *f, int threads, size_t)
 {
     ++g_asked;
+    if (g_per_cu < 0) return 1;
     *n = g_per_cu + (int)((uintptr_t)f % 3) + threads / 256;
     return 0;
 }
@@ -37,7 +39,8 @@ int main(int, char **argv)
     void *h = dlopen(argv[1], RTLD_NOW);
     if (!h) { puts(dlerror()); return 2; }
     auto blocks = (uint32_t(*)(const void *, int))dlsym(h, "_ZN4crsh15resident_blocksEPKvi");
-    if (!blocks) { puts("no lookup"); return 2; }
+    auto grid = (uint32_t(*)(const void *, int, uint64_t))dlsym(h, "_ZN4crsh13resident_gridEPKvim");
+    if (!blocks || !grid) { puts("no lookup"); return 2; }
     g_full = true;
     try {
         for (int round = 0; round < 3; ++round)
@@ -49,6 +52,11 @@ int main(int, char **argv)
         const int before = g_asked;
         for (int k = 0; k < 100; ++k) blocks((const void *)777, 256);
         if (g_asked - before > 1) { printf("asked %d times\n", g_asked - before); return 4; }
+        g_per_cu = -1;
+        if (grid((const void *)888, 256, 100000) != 256u || grid((const void *)888, 256, 7) != 7u) {
+            printf("unknown: %u\n", grid((const void *)888, 256, 100000));
+            return 5;
+        }
     } catch (const std::bad_alloc &) {
         puts("an exception left the lookup");
         return 1;
