@@ -363,7 +363,7 @@ uint32_t hit_pairs_launch(const hit_tris_ws &tri, const hit_slots_ws &hs, const 
 uint32_t hit_masked_launch(const hit_tris_ws &tri, const hit_slots_ws &hs, const crsh_pairs *level2,
                            const uint32_t *mask, int32_t merge, int32_t bundle, const crsh_scene *scene, float t_min,
                            crsh_hits *hits, crsh_meta *meta, const batch_dev *bd, int32_t hit_block, uint32_t parts,
-                           hipStream_t stream);
+                           uint32_t *rest, uint32_t *n_rest, hipStream_t stream);
 // parts: workgroups of the k_hit launch before (hit_pairs_launch's result)
 void hit_final_launch(const crsh_rays *sorted, const uint32_t *sorted_ids, const float4 *tri,
                       const hit_slots_ws &hs, int32_t bundle, const crsh_scene *scene, float t_min,

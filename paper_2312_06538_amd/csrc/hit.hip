@@ -239,16 +239,30 @@ constexpr uint32_t HIT_SPAN_WORDS = HIT_SPAN / 32;
 constexpr uint32_t HIT_SPAN_WPT = HIT_SPAN_WORDS / HIT_THREADS;
 static_assert(HIT_SPAN_WORDS + HIT_SPAN_WORDS / 2 <= HIT_CHUNK && HIT_SPAN_WPT * HIT_THREADS == HIT_SPAN_WORDS, "bitmap");
 
-// What the pairs are.  Fused: level-2 pairs and a pass bit per child (the
-// level-1 pairs are never stored): pair q keeps child j (leaf first + j, first
-// = node * F or the build's record) when bit q * nf + j of `mask` is set.
+// What the pairs are.  Fused and listed: level-2 pairs and a pass bit per child
+// (the level-1 pairs are never stored): pair q keeps child j (leaf first + j,
+// first = node * F or the build's record) when bit q * nf + j of `mask` is set.
+// Fused (nf <= 4): every thread walks the children of its pairs.  Listed: the
+// children kept, few of many, are listed in LDS first, and a chunk with more than
+// hit_later() of them -- where nodes are hardly ever culled, up to 32,768 -- is left,
+// as tiles of HIT_TILE pairs, to another launch (`rest`, `n_rest`; deferred: this
+// is that launch), so that no workgroup is long alone with one.
 // parts: workgroups of the launch before, whose counts stay.
-enum { HIT_STORED, HIT_PACKED, HIT_FUSED };
+enum { HIT_STORED, HIT_PACKED, HIT_FUSED, HIT_LISTED };
 struct fused_in {
     const uint32_t *mask;
     uint32_t nf, F, parts;
+    uint32_t *rest, *n_rest;
+    bool deferred;
 };
 constexpr uint32_t HIT_FUSED_PPT = 8;                   // level-2 pairs per thread of a chunk
+constexpr uint32_t HIT_TILE = 256;                      // pairs of such a tile
+static_assert(64 * HIT_FUSED_PPT % HIT_TILE == 0 && HIT_TILE >= LEVEL_TILE, "whole tiles, no more than counts");
+// most children that a chunk takes in parts by itself.  Small groups have the most
+// pairs per workgroup, and the longest waits: 72x48, bundle 2 of 8 nodes, 5 levels
+// 1,043 us at 2 chunks, 1,151 at 3; 512x512, bundle 16 of 8 nodes, 4 levels 2,380
+// at 2, 2,305 at 3 (whole calls)
+__host__ __device__ constexpr uint32_t hit_later(int lg) { return (lg == 2 ? 2u : 3u) * HIT_CHUNK; }
 
 typedef float mfma4 __attribute__((ext_vector_type(4)));
 
@@ -328,14 +342,17 @@ __global__ __launch_bounds__(HIT_THREADS, hit_waves_per_simd(LG)) void k_hit(hit
                                                      uint32_t tri_base, batch_dev bd, float t_min, uint32_t chunk_max,
                                                      fused_in fu)
 {
-    constexpr bool PACKED = IN == HIT_PACKED, FUSED = IN == HIT_FUSED;
-    constexpr uint32_t PPT = FUSED ? HIT_FUSED_PPT : HIT_PPT;
+    constexpr bool PACKED = IN == HIT_PACKED, LIST = IN == HIT_LISTED, FUSED = IN == HIT_FUSED || LIST;
+    // pairs of a thread: children of a list as many as stored pairs
+    constexpr uint32_t PPT = IN == HIT_FUSED ? HIT_FUSED_PPT : HIT_PPT;
     constexpr uint32_t G = 1u << LG;                // lanes, and triangles of a block, per group
     constexpr uint32_t GPW = WAVE / G;              // groups of a wave
     constexpr uint32_t NONE = 0xFFFFFFFFu;
-    __shared__ uint32_t s_tri[HIT_CHUNK];           // triangle ids, leaf by leaf
-    __shared__ __attribute__((aligned(8))) uint32_t s_cnt[HIT_BINS];            // pairs per leaf, then the leaf's first place
-    __shared__ uint32_t s_blk[HIT_CHUNK / G + HIT_BINS];    // first the leaves of the bins, if not consecutive
+    __shared__ __attribute__((aligned(8))) uint32_t s_tri[HIT_CHUNK];           // triangle ids, leaf by leaf
+    __shared__ uint32_t s_binned[HIT_BINS + HIT_CHUNK / G + HIT_BINS];
+    uint32_t *const s_cnt = s_binned;               // pairs per bin, then the bin's first place
+    uint32_t *const s_blk = s_binned + HIT_BINS;    // blocks; first the leaves of the bins, if not consecutive
+    static_assert(2 * HIT_CHUNK <= sizeof(s_binned) && HIT_FUSED_PPT * HIT_THREADS * 2 <= HIT_CHUNK, "fused lists");
     __shared__ uint32_t s_from;
     __shared__ uint2 s_queue[HIT_WAVES][HIT_QUEUE];
     __shared__ uint2 s_scan[HIT_WAVES], s_lohi[HIT_WAVES];
@@ -392,7 +409,8 @@ __global__ __launch_bounds__(HIT_THREADS, hit_waves_per_simd(LG)) void k_hit(hit
     // near-equal chunks in whole rounds of the grid, at most chunk_max pairs each
     const float rounds = ceilf((float)np / ((float)gridDim.x * (float)chunk_max));
     uint32_t cs = rounds > 0.0f ? (uint32_t)((float)np / (rounds * (float)gridDim.x)) + 1u : 1u;
-    cs = min(max((cs + 63u) & ~63u, HIT_MIN_CHUNK), chunk_max);
+    constexpr uint32_t UNIT = LIST ? HIT_TILE : HIT_MIN_CHUNK;
+    cs = min(max((cs + UNIT - 1u) & ~(UNIT - 1u), UNIT), chunk_max);
     // pass bits of the four pairs from q on (q a multiple of 4), pair q + i in
     // the bits from i * nf on
     auto load_bits = [&](uint64_t q, uint2 &w, uint32_t &sh) {
@@ -405,19 +423,24 @@ __global__ __launch_bounds__(HIT_THREADS, hit_waves_per_simd(LG)) void k_hit(hit
         const uint32_t at = sh + i * fu.nf;
         return (at < 32u ? w.x >> at : w.y >> (at - 32u)) & ((1u << fu.nf) - 1u);
     };
-    for (uint64_t chunk = (uint64_t)blockIdx.x * cs; chunk < np; chunk += (uint64_t)gridDim.x * cs) {
+    const bool deferred = LIST && fu.deferred;
+    if (deferred) cs = HIT_TILE;
+    const uint64_t chunks = deferred ? (np ? *fu.n_rest : 0u) : (np + cs - 1) / cs;
+    for (uint64_t ci = blockIdx.x; ci < chunks; ci += gridDim.x) {
+    const uint64_t chunk = (uint64_t)cs * (deferred ? fu.rest[ci] : ci);
     const uint32_t chunk_n = (uint32_t)min(np - chunk, (uint64_t)cs);
     // (once; fused: as many pairs at a time as have survivors that fit)
     for (uint32_t done = 0, cn; done < chunk_n; done += cn) {
         const uint64_t c0 = chunk + done;
         cn = chunk_n - done;
+        bool later = false;
         if constexpr (FUSED) {
             // equal parts of the rest as long as the survivors do not fit
             // (those of 256 pairs always do)
             for (;;) {
                 uint32_t kids = 0u;
 #pragma unroll
-                for (uint32_t k = 0; k < PPT; k += 4) {
+                for (uint32_t k = 0; k < HIT_FUSED_PPT; k += 4) {
                     const uint32_t q = k * HIT_THREADS + 4 * threadIdx.x;
                     if (q >= cn) continue;
                     uint2 w;
@@ -435,56 +458,124 @@ __global__ __launch_bounds__(HIT_THREADS, hit_waves_per_simd(LG)) void k_hit(hit
                 __syncthreads();                    // s_lohi is written again
                 kids = __builtin_amdgcn_readfirstlane(kids);
                 if (kids <= HIT_CHUNK) break;
+                later = LIST && !deferred && kids > hit_later(LG);
+                if (later) break;
                 const uint32_t parts = (kids - 1u) / HIT_CHUNK + 1u;        // at least 2
                 cn = ((cn - 1u) / parts + 64u) & ~63u;
             }
+        }
+        if (later) {
+            const uint32_t n = (cn + HIT_TILE - 1u) / HIT_TILE;
+            if (threadIdx.x == 0) s_from = atomicAdd(fu.n_rest, n);
+            __syncthreads();
+            if (threadIdx.x < n) fu.rest[s_from + threadIdx.x] = (uint32_t)(c0 / HIT_TILE) + threadIdx.x;
+            __syncthreads();                        // s_from is written again
+            continue;
         }
         uint32_t from = 0u;                         // first leaf not binned yet
         for (bool more = true; more;) {
             uint32_t tid = threadIdx.x;
             asm volatile("" : "+v"(tid));           // nothing of a round is kept over the next
             // my_leaf: the pair's leaf (fused: the first child of its node)
-            uint32_t my_t[PPT], my_leaf[PPT], my_bits[FUSED ? PPT : 1];
+            uint32_t my_t[PPT], my_leaf[PPT], my_bits[IN == HIT_FUSED ? PPT : 1];
             uint32_t lo = NONE, hi = 0u;            // the leaves still to do: smallest and largest
+            // pass bits of pair i of four, of the children that have rays (a pair
+            // out of range has none); f: its first child
+            auto kept = [&](uint32_t q, uint32_t t, uint32_t node, uint2 w, uint32_t sh, uint32_t i, uint32_t &f) {
+                uint32_t b = q < cn && t < m && node < np2 ? bits_of(w, sh, i) : 0u;
+                f = node * fu.F;
+                if constexpr (BATCH) f = b ? bd.node_first[off2 + node] : 0u;
+                return f <= last_leaf ? b & (uint32_t)((1ull << min(last_leaf - f + 1u, 16u)) - 1ull) : 0u;
+            };
+            if constexpr (LIST) {
+                // the children that the pass bits keep, listed in LDS (pair of
+                // the chunk, child) with the pairs beside them (triangle, first
+                // child), so that the lanes share them evenly
+                uint2 *const par = (uint2 *)s_tri;
+                uint16_t *const item = (uint16_t *)s_binned;
+                uint32_t bits[HIT_FUSED_PPT], n = 0u;
+                __syncthreads();                    // the round before is done with these
 #pragma unroll
-            for (uint32_t k = 0; k < PPT; k += 4) {     // four consecutive pairs a load
-                const uint32_t q = k * HIT_THREADS + 4 * tid;
-                load4(ptri + c0, q, cn, &my_t[k]);
-                if constexpr (!PACKED) load4(pnode + c0, q, cn, &my_leaf[k]);
-                if constexpr (FUSED) {
+                for (uint32_t k = 0; k < HIT_FUSED_PPT; k += 4) {
+                    const uint32_t q = k * HIT_THREADS + 4 * tid;
+                    uint32_t t[4], node[4], sh = 0u;
+                    load4(ptri + c0, q, cn, t);
+                    load4(pnode + c0, q, cn, node);
                     uint2 w = make_uint2(0u, 0u);
-                    uint32_t sh = 0u;
                     if (q < cn) load_bits(c0 + q, w, sh);
 #pragma unroll
-                    for (uint32_t i = 0; i < 4; ++i) my_bits[k + i] = bits_of(w, sh, i);
+                    for (uint32_t i = 0; i < 4; ++i) {
+                        uint32_t f;
+                        bits[k + i] = kept(q + i, t[i], node[i], w, sh, i, f);
+                        n += (uint32_t)__popc(bits[k + i]);
+                        par[q + i] = make_uint2(t[i], f);
+                    }
                 }
-            }
+                uint32_t at = wave_scan_dpp(n), all = 0u;
+                if (l == WAVE - 1) s_scan[wib].x = at;
+                at -= n;
+                __syncthreads();
 #pragma unroll
-            for (uint32_t k = 0; k < PPT; ++k) {
-                const uint32_t q = k / 4 * 4 * HIT_THREADS + 4 * tid + k % 4;
-                if constexpr (FUSED) {
-                    // the leaves from `from` on that have rays; a pair out of range has none
-                    const uint32_t node = my_leaf[k];
-                    uint32_t b = q < cn && my_t[k] < m && node < np2 ? my_bits[k] : 0u;
-                    uint32_t f = node * fu.F;
-                    if constexpr (BATCH) f = b ? bd.node_first[off2 + node] : 0u;
-                    b = f <= last_leaf ? b & (uint32_t)((1ull << min(last_leaf - f + 1u, 16u)) - 1ull) : 0u;
-                    b = f < from ? b >> min(from - f, 31u) << min(from - f, 31u) : b;
-                    my_bits[k] = b;
-                    my_leaf[k] = f;
-                    lo = b ? min(lo, f + (uint32_t)__builtin_ctz(b)) : lo;
-                    hi = b ? max(hi, f + 31u - (uint32_t)__builtin_clz(b)) : hi;
-                    continue;
+                for (uint32_t w = 0; w < HIT_WAVES; ++w) {
+                    const uint32_t v = s_scan[w].x;
+                    at += w < wib ? v : 0u;
+                    all += v;
                 }
-                if constexpr (PACKED) {
-                    my_leaf[k] = my_t[k] >> CRSH_PACKED_TRI_BITS;
-                    my_t[k] = tri_base + (my_t[k] & ((1u << CRSH_PACKED_TRI_BITS) - 1u));
+#pragma unroll
+                for (uint32_t k = 0; k < HIT_FUSED_PPT; ++k) {
+                    const uint32_t q = k / 4 * 4 * HIT_THREADS + 4 * tid + k % 4;
+                    for (uint32_t b = bits[k]; b != 0u; b &= b - 1u)
+                        item[at++] = (uint16_t)(q << 4 | (uint32_t)__builtin_ctz(b));
                 }
-                // a pair out of range has no tests
-                const bool ok = q < cn && my_t[k] < m && my_leaf[k] <= last_leaf && my_leaf[k] >= from;
-                hi = ok ? max(hi, my_leaf[k]) : hi;
-                my_leaf[k] = ok ? my_leaf[k] : NONE;
-                lo = min(lo, my_leaf[k]);
+                __syncthreads();
+#pragma unroll
+                for (uint32_t k = 0; k < HIT_PPT; ++k) {
+                    const uint32_t i = k * HIT_THREADS + tid;
+                    const uint32_t it = item[i < all ? i : 0u];
+                    const uint2 p = par[it >> 4];
+                    const uint32_t leaf = p.y + (it & 15u);
+                    const bool ok = i < all && leaf >= from;
+                    my_t[k] = p.x;
+                    hi = ok ? max(hi, leaf) : hi;
+                    my_leaf[k] = ok ? leaf : NONE;
+                    lo = min(lo, my_leaf[k]);
+                }
+                __syncthreads();                    // s_cnt is cleared
+            } else {
+#pragma unroll
+                for (uint32_t k = 0; k < PPT; k += 4) {     // four consecutive pairs a load
+                    const uint32_t q = k * HIT_THREADS + 4 * tid;
+                    load4(ptri + c0, q, cn, &my_t[k]);
+                    if constexpr (!PACKED) load4(pnode + c0, q, cn, &my_leaf[k]);
+                    if constexpr (FUSED) {
+                        uint2 w = make_uint2(0u, 0u);
+                        uint32_t sh = 0u;
+                        if (q < cn) load_bits(c0 + q, w, sh);
+#pragma unroll
+                        for (uint32_t i = 0; i < 4; ++i) {
+                            uint32_t f, b = kept(q + i, my_t[k + i], my_leaf[k + i], w, sh, i, f);
+                            b = f < from ? b >> min(from - f, 31u) << min(from - f, 31u) : b;
+                            my_bits[k + i] = b;
+                            my_leaf[k + i] = f;
+                            lo = b ? min(lo, f + (uint32_t)__builtin_ctz(b)) : lo;
+                            hi = b ? max(hi, f + 31u - (uint32_t)__builtin_clz(b)) : hi;
+                        }
+                    }
+                }
+                if constexpr (!FUSED)
+#pragma unroll
+                for (uint32_t k = 0; k < PPT; ++k) {
+                    const uint32_t q = k / 4 * 4 * HIT_THREADS + 4 * tid + k % 4;
+                    if constexpr (PACKED) {
+                        my_leaf[k] = my_t[k] >> CRSH_PACKED_TRI_BITS;
+                        my_t[k] = tri_base + (my_t[k] & ((1u << CRSH_PACKED_TRI_BITS) - 1u));
+                    }
+                    // a pair out of range has no tests
+                    const bool ok = q < cn && my_t[k] < m && my_leaf[k] <= last_leaf && my_leaf[k] >= from;
+                    hi = ok ? max(hi, my_leaf[k]) : hi;
+                    my_leaf[k] = ok ? my_leaf[k] : NONE;
+                    lo = min(lo, my_leaf[k]);
+                }
             }
             lo = wave_reduce(lo, NONE, [](uint32_t a, uint32_t b) { return min(a, b); });
             hi = wave_reduce(hi, 0u, [](uint32_t a, uint32_t b) { return max(a, b); });
@@ -502,25 +593,21 @@ __global__ __launch_bounds__(HIT_THREADS, hit_waves_per_simd(LG)) void k_hit(hit
             hi = __builtin_amdgcn_readfirstlane(hi);
             const bool wide = base != NONE && hi - base >= HIT_BINS;
             uint32_t used = min(hi - base + 1u, HIT_BINS);      // bins in use
+            uint32_t leaves = 0u;                               // (wide) that have pairs
             more = false;
             // the leaves counted from the round's first on
 #pragma unroll
-            for (uint32_t k = 0; k < PPT; ++k) {
-                if constexpr (FUSED) {
-                    // (may be below it; the bits of such children are clear)
-                    my_leaf[k] -= base;
-                } else {
-                    my_leaf[k] = my_leaf[k] != NONE ? my_leaf[k] - base : NONE;
-                }
-            }
+            for (uint32_t k = 0; k < PPT; ++k)
+                my_leaf[k] = IN == HIT_FUSED || my_leaf[k] != NONE ? my_leaf[k] - base : NONE;
             // wide: the bins are the leaves that have pairs, in order, and
-            // my_leaf becomes the bin (fused: of the first child, with a bit for
-            // each child that has a bin in the high half)
+            // my_leaf becomes the bin (fused: the first child in the low 15
+            // bits, then a bit for each child that has a bin, then the first bin)
             if (wide) {
-                if constexpr (FUSED) {
+                if constexpr (IN == HIT_FUSED) {
+                    // first children before the round's first: those bits are clear
 #pragma unroll
                     for (uint32_t k = 0; k < PPT; ++k) {
-                        const uint32_t sh = 0u - my_leaf[k] < 16u ? 0u - my_leaf[k] : 0u;
+                        const uint32_t sh = 0u - my_leaf[k] < 4u ? 0u - my_leaf[k] : 0u;
                         my_bits[k] >>= sh;
                         my_leaf[k] += sh;
                     }
@@ -533,7 +620,7 @@ __global__ __launch_bounds__(HIT_THREADS, hit_waves_per_simd(LG)) void k_hit(hit
 #pragma unroll
                 for (uint32_t k = 0; k < PPT; ++k) {
                     const uint32_t w = my_leaf[k] / 32u;
-                    if constexpr (FUSED) {
+                    if constexpr (IN == HIT_FUSED) {
                         const uint64_t b = (uint64_t)my_bits[k] << (my_leaf[k] & 31u);
                         if ((uint32_t)b != 0u && w < HIT_SPAN_WORDS) atomicOr(&map[w], (uint32_t)b);
                         if (b >> 32 != 0u && w < HIT_SPAN_WORDS - 1u) atomicOr(&map[w + 1], (uint32_t)(b >> 32));
@@ -548,7 +635,7 @@ __global__ __launch_bounds__(HIT_THREADS, hit_waves_per_simd(LG)) void k_hit(hit
                     own[k] = map[HIT_SPAN_WPT * tid + k];
                     n += (uint32_t)__popc(own[k]);
                 }
-                uint32_t bin = wave_scan_dpp(n), leaves = 0u;
+                uint32_t bin = wave_scan_dpp(n);
                 if (l == WAVE - 1) s_scan[wib].x = bin;
                 bin -= n;
                 __syncthreads();
@@ -561,30 +648,32 @@ __global__ __launch_bounds__(HIT_THREADS, hit_waves_per_simd(LG)) void k_hit(hit
                 leaves = __builtin_amdgcn_readfirstlane(leaves);
 #pragma unroll
                 for (uint32_t k = 0; k < HIT_SPAN_WPT; ++k) {
-                    const uint32_t w = HIT_SPAN_WPT * tid + k;
-                    before[w] = (uint16_t)bin;
-                    for (; own[k] != 0u; own[k] &= own[k] - 1u, ++bin) {
-                        const uint32_t leaf = w * 32u + (uint32_t)__builtin_ctz(own[k]);
-                        if (bin < HIT_BINS) s_blk[bin] = leaf;
-                        if (bin == HIT_BINS) s_from = base + leaf;
-                    }
+                    before[HIT_SPAN_WPT * tid + k] = (uint16_t)bin;
+                    bin += (uint32_t)__popc(own[k]);
                 }
                 __syncthreads();
-                // what has no bin waits
-                more = leaves > HIT_BINS || hi - base >= HIT_SPAN;
-                from = leaves > HIT_BINS ? __builtin_amdgcn_readfirstlane(s_from) : base + HIT_SPAN;
                 used = min(leaves, HIT_BINS);
 #pragma unroll
                 for (uint32_t k = 0; k < PPT; ++k) {
                     const uint32_t w = min(my_leaf[k] / 32u, HIT_SPAN_WORDS - 1u), sh = my_leaf[k] & 31u;
                     const uint32_t bits = map[w], b = before[w] + (uint32_t)__popc(bits & ((1u << sh) - 1u));
                     const bool in = my_leaf[k] < HIT_SPAN;
-                    if constexpr (FUSED) {
+                    // (the leaf of a bin is put down by all its pairs)
+                    if constexpr (IN == HIT_FUSED) {
                         const uint32_t up = w + 1 < HIT_SPAN_WORDS ? map[w + 1] : 0u;
-                        const uint32_t has = (uint32_t)(((uint64_t)up << 32 | bits) >> sh) & 0xFFFFu;
+                        const uint32_t has = (uint32_t)(((uint64_t)up << 32 | bits) >> sh) & 15u;
                         my_bits[k] = in ? my_bits[k] & has : 0u;
-                        my_leaf[k] = b | has << 16;
+                        uint32_t at = b;
+#pragma unroll
+                        for (uint32_t c = 0; c < 4; ++c) {
+                            if ((my_bits[k] >> c & 1u) != 0u && at < HIT_BINS) s_blk[at] = my_leaf[k] + c;
+                            if ((my_bits[k] >> c & 1u) != 0u && at == HIT_BINS) s_from = base + my_leaf[k] + c;
+                            at += has >> c & 1u;
+                        }
+                        my_leaf[k] = (my_leaf[k] & (HIT_SPAN - 1u)) | has << 15 | b << 19;
                     } else {
+                        if (in && b < HIT_BINS) s_blk[b] = my_leaf[k];
+                        if (in && b == HIT_BINS) s_from = base + my_leaf[k];
                         my_leaf[k] = in ? b : NONE;
                     }
                     if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);     // few in flight: registers
@@ -604,13 +693,13 @@ __global__ __launch_bounds__(HIT_THREADS, hit_waves_per_simd(LG)) void k_hit(hit
                         }
                 };
                 if (wide)
-                    each([](uint32_t v, uint32_t c) { return (v & 0xFFFFu) + (uint32_t)__popc((v >> 16) & ((1u << c) - 1u)); });
+                    each([](uint32_t v, uint32_t c) { return (v >> 19) + (uint32_t)__popc((v >> 15) & ((1u << c) - 1u)); });
                 else
                     each([](uint32_t v, uint32_t c) { return v + c; });
             };
-            // pairs per leaf; each pair's bin and its place in the leaf's run
+            // pairs per leaf; each pair's bin and its place in the bin's run
             // (fused: the place is taken when the triangle is put there)
-            if constexpr (FUSED)
+            if constexpr (IN == HIT_FUSED)
                 children([&](uint32_t bin, uint32_t) { atomicAdd(&s_cnt[bin], 1u); });
             else
 #pragma unroll
@@ -621,6 +710,10 @@ __global__ __launch_bounds__(HIT_THREADS, hit_waves_per_simd(LG)) void k_hit(hit
                 if (ok) my_leaf[k] = bin | atomicAdd(&s_cnt[bin], 1u) * HIT_BINS;
             }
             __syncthreads();
+            if (wide) {                 // what has no bin waits
+                more = leaves > HIT_BINS || hi - base >= HIT_SPAN;
+                from = leaves > HIT_BINS ? __builtin_amdgcn_readfirstlane(s_from) : base + HIT_SPAN;
+            }
             // places, whole blocks and remainders of the leaves
             uint32_t nfull = 0u, nblk = 0u;
             auto count_tests = [&](uint32_t leaf, uint32_t pairs) {
@@ -711,7 +804,7 @@ __global__ __launch_bounds__(HIT_THREADS, hit_waves_per_simd(LG)) void k_hit(hit
                 }
             }
             __syncthreads();
-            if constexpr (FUSED)
+            if constexpr (IN == HIT_FUSED)
                 children([&](uint32_t bin, uint32_t k) { s_tri[atomicAdd(&s_cnt[bin], 1u)] = my_t[k]; });
             else
 #pragma unroll
@@ -916,7 +1009,6 @@ static uint32_t k_hit_launch(const hit_slots_ws &hs, const hit_tris_ws &tri, con
                              crsh_hits *hits, crsh_meta *meta, uint32_t m, uint32_t tri_base, const batch_dev *bd,
                              float t_min, uint32_t chunk, const fused_in &fu, hipStream_t stream)
 {
-    prof_scope ps("k_hit", stream);
 #define CRSH_HIT(LG) \
     return k_hit_launch<LG, IN>(hs, tri, pairs, B, hits, meta, m, tri_base, bd, t_min, chunk, fu, stream)
     if (B <= 4)
@@ -937,6 +1029,7 @@ uint32_t hit_pairs_launch(const hit_tris_ws &tri, const hit_slots_ws &hs,
 {
     if (!level1->capacity) return 0u;
     const uint32_t chunk = (uint32_t)hit_block * (HIT_CHUNK / 256u);
+    prof_scope ps("k_hit", stream);
     return packed ? k_hit_launch<HIT_PACKED>(hs, tri, level1, (uint32_t)bundle, hits, meta, scene->m, tri_base, bd,
                                              t_min, chunk, fused_in{}, stream)
                   : k_hit_launch<HIT_STORED>(hs, tri, level1, (uint32_t)bundle, hits, meta, scene->m, tri_base, bd,
@@ -944,18 +1037,25 @@ uint32_t hit_pairs_launch(const hit_tris_ws &tri, const hit_slots_ws &hs,
 }
 
 // level-2 pairs with the pass bits of their children; `parts` workgroups of
-// the launch before keep their counts.  Returns the workgroups that have counts.
+// the launch before keep their counts.  rest: room for a word per HIT_TILE pairs,
+// n_rest: a word that is zero.  Returns the workgroups that have counts.
 uint32_t hit_masked_launch(const hit_tris_ws &tri, const hit_slots_ws &hs, const crsh_pairs *level2,
                            const uint32_t *mask, int32_t merge, int32_t bundle, const crsh_scene *scene, float t_min,
                            crsh_hits *hits, crsh_meta *meta, const batch_dev *bd, int32_t hit_block, uint32_t parts,
-                           hipStream_t stream)
+                           uint32_t *rest, uint32_t *n_rest, hipStream_t stream)
 {
     uint32_t nf = 2;
     while (nf < (uint32_t)merge) nf *= 2;
     const uint32_t chunk = (uint32_t)hit_block * HIT_FUSED_PPT;
-    const uint32_t g = k_hit_launch<HIT_FUSED>(hs, tri, level2, (uint32_t)bundle, hits, meta, scene->m, 0u, bd, t_min,
-                                               chunk, fused_in{mask, nf, (uint32_t)merge, parts}, stream);
-    return std::max(g, parts);
+    fused_in fu{mask, nf, (uint32_t)merge, parts, rest, n_rest, false};
+    prof_scope ps("k_hit", stream);
+    if (nf <= 4)
+        return std::max(parts, k_hit_launch<HIT_FUSED>(hs, tri, level2, (uint32_t)bundle, hits, meta, scene->m, 0u, bd,
+                                                       t_min, chunk, fu, stream));
+    for (int pass = 0; pass < 2; ++pass, fu.deferred = true)
+        fu.parts = std::max(fu.parts, k_hit_launch<HIT_LISTED>(hs, tri, level2, (uint32_t)bundle, hits, meta, scene->m,
+                                                               0u, bd, t_min, chunk, fu, stream));
+    return fu.parts;
 }
 
 void hit_final_launch(const crsh_rays *sorted, const uint32_t *sorted_ids, const float4 *tri,

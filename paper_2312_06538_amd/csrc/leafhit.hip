@@ -60,9 +60,12 @@ size_t leaf_hit_ws_bytes(uint32_t m, uint32_t node_cap, uint64_t cap2, uint32_t 
            align256(tiles * LEVEL_THREADS * 4 + 4);
 }
 
-// level-1 pairs formed: the survivors of every tile of the level-1 count
+// level-1 pairs formed: the survivors of every tile of the level-1 count, whose
+// places then take the tiles that the final tests put off (one more word, cleared
+// here, counts those)
 __global__ void k_lh_survivors(trav_scratch S, crsh_meta *meta, uint64_t cap2)
 {
+    if (blockIdx.x == 0 && threadIdx.x == 0) S.cnt[(cap2 + LEVEL_TILE - 1) / LEVEL_TILE] = 0u;
     __shared__ uint64_t s_red[256 / WAVE];
     uint64_t nin = meta->n_levels >= 2 ? meta->pairs[1] : 0u;
     nin = nin < cap2 ? nin : cap2;
@@ -125,7 +128,7 @@ crsh_status leaf_hit_launch(const crsh_rays *sorted, const uint32_t *sorted_ids,
                                                                         1024), 1);
     k_lh_survivors<<<gs, 256, 0, stream>>>(L.S, meta, level2->capacity);
     const uint32_t all = hit_masked_launch(L.tri, L.hs, level2, L.S.bits, merge, bundle, scene, t_min, hits, meta, bd,
-                                           hit_block, parts, stream);
+                                           hit_block, parts, L.S.cnt, L.S.cnt + lh_tiles(level2->capacity), stream);
     hit_final_launch(sorted, sorted_ids, L.tri.tri, L.hs, bundle, scene, t_min, hits, meta, bd, all, stream);
     return hip_check(hipGetLastError(), "crsh_leaf_hit launch");
 }

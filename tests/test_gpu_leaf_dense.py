@@ -1,0 +1,140 @@
+"""Fused last level of level-2 pairs with 5 to 16 children each of which far more
+pass than a workgroup holds, so that whole chunks wait for a second launch, beside
+chunks that hardly have any: plain, with a merge factor that is no power of two,
+with pairs in node order and in no order, and batched; every hit and counter
+exactly the oracle's.  And a bound on what such pairs cost."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from conftest import workload
+from oracle import oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _case(B, F, nodes, m, seed):
+    """Rays, hierarchy of two levels and level-2 pairs: rays of any direction,
+    whose nodes no triangle is outside of, but for the nodes' last sixth, whose
+    rays are nearly parallel."""
+    from workloads.scenes import Scene
+    rng = np.random.default_rng(seed)
+    n = nodes * F * B - F * B // 3
+    v0 = rng.uniform(-10, 10, (m, 3))
+    tris = np.stack([v0, v0 + rng.normal(0, 2, (m, 3)), v0 + rng.normal(0, 2, (m, 3))], 1).astype(np.float32)
+    o = rng.uniform(-20, 20, (n, 3))
+    d = tris[rng.integers(0, m, n)].mean(1) - o
+    some = np.arange(n) >= n * 5 // 6
+    o[some] = [0, 0, -40] + rng.uniform(-1, 1, (int(some.sum()), 3))
+    d[some] = [0, 0, 1] + rng.uniform(-.02, .02, (int(some.sum()), 3))
+    d /= np.linalg.norm(d, axis=1, keepdims=True)
+    o, d = o.astype(np.float32), d.astype(np.float32)
+    rays = {"ox": o[:, 0], "oy": o[:, 1], "oz": o[:, 2], "dx": d[:, 0], "dy": d[:, 1], "dz": d[:, 2],
+            "tmax": np.full(n, np.finfo(np.float32).max, np.float32), "pix": np.zeros(n, np.uint32)}
+    sc = Scene(tris=tris, mesh_first=np.zeros(1, np.uint32), mesh_count=np.array([m], np.uint32),
+               mesh_sphere=np.array([[0, 0, 0, 1e30]], np.float32), mesh_mat=np.zeros(1, np.int32),
+               mat_flags=np.zeros(1, np.uint32), mat_ior=np.ones(1, np.float32))
+    tree = O.build_tree(rays, np.arange(n, dtype=np.uint32), B, F, 2)
+    return rays, sc, tree
+
+
+def _leaf_hit(rays, sc, tree, B, F, pairs2, times=1):
+    """crsh_leaf_hit of those level-2 pairs: hits, meta and the best time in us."""
+    import gpu_util as U
+    import torch
+    from paper_2312_06538_amd import crsh as X
+    n = len(rays["ox"])
+    r = {k: U.dev_f32(rays[k]) for k in U.RAY_KEYS}
+    c_r = X.Rays(*[r[k].data_ptr() for k in U.RAY_KEYS], None, n)
+    ids = torch.arange(n, dtype=torch.int32, device="cuda")
+    ncap = int(sum(tree["level_cnt"]))
+    nodes = {k: U.dev_f32(tree["nodes"][k], ncap) for k in U.NODE_KEYS}
+    c_nodes = X.Nodes(*[nodes[k].data_ptr() for k in U.NODE_KEYS], ncap)
+    c_sc, keep = U._scene(sc)
+    p = [U.dev_u32(a) for a in pairs2]
+    low = torch.zeros(2, dtype=torch.int32, device="cuda")
+    table = X.PairTable()
+    table[0] = X.Pairs(low.data_ptr(), low.data_ptr() + 4, 1)
+    table[1] = X.Pairs(p[0].data_ptr(), p[1].data_ptr(), len(pairs2[0]))
+    out = [torch.zeros(n, dtype=dt, device="cuda") for dt in (torch.int64, torch.int32, *[torch.float32] * 3)]
+    hits = X.Hits(*[x.data_ptr() for x in out], n)
+    wsb = X.crsh_workspace_size(n, sc.m, sc.n_mesh, ncap, len(pairs2[0]))
+    ws = U.ws_tensor(wsb)
+    best = float("inf")
+    for _ in range(times):
+        meta = U.new_meta(n_rays=n, n_levels=2, level_off=list(tree["level_off"]), level_cnt=list(tree["level_cnt"]),
+                          pairs=[0, len(pairs2[0])])
+        X.crsh_hits_reset(hits, U.s())
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        X.crsh_leaf_hit(c_r, ids.data_ptr(), B, F, c_nodes, table, c_sc, 1e-4, hits, meta.data_ptr(), ws.data_ptr(),
+                        wsb, U.s())
+        b.record()
+        m, st = U.read_meta(meta)
+        assert st == 0
+        best = min(best, a.elapsed_time(b) * 1e3)
+    h = [x.cpu().numpy() for x in out[1:]]
+    return h, m, best
+
+
+# at least 1.1 M level-2 pairs: then a chunk is over 768 of them, with over
+# 12,000 children where none are culled
+@pytest.mark.parametrize("B,F,nodes,m,mixed", [
+    (2, 16, 2000, 700, True), (4, 16, 1100, 1200, False), (2, 13, 2500, 600, True), (16, 16, 400, 4000, True),
+    (3, 8, 4300, 600, False), (32, 9, 300, 6000, True), (8, 5, 3000, 900, True)])
+def test_dense_pairs_match_oracle(B, F, nodes, m, mixed):
+    rays, sc, tree = _case(B, F, nodes, m, B * F)
+    t = O.traverse(tree, sc)
+    pairs2, (t1, l1) = t["pairs"][2], t["pairs"][1]
+    print(f"[leaf dense] B={B} F={F}: {len(pairs2[0])} level-2 pairs, {len(t1)} level-1 pairs", flush=True)
+    assert len(pairs2[0]) > 1100000 and len(t1) > 4.5 * len(pairs2[0])
+    if mixed:
+        k = np.random.default_rng(1).permutation(len(pairs2[0]))
+        pairs2 = tuple(np.asarray(a)[k] for a in pairs2)
+    stages = {}
+    n = len(rays["ox"])
+    ref = O.closest_hit(rays, np.arange(n, dtype=np.uint32), B, (t1, l1), sc, 1e-4, stages=stages)
+    for _ in range(2):
+        h, meta, _ = _leaf_hit(rays, sc, tree, B, F, pairs2)
+        for a, b in zip(h, ref):
+            assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
+        assert int(meta.hits[0]) == len(t1)
+        assert int(meta.final_tests) == int(np.minimum(B, n - np.asarray(l1, np.int64) * B).sum())
+        assert (int(meta.final_u_pass), int(meta.final_uv_pass)) == (stages["u"], stages["uv"])
+
+
+@pytest.mark.parametrize("B,F,n", [(2, 16, 4), (4, 8, 4)])
+def test_dense_batch_matches_oracle(B, F, n):
+    from paper_2312_06538_amd.batch import DeviceBatch
+    wls = [dataclasses.replace(workload("mixed_1080p", W=w, H=h, n_meshes=48), B=B, F=F, n=n)
+           for w, h in ((128, 72), (40, 30))]
+    orcs = [O.run_pipeline(wl) for wl in wls]
+    print(f"[leaf dense] batch B={B} F={F}: {sum(len(o['trav']['pairs'][2][0]) for o in orcs)} level-2 pairs", flush=True)
+    db = DeviceBatch(wls, B, F, n, pair_capacity=1 << 20, leaf_hit=True)
+    m = db.run_with_retry()
+    assert int(m.final_tests) == sum(o["trav"]["final_tests"] for o in orcs)
+    for r, o in zip(db.frame_results(m, with_pairs=False), orcs):
+        for a, b in zip(r["hit"], o["hits"]):
+            assert np.array_equal(np.asarray(a).view(np.uint32), np.asarray(b).view(np.uint32))
+
+
+def test_dense_pairs_cost():
+    """Level-2 pairs in no order, most with all of 16 children, and as many
+    level-1 pairs of 4 to a node: 1.3 to 1.6 times as long when every lane goes
+    through its own children and dense chunks stay with their workgroup."""
+    us = {}
+    for F, nodes in ((4, 8192), (16, 2048)):
+        rays, sc, tree = _case(2, F, nodes, 700, 5)
+        t = O.traverse(tree, sc)
+        k = np.random.default_rng(1).permutation(len(t["pairs"][2][0]))
+        us[F] = _leaf_hit(rays, sc, tree, 2, F, tuple(np.asarray(a)[k] for a in t["pairs"][2]), 6)[2]
+    print(f"[leaf dense] {us[4]:.0f} us at 4 children, {us[16]:.0f} us at 16", flush=True)
+    assert us[16] < 1.25 * us[4]
