@@ -218,30 +218,6 @@ __device__ __forceinline__ uint64_t lookback_wave(uint64_t *flags, uint32_t tile
     return excl;
 }
 
-// Called by one thread of the tile; returns the exclusive prefix of `count`.
-__device__ __forceinline__ uint64_t lookback(uint64_t *flags, uint32_t tile, uint64_t count)
-{
-    if (tile == 0) {
-        lb_store(&flags[0], LB_INC | count);
-        return 0;
-    }
-    lb_store(&flags[tile], LB_AGG | count);
-    uint64_t excl = 0;
-    int64_t j = (int64_t)tile - 1;
-    while (j >= 0) {
-        uint64_t f = lb_load(&flags[j]);
-        if ((f & ~LB_MASK) == 0) {
-            __builtin_amdgcn_s_sleep(1);
-            continue;
-        }
-        excl += f & LB_MASK;
-        if ((f & ~LB_MASK) == LB_INC) break;
-        --j;
-    }
-    lb_store(&flags[tile], LB_INC | (excl + count));
-    return excl;
-}
-
 // ------------------------------------------------------------- workspace
 // Every stage carves its scratch from the start of the caller's workspace;
 // these are the byte counts each stage needs.

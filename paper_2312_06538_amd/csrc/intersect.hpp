@@ -135,24 +135,4 @@ __device__ __forceinline__ void mt_second_half(f3 D, float t_min, float tmax, co
     hit = puv & ballot(t > t_min) & ballot(t < tmax);
 }
 
-// The same test for the final-test kernel, without early exits: every
-// quantity of the test is computed and the acceptance conditions are combined
-// at the end, so the whole wave runs one straight sequence (the division
-// included) instead of branching on each condition.  Values and the accept
-// decision are those of moller_trumbore.
-__device__ __forceinline__ bool moller_trumbore_t(f3 O, f3 D, float t_min, float tmax, const tri_t &tr, float &tt)
-{
-    const f3 p = cross(D, tr.e2);
-    const float det = dot(tr.e1, p);
-    const float inv = 1.0f / det;
-    const f3 T = O - tr.v0;
-    const float u = dot(T, p) * inv;
-    const f3 q = cross(T, tr.e1);
-    const float v = dot(D, q) * inv;
-    const float t = dot(tr.e2, q) * inv;
-    tt = t;
-    return fabsf(det) >= DET_EPS && (u >= 0.0f && u <= 1.0f) && (v >= 0.0f && u + v <= 1.0f) &&
-           (t > t_min && t < tmax);
-}
-
 }  // namespace crsh

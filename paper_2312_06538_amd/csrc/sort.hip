@@ -19,30 +19,12 @@
 namespace crsh {
 
 constexpr uint32_t SORT_THREADS = 256;
-#ifndef CRSH_SORT_PASS_THREADS
-#define CRSH_SORT_PASS_THREADS 512
-#endif
-#ifndef CRSH_SORT_PASS_ITEMS
-#define CRSH_SORT_PASS_ITEMS 16
-#endif
-constexpr uint32_t PASS_THREADS = CRSH_SORT_PASS_THREADS;  // threads of a pass tile
-constexpr uint32_t PASS_ITEMS = CRSH_SORT_PASS_ITEMS;      // keys per thread
-constexpr uint32_t PASS_TILE = PASS_THREADS * PASS_ITEMS;  // keys per pass tile (8192)
-#ifndef CRSH_SORT_HIST_BLOCKS
-#define CRSH_SORT_HIST_BLOCKS 1024
-#endif
-constexpr uint32_t SORT_HIST_BLOCKS = CRSH_SORT_HIST_BLOCKS;  // most blocks of the histogram kernel
-#ifndef CRSH_SORT_FEW_THREADS
-#define CRSH_SORT_FEW_THREADS 1024
-#endif
-#ifndef CRSH_SORT_FEW_ITEMS
-#define CRSH_SORT_FEW_ITEMS 4
-#endif
-#ifndef CRSH_SORT_FEW
-#define CRSH_SORT_FEW (1u << 18)
-#endif
-constexpr uint32_t FEW_THREADS = CRSH_SORT_FEW_THREADS, FEW_ITEMS = CRSH_SORT_FEW_ITEMS;
-constexpr uint32_t FEW = CRSH_SORT_FEW;   // capacities up to here take tiles of FEW_THREADS * FEW_ITEMS keys
+constexpr uint32_t PASS_THREADS = 512;          // threads of a pass tile
+constexpr uint32_t PASS_ITEMS = 16;             // keys per thread
+constexpr uint32_t PASS_TILE = PASS_THREADS * PASS_ITEMS;       // keys per pass tile (8192)
+constexpr uint32_t SORT_HIST_BLOCKS = 1024;     // most blocks of the histogram kernel
+constexpr uint32_t FEW_THREADS = 1024, FEW_ITEMS = 4;
+constexpr uint32_t FEW = 1u << 18;      // capacities up to here take tiles of FEW_THREADS * FEW_ITEMS keys
 
 // look-back words: flag in bits 31-30 (1 tile count, 2 inclusive prefix)
 constexpr uint32_t SLB_AGG = 1u << 30;
@@ -53,10 +35,7 @@ constexpr uint32_t SLB_MASK = (1u << 30) - 1;
 // ray, read through the value (ray id) from a per-ray frame table.
 constexpr uint32_t MAX_PASSES = SORT_PASSES + 1;
 
-#ifndef CRSH_SORT_LOOK
-#define CRSH_SORT_LOOK 4
-#endif
-constexpr int32_t LOOK = CRSH_SORT_LOOK;   // look-back words read at once
+constexpr int32_t LOOK = 4;     // look-back words read at once
 
 // plan codes for the source / destination of each pass
 enum : uint32_t { BUF_IN = 0, BUF_OUT = 1, BUF_ALT = 2, BUF_SKIP = 3 };

@@ -19,19 +19,6 @@ struct pairs_dev {
 // PACKED is a compile-time choice so that the two-array kernels are the
 // same code as without packed support.
 template <bool PACKED>
-__device__ __forceinline__ void pair_get(const pairs_dev &p, uint64_t q, uint32_t &tri, uint32_t &node)
-{
-    if constexpr (PACKED) {
-        const uint32_t w = p.tri[q];
-        tri = p.tri_base + (w & ((1u << CRSH_PACKED_TRI_BITS) - 1u));
-        node = w >> CRSH_PACKED_TRI_BITS;
-    } else {
-        tri = p.tri[q];
-        node = p.node[q];
-    }
-}
-
-template <bool PACKED>
 __device__ __forceinline__ void pair_put(const pairs_dev &p, uint64_t at, uint32_t tri, uint32_t node)
 {
     if constexpr (PACKED) {
