@@ -481,7 +481,9 @@ typedef struct crsh_frame_meta {
  * pair counts, counters summed over frames).  nodes, pairs and hits as in
  * the plain calls.  top_item_capacity bounds the (top node, mesh) items of
  * one top-level pass: the sum over the frames that share a top level of
- * top nodes x meshes.  bundle / merge / levels shape every frame's
+ * top nodes x meshes.  Items may be cut into parts of their triangles for
+ * speed, as many as there is room for (16 to an item where there are few, 4
+ * above 4,096 items); one per item is enough.  bundle / merge / levels shape every frame's
  * hierarchy; hit_block (64, 128 or 256) sets how many level-1 pairs a
  * workgroup of the final tests takes at a time (16 x hit_block at most); it
  * never changes a result.  ws: crsh_batch_ws_size() bytes. */

@@ -8,20 +8,21 @@
 //              is binned by leaf in LDS, each leaf's rays are tested against
 //              its triangles with matrix instructions, and what that filter
 //              cannot reject goes through the test as written (the fused form
-//              reads level-2 pairs and the pass bits of their children).  A hit lowers
-//              the ray's 64-bit (order-mapped t, triangle) key with an atomic
-//              minimum: the closest hit, ties to the lower triangle id.
+//              reads level-2 pairs and the pass bits of their children).  A hit
+//              lowers the ray's 64-bit (order-mapped t, triangle) key with an
+//              atomic minimum: the closest hit, ties to the lower triangle id.
 // k_hit_final  one thread per sorted ray: decode the key, recompute u, v with
 //              the same test, write the result at the ray id.
 // Ray slots: k_hit reads the rays of leaf l at slots l * B + j, j < B, of
 // three packed arrays of 16 bytes a slot: (origin, tmax), (direction, its
 // length) and, with the origin o taken from a point of the scene, (o x direction,
-// |o| |direction|); the interval start t_min is the frame's.  In the plain form slot s is sorted ray s.  In the
-// batched form a frame's rays are bundled B at a time from its own first ray,
-// so only a frame's last leaf can hold fewer than B rays; its slots are padded
-// (zeros, a length of -1) and the closest-hit keys are kept by slot, so the
-// pair loop finds a ray with no per-leaf lookup.  k_hit_final maps each
-// sorted ray back to its slot through its frame's first leaf and first ray.
+// |o| |direction|); the interval start t_min is the frame's.  In the plain form
+// slot s is sorted ray s.  In the batched form a frame's rays are bundled B at a
+// time from its own first ray, so only a frame's last leaf can hold fewer than B
+// rays; its slots are padded (zeros, a length of -1) and the closest-hit keys are
+// kept by slot, so the pair loop finds a ray with no per-leaf lookup.
+// k_hit_final maps each sorted ray back to its slot through its frame's first
+// leaf and first ray.
 #include "batch.hpp"
 #include "intersect.hpp"
 
@@ -174,8 +175,8 @@ __global__ void k_hit_pack(tri_verts V, uint32_t m, hit_tris_ws tri, sorted_rays
 // Batched form: the build's per-node record of a leaf (bd.node_info) holds
 // its ray count and frame, and the frame its interval start.
 //
-// FUSED: the level-1 pairs are not stored; they are the children that the pass
-// bits of the level-2 pairs keep, placed in the leaf runs straight from there.
+// Fused and listed: the level-1 pairs are not stored; they are the children that
+// the pass bits of the level-2 pairs keep, placed in the leaf runs from there.
 //
 // A workgroup takes a chunk of consecutive pairs.  Pairs of one top-level
 // node name a few hundred leaves in triangle order, so a chunk holds many
@@ -193,13 +194,14 @@ __global__ void k_hit_pack(tri_verts V, uint32_t m, hit_tris_ws tri, sorted_rays
 // for det, two for T (see put_tri).  What the filter lets through --
 // (triangle, slot) items -- is queued in LDS and goes through the test as
 // written 64 at a time, so the division and the rest run on full waves and
-// only for the few percent of the tests whose u can pass.  Every count is
-// exact: tests are counted per leaf, u and u-v passes by the exact test.
+// only for the few percent of the tests whose u can pass (more where the filter's
+// error bound is large next to the triangles: see there).  Every count is exact:
+// tests are counted per leaf, u and u-v passes by the exact test.
 //
-// Measured (level-1 pairs of 1920x1080 rays against 492,032 triangles, 15.3 G
-// tests, B = 16): 19.5 ms with one lane per (pair, ray) and no matrix
-// instructions, 7.9 ms so (bounce rays of a 512x512 frame 5.6 to 2.1 ms, 24
-// frames batched 9.5 to 4.3 ms).  97 % of the matrix work is on real pairs.
+// Measured (whole stage, 881.7 M level-1 pairs and 14.1 G tests of a 1920x1080
+// frame, B = 16): 18.2 ms with one lane per (pair, ray) and no matrix
+// instructions, 7.8 ms so (1024x1024 reflections, 1.57 G tests, 2.00 to 1.14 ms,
+// bounce rays of a 512x512 frame 5.6 to 2.1, 24 frames batched 9.5 to 4.3).  97 % of the matrix work is on real pairs.
 // The vector L1 is busiest (three 16-byte reads of a triangle's entry per
 // pair), then vector issue.  On the same pairs: chunks of 8,192 pairs in 512
 // threads 8.2 ms, of 2,048 10.0 ms; reading a step ahead 8.4 ms (registers);
@@ -209,7 +211,8 @@ __global__ void k_hit_pack(tri_verts V, uint32_t m, hit_tris_ws tri, sorted_rays
 // Where a top-level node has more leaves than there are bins, a chunk's pairs
 // still name few of them (256 of 12,700 spanned on average, 128x72 mixed rays, 2 to
 // a leaf, merge factor 4, 8 levels): in windows of 1,024 leaves it was read 7
-// times, 324 us; by the leaves that have pairs once, 212.
+// times, 332 us (whole stage); by the leaves that have pairs once, 179, and 161
+// with a lane per (pair, ray).
 // Where a chunk has at most 256 leaves, each has several bins and the threads of
 // those cut its blocks.  With one bin a leaf, and its one thread to cut up to 1,024
 // blocks, pairs of few leaves took longest: 128x72 mixed rays, 4 to a leaf, 24 M
@@ -219,6 +222,10 @@ __global__ void k_hit_pack(tri_verts V, uint32_t m, hit_tris_ws tri, sorted_rays
 // children there; 1,536 1.96 ms, 1,792 1.91, 2,560 2.17, 3,072 2.18 (more
 // chunks overflow and are taken in halves); parts of what is expected to fit
 // instead of equal ones 2.06 (a small rest each).
+// Listed (merge factors above 4: about one of 16 children kept, here and there
+// all), 256x256 reflections, bundle 2 of 16 nodes, 4 levels, whole call: 4.4 ms
+// with every lane at its own children, 2.9 so, 2.8 with a lane per (child, ray);
+// of 72x48 mixed rays 1.72, 1.10 and 1.01, bundle 16 of 8 2.29, 2.30 and 3.91.
 constexpr uint32_t HIT_THREADS = 256;
 constexpr uint32_t HIT_WAVES = HIT_THREADS / WAVE;
 constexpr uint32_t HIT_PPT = 16;                            // pairs per thread of a chunk
@@ -877,9 +884,9 @@ struct hit_out {
     float *t, *u, *v;
 };
 
-// Batched form: the key of sorted ray s is the smaller of its slot's key and
-// tkey[s] (the level-1 pairs of the fused path test by sorted ray), and is
-// left in tkey[s] as in the plain form.
+// Batched form: the key of sorted ray s is its slot's (all of a call's tests go
+// there, and a batch starts with no hits), and is left in tkey[s] as in the plain
+// form.
 template <bool BATCH>
 __global__ void k_hit_final(sorted_rays R, const float4 *__restrict__ tri, const uint32_t *__restrict__ sorted_ids,
                             float t_min0, unsigned long long *tkey, const unsigned long long *__restrict__ keys,
@@ -908,7 +915,7 @@ __global__ void k_hit_final(sorted_rays R, const float4 *__restrict__ tri, const
     const uint32_t n = min(meta->n_rays, ray_cap);
     const uint32_t ns = BATCH ? batch_slots(meta, B, slot_cap) : 0u;
     for (uint32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < n; s += gridDim.x * blockDim.x) {
-        unsigned long long key = tkey[s];
+        unsigned long long key = BATCH ? ~0ull : tkey[s];
         const uint32_t id = sorted_ids[s];
         if (id >= ray_cap) continue;    // ids come from the sort: never taken
         float t_min = t_min0;
@@ -917,7 +924,7 @@ __global__ void k_hit_final(sorted_rays R, const float4 *__restrict__ tri, const
             t_min = bd.frames[f].t_min;
             const uint32_t rb = bd.fm[f].ray_begin;
             const uint64_t p = (uint64_t)bd.fm[f].level_base[0] * B + (s - rb);
-            if (s >= rb && p < ns) key = min(key, keys[p]);
+            if (s >= rb && p < ns) key = keys[p];
             tkey[s] = key;
         }
         int32_t best = -1;
@@ -1107,7 +1114,7 @@ crsh_status hit_check(const crsh_rays *sorted, const uint32_t *sorted_ids, int32
         set_error("%s: hit capacity below the ray capacity", who);
         return CRSH_ERR_INVALID;
     }
-    // the final tests address ray slots (16 B in each of two arrays) and
+    // the final tests address ray slots (16 B in each of three arrays) and
     // triangles (48 B) by 32-bit byte offsets
     if ((uint64_t)sorted->capacity + (uint64_t)CRSH_MAX_FRAMES * (CRSH_MAX_BUNDLE - 1) > CRSH_HIT_MAX_SLOTS ||
         scene->m > CRSH_HIT_MAX_TRIS) {

@@ -6,12 +6,12 @@
 // count pass of the traversal runs on the level-2 pairs (its pass bits, one
 // per (parent pair, child), land in the workspace) and the final-test kernel
 // reads the level-2 pairs with their pass bits instead of level-1 pairs,
-// binning the children by leaf in LDS: the level-1 pairs are never stored, and neither the scan nor the emit of level 1 runs.  The counters
-// are those of the stage order (level-1 node tests, level-1 pairs formed,
-// ray-triangle tests and how far they got) and so are the closest hits (the
-// same tests, the same minimum).  Level-1 pairs that a top-level pass wrote (a
-// hierarchy whose top is level 1) go through the plain final-test kernel
-// first.
+// binning the children by leaf in LDS: the level-1 pairs are never stored, and
+// neither the scan nor the writing step of level 1 runs.  The counters are those
+// of the stage order (level-1 node tests, level-1 pairs formed, ray-triangle tests
+// and how far they got) and so are the closest hits (the same tests, the same
+// minimum).  Level-1 pairs that a top-level pass wrote (a hierarchy whose top is
+// level 1) go through the plain final-test kernel first.
 #include "traverse.hpp"
 
 namespace crsh {
