@@ -846,13 +846,14 @@ __global__ __launch_bounds__(COUNT_THREADS) void k_level_count_lanes(int32_t par
 // a top node (bundle 4) 6.0 ms with merge factor 8, the traversal 7.2; so 2.7,
 // and with merge factor 4 the traversal 4.2 and 2.8.
 //
-// What bounds it: the tests' arithmetic (1080p frame of 201,632 triangles, the
-// step that tests level 1: vector ALUs 75 % busy, 175 lane instructions per
-// written pair, about 30 a test); the last step (no test) writes and reads
-// pairs at 4.6 TB/s, near the 5.3 TB/s a large copy reaches.  Measured on that
-// frame: steps 1.33 + 2.45 + 5.13 + 8.40 + 4.29 ms and the top emit 0.61, where
-// a count pass and an emit pass per level, each reading the pair list, took
-// 29.1 ms; 1024x1024 reflections 2.07 ms (2.7), 24 frames of a batch 5.3 (7.4).
+// What bounds it: the tests' arithmetic (1920x1080 frame against 482,048
+// triangles, the step that tests level 1: vector issue 80 % busy, 199
+// instructions per 64 written pairs, 46 per 64 tests); the last step (no test)
+// writes and reads pairs at 4.5 TB/s, near the 5.3 TB/s a large copy reaches.
+// Measured on that frame: steps 1.28 + 2.40 + 5.26 + 8.82 + 4.68 ms and the top
+// emit 0.60.  A count pass and an emit pass per level, each reading the pair
+// list, took 29.0 ms for the traversal of another such frame where the steps take
+// 21.1; 1024x1024 reflections 2.07 ms (2.7), 24 frames of a batch 5.3 (7.4).
 // Requesting a tile's inputs a tile ahead is what pays for the fusion (24 to 28
 // ms without; the next 64 pairs' spheres before these are tested: 21.6 to 21.3
 // in all), and 6 waves per SIMD: the compiler's own choice is 4, where only
