@@ -847,11 +847,11 @@ __global__ __launch_bounds__(COUNT_THREADS) void k_level_count_lanes(int32_t par
 // and with merge factor 4 the traversal 4.2 and 2.8.
 //
 // What bounds it: the tests' arithmetic (1920x1080 frame against 482,048
-// triangles, the step that tests level 1: vector issue 80 % busy, 199
+// triangles, the step that tests level 1: vector issue 81 % busy, 199
 // instructions per 64 written pairs, 46 per 64 tests); the last step (no test)
 // writes and reads pairs at 4.5 TB/s, near the 5.3 TB/s a large copy reaches.
-// Measured on that frame: steps 1.28 + 2.40 + 5.26 + 8.82 + 4.68 ms and the top
-// emit 0.60.  A count pass and an emit pass per level, each reading the pair
+// Measured on that frame: steps 1.27 + 2.39 + 5.18 + 8.70 + 4.67 ms and the top
+// emit 0.59.  A count pass and an emit pass per level, each reading the pair
 // list, took 29.0 ms for the traversal of another such frame where the steps take
 // 21.1; 1024x1024 reflections 2.07 ms (2.7), 24 frames of a batch 5.3 (7.4).
 // Requesting a tile's inputs a tile ahead is what pays for the fusion (24 to 28
