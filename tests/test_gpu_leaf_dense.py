@@ -135,6 +135,6 @@ def test_dense_pairs_cost():
         rays, sc, tree = _case(2, F, nodes, 700, 5)
         t = O.traverse(tree, sc)
         k = np.random.default_rng(1).permutation(len(t["pairs"][2][0]))
-        us[F] = _leaf_hit(rays, sc, tree, 2, F, tuple(np.asarray(a)[k] for a in t["pairs"][2]), 6)[2]
+        us[F] = _leaf_hit(rays, sc, tree, 2, F, tuple(np.asarray(a)[k] for a in t["pairs"][2]), 20)[2]
     print(f"[leaf dense] {us[4]:.0f} us at 4 children, {us[16]:.0f} us at 16", flush=True)
     assert us[16] < 1.25 * us[4]
